@@ -240,6 +240,18 @@ int bsp_linear_transposed(const void *U, int udt, int64_t T, int64_t M, int64_t 
                           const int32_t *blk_cnt, const int32_t *blk_ptr, const int32_t *col_idx,
                           const void *vals, const void *bias, void *Z, void *stream);
 
+/* The same call with scratch memory, which makes it several times faster: for 16-bit types and R % 8 == 0 the storage
+ * is expanded into ws and multiplied densely by the matrix cores (fp32 sums, one rounding).  Pruned positions still
+ * meet nothing: a token whose sums are not finite is computed again from the storage alone.  ws: at least
+ * bsp_linear_transposed_workspace_bytes(...) bytes, 256-byte aligned, undefined before and after; calls that may
+ * overlap need one each.
+ * That query returns 0 where no scratch is used; with ws == NULL, or U not 16-byte aligned, the call is
+ * bsp_linear_transposed.  Errors as there, and BSP_ERR_CAPACITY (ws_bytes too small), BSP_ERR_SHAPE (ws alignment). */
+size_t bsp_linear_transposed_workspace_bytes(int udt, int64_t T, int64_t M, int64_t N, int32_t R);
+int bsp_linear_transposed_ws(const void *U, int udt, int64_t T, int64_t M, int64_t N, int32_t R, int32_t k_align,
+                             const int32_t *blk_cnt, const int32_t *blk_ptr, const int32_t *col_idx,
+                             const void *vals, const void *bias, void *Z, void *ws, size_t ws_bytes, void *stream);
+
 /* The same product from the masked dense matrix instead of the compact storage (Sec. 3.1: dX = dY Wp
  * with Wp the matrix after Alg. 1, i.e. W after bsp_mask_weights):
  *   Z[t, n] = bias[n] + sum_m U[t, m] * Wm[m, n]      U: [T, M], Wm: [M, N], Z: [T, N], one dtype udt

@@ -71,6 +71,9 @@ def lib():
     L.bsp_packed_validate.argtypes = [i64, i64, i32, i32, vp, vp, vp, i64, vp, vp]
     L.bsp_linear.argtypes = [vp, C.c_int, i64, i64, i64, i32, i32, vp, vp, vp, vp, vp, vp, vp]
     L.bsp_linear_transposed.argtypes = [vp, C.c_int, i64, i64, i64, i32, i32, vp, vp, vp, vp, vp, vp, vp]
+    L.bsp_linear_transposed_workspace_bytes.argtypes = [C.c_int, i64, i64, i64, i32]
+    L.bsp_linear_transposed_workspace_bytes.restype = sz
+    L.bsp_linear_transposed_ws.argtypes = [vp, C.c_int, i64, i64, i64, i32, i32, vp, vp, vp, vp, vp, vp, vp, sz, vp]
     L.bsp_linear_transposed_dense.argtypes = [vp, C.c_int, i64, i64, i64, vp, vp, vp, vp]
     L.bsp_linear_dvals_workspace_bytes.argtypes = [i64, i64, i32, i64]
     L.bsp_linear_dvals_workspace_bytes.restype = sz
@@ -89,7 +92,7 @@ def lib():
     L.bsp_last_hip_error.restype = C.c_int
     L.bsp_version.restype = C.c_char_p
     for name in ("bsp_group_norms", "bsp_penalty_grad", "bsp_prune_mask", "bsp_pack_count", "bsp_pack",
-                 "bsp_packed_validate", "bsp_linear", "bsp_linear_transposed", "bsp_linear_transposed_dense", "bsp_linear_dvals", "bsp_linear_plan", "bsp_linear_planned", "bsp_linear_planned_fused",
+                 "bsp_packed_validate", "bsp_linear", "bsp_linear_transposed", "bsp_linear_transposed_ws", "bsp_linear_transposed_dense", "bsp_linear_dvals", "bsp_linear_plan", "bsp_linear_planned", "bsp_linear_planned_fused",
                  "bsp_mask_weights",
                  "bsp_group_norms_grad", "bsp_adam_step", "bsp_prune_mask_count"):
         getattr(L, name).restype = C.c_int
@@ -369,9 +372,11 @@ def bsp_linear_transposed(U, p: Packed, bias=None, Z=None):
     if Z is None:
         Z = torch.empty((T, p.N), dtype=U.dtype, device=U.device)
     has = p.total_cols > 0
-    st = lib().bsp_linear_transposed(_ptr(U), _DT[U.dtype], T, M, p.N, p.R, p.k_align, _ptr(p.blk_cnt),
-                                     _ptr(p.blk_ptr), _ptr(p.col_idx) if has else None,
-                                     _ptr(p.vals) if has else None, _ptr(bias), _ptr(Z), _stream())
+    need = lib().bsp_linear_transposed_workspace_bytes(_DT[U.dtype], T, M, p.N, p.R)
+    ws = torch.empty(need, dtype=torch.uint8, device=U.device) if need else None
+    st = lib().bsp_linear_transposed_ws(_ptr(U), _DT[U.dtype], T, M, p.N, p.R, p.k_align, _ptr(p.blk_cnt),
+                                        _ptr(p.blk_ptr), _ptr(p.col_idx) if has else None,
+                                        _ptr(p.vals) if has else None, _ptr(bias), _ptr(Z), _ptr(ws), need, _stream())
     _check(st, "bsp_linear_transposed")
     return Z
 

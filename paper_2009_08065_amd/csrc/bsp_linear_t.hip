@@ -6,6 +6,8 @@
 // pruned groups are row segments of column blocks (the other division of Alg. 1) and the
 // matrix is stored transposed.
 //
+// Without scratch memory, or for R % 8 != 0; otherwise bsp_linear_t_expand.hip is several times faster.
+//
 // Per row-block the product is a small dense one (tokens x R times R x kept columns) whose
 // result is scattered to the kept columns' positions.  A workgroup owns a tile of tokens x a
 // range of output columns as fp32 sums in LDS and walks the row-blocks; the kept columns of a
@@ -18,6 +20,7 @@
 // twelve times the read, add and write.)  No sum leaves the compute unit before it is complete;
 // the tile is rounded once on the way out.
 #include "bsp_common.h"
+#include "bsp_linear_internal.h"
 
 namespace bsp {
 namespace {
@@ -449,10 +452,22 @@ int launch_mfma(dim3 grid, size_t lds, hipStream_t s, const uint16_t *U, int64_t
 
 using namespace bsp;
 
+extern "C" size_t bsp_linear_transposed_workspace_bytes(int udt, int64_t T, int64_t M, int64_t N, int32_t R) {
+    if (!valid_dtype(udt) || T <= 0 || M <= 0 || N <= 0 || R < 1 || R > 64 || M % R != 0) return 0;
+    return linear_t_expand_supported(udt, M, R) ? linear_t_expand_bytes(M, N) : 0;
+}
+
 extern "C" int bsp_linear_transposed(const void *U, int udt, int64_t T, int64_t M, int64_t N, int32_t R,
                                      int32_t k_align, const int32_t *blk_cnt, const int32_t *blk_ptr,
                                      const int32_t *col_idx, const void *vals, const void *bias, void *Z,
                                      void *stream) {
+    return bsp_linear_transposed_ws(U, udt, T, M, N, R, k_align, blk_cnt, blk_ptr, col_idx, vals, bias, Z, nullptr, 0, stream);
+}
+
+extern "C" int bsp_linear_transposed_ws(const void *U, int udt, int64_t T, int64_t M, int64_t N, int32_t R,
+                                        int32_t k_align, const int32_t *blk_cnt, const int32_t *blk_ptr,
+                                        const int32_t *col_idx, const void *vals, const void *bias, void *Z,
+                                        void *ws, size_t ws_bytes, void *stream) {
     if (!U || !blk_cnt || !blk_ptr || !Z) return BSP_ERR_NULL;
     if (!valid_dtype(udt)) return BSP_ERR_DTYPE;
     if (T < 0 || M <= 0 || N <= 0 || R < 1 || R > 64 || M % R != 0) return BSP_ERR_SHAPE;
@@ -465,7 +480,12 @@ extern "C" int bsp_linear_transposed(const void *U, int udt, int64_t T, int64_t 
     // the matrix-core kernel indexes the storage with 32 bits: at most M (N + k_align) values
     const bool mfma_ok = udt != BSP_F32 && R % 4 == 0 && k_align % 8 == 0 && col_idx && vals && aligned(U, 4) &&
                          aligned(vals, 4) && (double)M * (double)(N + 64) < 4.0e9;
-    if (mfma_ok) {
+    if (ws && col_idx && vals && aligned(U, 16) && linear_t_expand_supported(udt, M, R)) {
+        if (ws_bytes < linear_t_expand_bytes(M, N)) return BSP_ERR_CAPACITY;
+        if (!aligned(ws, 256)) return BSP_ERR_SHAPE;
+        const int st = linear_t_expand(U, udt, T, M, N, R, blk_cnt, blk_ptr, col_idx, vals, bias, Z, ws, s);
+        if (st != BSP_OK) return st;
+    } else if (mfma_ok) {
         const int64_t tiles = (T + kTok - 1) / kTok;
         const int64_t wgs = (tiles + 7) / 8 * 8 * ranges;  // whole rounds of the 8 XCDs
         if (wgs >= ((int64_t)1 << 31)) return BSP_ERR_SHAPE;

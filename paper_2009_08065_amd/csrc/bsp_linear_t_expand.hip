@@ -1,0 +1,397 @@
+// The transposed product Z = U Wp (+ bias) (see bsp_linear_t.hip) as a dense product on the expanded matrix, both
+// written here; bf16 / fp16, R % 8 == 0, with a workspace for the expanded matrix.
+//
+// Measured (MI355X, 8192 tokens, R = 16, 5x, both kernels): 4096 x 1024 64 us, 3072 x 1024 51, 1024 x 1024 27,
+// 1024 x 4096 76, against 217 / 171 / 67 / 227 of the scattering kernel; 2304 x 768, R = 8, 2x, 509 tokens: 20 against 337.
+//
+// Why dense: the result of a row-block's small product has to be scattered to the kept columns' positions, and an
+// addition to a scattered position costs an LDS read and write of 4 bytes for R multiply-adds.  That bounds the
+// scattering kernel of bsp_linear_t.hip near 160 TFLOP/s of useful work for R = 16, and it reached 60.  Multiplying
+// the pruned zeros as well costs 1 / density times the products, but the sums stay in registers.
+//
+// Two kernels: expand_kernel writes Wp as matrix-core operands, tile_kernel multiplies.
+//
+// A pruned weight must not meet U: 0 times an infinite input would be NaN.  Every column of a token with a
+// non-finite input gets a non-finite sum here, so sums that are all finite are the right ones, and a token with a
+// non-finite sum is computed again from the compact storage alone (recompute_token).
+#include "bsp_common.h"
+#include "bsp_linear_internal.h"
+#include "bsp_mfma_device.h"
+
+namespace bsp {
+namespace {
+
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+
+constexpr int kThreadsX = 256;
+constexpr int kRing = 4;       // stages of U in LDS
+constexpr int kStageK = 64;    // rows of the matrix per stage
+constexpr int kRowBytes = 2 * kStageK;
+constexpr int kColPad = 256;   // columns of the expanded matrix are padded to whole workgroup tiles
+constexpr uint32_t kRangeGroup = 4;
+constexpr int kFrag = 1024;    // bytes of an operand of v_mfma_f32_32x32x16: 32 columns x 16 rows
+
+template <int DT>
+__device__ __forceinline__ f32x16 mfma32(uint4 a, uint4 b, f32x16 c) {
+    if constexpr (DT == BSP_BF16)
+        return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c,
+                                                       0, 0, 0);
+    else
+        return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0,
+                                                      0, 0);
+}
+
+// ---------------------------------------------------------------------------------------
+// Expansion.  The expanded matrix is stored as operands: fragment (n / 32, m / 16) at (n / 32) frags_m + m / 16, lane l
+// of it holding column n % 32 = l % 32, rows 8 (l / 32) .. + 7 of the 16.  One workgroup per row-block, 256 columns and
+// 16 of its rows: an inverse map (column -> kept position) in LDS, then one 16-byte piece per thread and 8 rows, its
+// values gathered down the panel (neighbouring kept columns are neighbouring positions).  It is a chain of four loads
+// that wait for each other, so what counts is that all of them are in flight at once: 1024 columns per workgroup
+// took 9 us for the BERT-large matrices.
+// ---------------------------------------------------------------------------------------
+__global__ __launch_bounds__(kThreadsX) void expand_kernel(int32_t R, int32_t B, int32_t frags_m,
+                                                           const int32_t *__restrict__ blk_cnt,
+                                                           const int32_t *__restrict__ blk_ptr,
+                                                           const int32_t *__restrict__ col_idx,
+                                                           const uint16_t *__restrict__ vals, uint8_t *__restrict__ out) {
+    __shared__ int32_t place[kColPad];
+    const int tid = threadIdx.x, b = blockIdx.x, c0 = blockIdx.y * kColPad, r0 = blockIdx.z * 16;
+    place[tid] = -1;
+    const int64_t base = blk_ptr[b];
+    const int kp = (int)(blk_ptr[b + 1] - base), k = blk_cnt[b];
+    __syncthreads();
+    for (int p = tid; p < k; p += kThreadsX) {
+        const int c = col_idx[base + p] - c0;
+        if ((unsigned)c < (unsigned)kColPad) place[c] = p;
+    }
+    __syncthreads();
+    const int p = place[tid], n = c0 + tid;
+    const uint16_t *v = vals + ((int64_t)R * base + (int64_t)r0 * kp + (p < 0 ? 0 : p));
+    uint8_t *column = out + (int64_t)(n >> 5) * frags_m * kFrag + (n & 31) * 16;
+    const int o0 = (b * R + r0) >> 3;
+#pragma unroll
+    for (int o = 0; o < 2; ++o) {
+        if (r0 + 8 * o >= R) break;  // uniform (R is a multiple of 8)
+        uint32_t d[4] = {0u, 0u, 0u, 0u};
+        if (p >= 0) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                d[j] = v[(int64_t)(8 * o + 2 * j) * kp] | ((uint32_t)v[(int64_t)(8 * o + 2 * j + 1) * kp] << 16);
+        }
+        *reinterpret_cast<uint4 *>(column + (int64_t)((o0 + o) >> 1) * kFrag + (((o0 + o) & 1) << 9)) = make_uint4(d[0], d[1], d[2], d[3]);
+    }
+    if (b == B - 1 && blockIdx.z == 0)  // the zero rows that fill the last stage
+        for (int o = (B * R) >> 3; o < 2 * frags_m; ++o)
+            *reinterpret_cast<uint4 *>(column + (int64_t)(o >> 1) * kFrag + ((o & 1) << 9)) = make_uint4(0u, 0u, 0u, 0u);
+}
+
+// One token's sums over the kept positions alone, for columns cr0 .. cr0 + ncol - 1, into row[] (every thread of
+// the workgroup calls it; sums: ncol floats of LDS).
+template <int DT>
+__device__ __forceinline__ void recompute_token(const uint16_t *__restrict__ u, int64_t B, int32_t R,
+                                                const int32_t *__restrict__ blk_cnt,
+                                                const int32_t *__restrict__ blk_ptr,
+                                                const int32_t *__restrict__ col_idx, const uint16_t *__restrict__ vals,
+                                                const void *__restrict__ bias, int cr0, int ncol, float *sums,
+                                                uint16_t *row) {
+    const int tid = threadIdx.x;
+    for (int c = tid; c < ncol; c += kThreadsX) sums[c] = 0.0f;
+    for (int64_t b = 0; b < B; ++b) {
+        __syncthreads();
+        const int64_t base = blk_ptr[b];
+        const int kp = (int)(blk_ptr[b + 1] - base), k = blk_cnt[b];
+        for (int p = tid; p < k; p += kThreadsX) {
+            const int c = col_idx[base + p] - cr0;
+            if ((unsigned)c >= (unsigned)ncol) continue;
+            float acc = 0.0f;
+            for (int r = 0; r < R; ++r)
+                acc = __builtin_fmaf(elem<DT>::load(u, b * R + r), elem<DT>::load(vals, R * base + (int64_t)r * kp + p), acc);
+            sums[c] += acc;  // the kept columns of a row-block are distinct
+        }
+    }
+    __syncthreads();
+    for (int c = tid; c < ncol; c += kThreadsX)
+        row[c] = (uint16_t)elem<DT>::bits(sums[c] + (bias ? elem<DT>::load(bias, cr0 + c) : 0.0f));
+    __syncthreads();
+}
+
+// ---------------------------------------------------------------------------------------
+// The product.  A workgroup of 4 wavefronts owns 32 FT tokens x 128 FN columns and walks the rows in stages of 64.  U
+// goes through LDS ([token][64], 128 bytes per row, 16-byte pieces rotated so that the operand reads meet all
+// banks); the expanded weights are stored as operands and every wavefront has its own columns, so it loads them
+// straight into registers: through LDS as well, a stage of the 128 x 256 tile would move 144 KiB through it in the
+// 1024 clocks that its products take, more than the 128 bytes per clock it has.
+// While stage s is multiplied, stage s + 2 of U is written to LDS, stage s + 4 requested, and the weights of stages
+// s + 1 to s + 3 are on their way.  On the 4096 x 1024 matrix a stage takes 1490 clocks, 1024 of them with the matrix
+// cores busy (57 us, 1.2 PFLOP/s of dense work); with the loads of a stage issued in a row it was 2020, with 2-way bank
+// conflicts in the operand reads and the weights one stage ahead 2300.
+// ---------------------------------------------------------------------------------------
+template <int DT, int FT, int FN>
+__global__ __launch_bounds__(kThreadsX, 1) void tile_kernel(
+    const uint16_t *__restrict__ U, int64_t T, int32_t M, int32_t N, int32_t B, int32_t R, int32_t frags_m,
+    const uint8_t *__restrict__ W, const int32_t *__restrict__ blk_cnt,
+    const int32_t *__restrict__ blk_ptr, const int32_t *__restrict__ col_idx, const uint16_t *__restrict__ vals,
+    const void *__restrict__ bias, void *__restrict__ Z) {
+    constexpr int TT = 32 * FT, NN = 128 * FN;
+    constexpr int kUBytes = TT * kRowBytes;
+    constexpr int kPitch = NN * 2 + 16;  // bytes of a token's row in the output tile
+    constexpr int kPieces = FT;          // 16-byte pieces of U per thread and stage
+    extern __shared__ __align__(16) uint8_t smem[];
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l32 = lane & 31, kh = lane >> 5;
+    // Workgroup ids go round the 8 XCDs, each with an L2 of its own: id % 8 names the XCD, which owns the token tiles
+    // of that remainder.  It walks them for kRangeGroup column ranges at a time: the 32 workgroups of 128 x 256 that
+    // it runs at once then read 8 tiles of U and 4 ranges of the weights, the least there is to read.
+    const uint32_t nranges = (uint32_t)(N + NN - 1) / NN, ntiles = ((uint32_t)((T + TT - 1) / TT) + 7u) / 8u;  // per XCD
+    const uint32_t place = blockIdx.x >> 3;
+    const uint32_t group = place / (ntiles * kRangeGroup), in_group = place - group * ntiles * kRangeGroup;
+    const uint32_t width = nranges - group * kRangeGroup < kRangeGroup ? nranges - group * kRangeGroup : kRangeGroup;
+    const int64_t t0 = (int64_t)((in_group / width) * 8u + (blockIdx.x & 7u)) * TT;
+    if (t0 >= T) return;  // uniform: before any barrier
+    const int cr0 = (int)(group * kRangeGroup + in_group % width) * NN;
+    const int stages = frags_m / 4;
+
+    f32x16 acc[FN][FT];
+#pragma unroll
+    for (int n = 0; n < FN; ++n)
+#pragma unroll
+        for (int t = 0; t < FT; ++t)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[n][t][i] = 0.0f;
+
+    // as a loader of U: pieces tid % 8 of token rows tid / 8 + 32 i; a token past T reads the last one
+    const uint8_t *utile = reinterpret_cast<const uint8_t *>(U + t0 * M);
+    uint32_t urow[kPieces];
+#pragma unroll
+    for (int i = 0; i < kPieces; ++i) {
+        const int row = (tid >> 3) + 32 * i;
+        urow[i] = (uint32_t)(t0 + row < T ? row : (int)(T - 1 - t0)) * 2u * (uint32_t)M;
+    }
+    const uint32_t st_u = (tid >> 3) * kRowBytes + (((tid & 7) ^ ((tid >> 4) & 7)) << 4);
+    // as a consumer: lane l reads row l % 32 of a 32-row piece, 16-byte piece 2 kk + l / 32
+    const uint32_t lane_cell = l32 * kRowBytes + ((kh ^ ((l32 >> 1) & 7)) << 4);
+    const uint8_t *wcol = W + (int64_t)(cr0 / 32 + wave * FN) * frags_m * kFrag;  // uniform
+    const uint32_t lane16 = lane * 16;
+
+    u32x4 ru[2][kPieces];      // U of two stages on its way to LDS
+    uint4 wf[kRing][FN][4];    // weights of this stage and the next three
+    uint4 uf[2][FT];           // U of this quarter of a stage and the next
+    auto ask_u = [&](auto slot, auto piece, int stage) {
+        constexpr int s = decltype(slot)::value, I = decltype(piece)::value;
+        if constexpr (I < kPieces) {
+            const int k = stage * kStageK + 8 * (tid & 7);
+            const uint32_t kb = 2u * (uint32_t)(k < M - 8 ? k : M - 8);  // past the last row: any value, times zero
+            ru[s & 1][I] = *reinterpret_cast<const u32x4 *>(utile + (urow[I] + kb));
+        }
+    };
+    auto put_u = [&](auto slot, auto piece) {
+        constexpr int s = decltype(slot)::value, I = decltype(piece)::value;
+        if constexpr (I < kPieces) *reinterpret_cast<u32x4 *>(smem + st_u + s * kUBytes + I * 32 * kRowBytes) = ru[s & 1][I];
+    };
+    auto ask_w = [&](auto slot, auto n, auto quarter, int stage) {
+        constexpr int s = decltype(slot)::value, NI = decltype(n)::value, KK = decltype(quarter)::value;
+        const int at = stage < stages ? stage : stages - 1;
+        wf[s][NI][KK] = *reinterpret_cast<const uint4 *>(wcol + ((int64_t)NI * frags_m + 4 * at) * kFrag + (lane16 + KK * kFrag));
+    };
+    auto fetch = [&](auto slot, auto quarter, auto t) {
+        constexpr int s = decltype(slot)::value, kk = decltype(quarter)::value, TI = decltype(t)::value;
+        uf[kk & 1][TI] =
+            *reinterpret_cast<const uint4 *>(smem + (lane_cell ^ (kk << 5)) + s * kUBytes + TI * 32 * kRowBytes);
+    };
+    // every LDS write of the wavefront is done and its reads have returned; its loads stay on their way
+    auto stage_end = [] { asm volatile("s_waitcnt lgkmcnt(0)\n s_barrier" ::: "memory"); };
+    using I0 = std::integral_constant<int, 0>;
+    using I1 = std::integral_constant<int, 1>;
+
+    static_for<0, 2>([&](auto j) { static_for<0, kPieces>([&](auto i) { ask_u(j, i, j); }); });
+    static_for<0, 3>([&](auto s) {
+        static_for<0, FN>([&](auto n) { static_for<0, 4>([&](auto kk) { ask_w(s, n, kk, s); }); });
+    });
+    static_for<0, kPieces>([&](auto i) { put_u(I0{}, i); ask_u(I0{}, i, 2); });
+    static_for<0, kPieces>([&](auto i) { put_u(I1{}, i); ask_u(I1{}, i, 3); });
+    stage_end();
+    static_for<0, FT>([&](auto t) { fetch(I0{}, I0{}, t); });
+    // A stage is four quarters of 16 rows.  Between the products of a quarter go the reads of the next quarter's U, the
+    // loads of one quarter of the weights of stage s + 3, and a piece of U: stage s + 2 to LDS, stage s + 4 asked for.
+    // One at a time: the four wavefronts run in step, and loads issued in a row wait for each other with the matrix
+    // cores idle.  (Left to itself the compiler moves the reads behind the products and waits for them.)
+    auto stage = [&](auto j, int s) {
+        constexpr int J = decltype(j)::value;
+        using S2 = std::integral_constant<int, (J + 2) % kRing>;
+        using S3 = std::integral_constant<int, (J + 3) % kRing>;
+        static_for<0, 4>([&](auto quarter) {
+            constexpr int KK = decltype(quarter)::value;
+            using NextQ = std::integral_constant<int, (KK + 1) % 4>;
+            using NextS = std::integral_constant<int, (J + (KK + 1) / 4) % kRing>;
+            constexpr int kProducts = FN * FT, kOthers = FT + FN + 2;
+            static_for<0, kProducts>([&](auto i) {
+                constexpr int I = decltype(i)::value, NI = I / FT, TI = I % FT;
+                acc[NI][TI] = mfma32<DT>(wf[J][NI][KK], uf[KK & 1][TI], acc[NI][TI]);
+                static_for<0, kOthers>([&](auto o) {
+                    constexpr int O = decltype(o)::value;
+                    if constexpr (O * kProducts / kOthers == I) {
+                        if constexpr (O < FT) fetch(NextS{}, NextQ{}, o);
+                        else if constexpr (O < FT + FN) ask_w(S3{}, std::integral_constant<int, O - FT>{}, quarter, s + 3);
+                        else if constexpr (O == FT + FN) put_u(S2{}, quarter);
+                        else ask_u(S2{}, quarter, s + 4);
+                    }
+                });
+                __builtin_amdgcn_sched_barrier(0);
+            });
+        });
+        stage_end();
+    };
+    // (whole rounds apart from the rest: a round with exits in its middle would make every wait of the loop a full one)
+    int s0 = 0;
+    for (; s0 + kRing <= stages; s0 += kRing) static_for<0, kRing>([&](auto j) { stage(j, s0 + j); });
+    static_for<0, kRing - 1>([&](auto j) {
+        if (stages % kRing > j) stage(j, s0 + j);  // uniform
+    });
+    __syncthreads();
+
+    const int64_t left = T - t0;
+    // Round into a token-major tile in LDS (the stages' memory), bias added in fp32, then write whole rows.
+    uint8_t *tile = smem;
+    float *sums = reinterpret_cast<float *>(smem + TT * kPitch);
+    uint32_t *flags = reinterpret_cast<uint32_t *>(smem + TT * kPitch + NN * 4);  // one bit per token: non-finite sums
+    const int ncol = N - cr0 < NN ? N - cr0 : NN;
+    if (tid < FT) flags[tid] = 0u;
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < FT; ++t) {
+        const int tok = 32 * t + l32;
+        float bad = 0.0f;  // NaN once a sum is not finite
+#pragma unroll
+        for (int n = 0; n < FN; ++n)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int c = (wave * FN + n) * 32 + 8 * q + 4 * kh;  // four consecutive columns of one token
+                float v[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    v[i] = acc[n][t][4 * q + i];
+                    bad = __builtin_fmaf(v[i], 0.0f, bad);
+                    if (bias) v[i] += elem<DT>::load(bias, cr0 + c + i < N ? cr0 + c + i : N - 1);
+                }
+                *reinterpret_cast<uint2 *>(tile + tok * kPitch + c * 2) = make_uint2(cvt_pk<DT>(v[0], v[1]), cvt_pk<DT>(v[2], v[3]));
+            }
+        if (bad != 0.0f) atomicOr(&flags[t], 1u << l32);
+    }
+    __syncthreads();
+    for (int t = 0; t < FT; ++t) {
+        uint32_t todo = flags[t];  // uniform
+        while (todo) {
+            const int tok = 32 * t + __builtin_ctz(todo);
+            todo &= todo - 1;
+            if (tok < left)
+                recompute_token<DT>(U + (t0 + tok) * M, B, R, blk_cnt, blk_ptr, col_idx, vals, bias, cr0, ncol, sums,
+                                    reinterpret_cast<uint16_t *>(tile + tok * kPitch));
+        }
+    }
+    uint16_t *z = (uint16_t *)Z + t0 * N + cr0;
+    if ((N & 7) == 0 && (reinterpret_cast<uintptr_t>(Z) & 15) == 0) {
+        for (int i = tid; i < TT * (NN / 8); i += kThreadsX) {
+            const int tok = i / (NN / 8), c = (i % (NN / 8)) * 8;
+            if (tok < left && c < ncol)
+                *reinterpret_cast<uint4 *>(z + (int64_t)tok * N + c) = *reinterpret_cast<const uint4 *>(tile + tok * kPitch + c * 2);
+        }
+    } else {
+        for (int i = tid; i < TT * NN; i += kThreadsX) {
+            const int tok = i / NN, c = i % NN;
+            if (tok < left && c < ncol)
+                z[(int64_t)tok * N + c] = *reinterpret_cast<const uint16_t *>(tile + tok * kPitch + c * 2);
+        }
+    }
+}
+
+template <int FT, int FN>
+constexpr size_t tile_lds() {
+    constexpr size_t stages = (size_t)kRing * 32 * FT * kRowBytes;
+    constexpr size_t out = (size_t)32 * FT * (128 * FN * 2 + 16) + 128 * FN * 4 + 4 * FT;
+    return stages > out ? stages : out;
+}
+
+// Which tile: 128 x 256 (ft 4, fn 2), 128 x 128 (4, 1) or 64 x 128 (2, 1).  The larger a tile, the more products a
+// loaded operand serves, but one workgroup of the largest fills a compute unit, so what it cannot overlap shows: its
+// start and end (9 us) and the idle units of the last round.  The estimates are microseconds fitted to what was
+// measured at 512 to 8192 tokens of 768 to 4096 rows and columns: per stage 0.70, 0.46 (two on a unit together 1.03)
+// and 0.36 (two 0.62, four 1.25).  For example (MI355X, with the expansion): 4096 x 1024, 8192 tokens 64 / 73 / 85;
+// 1024 x 4096, 8192 tokens 84 / 76 / 95; 3072 x 768, 4096 tokens 42 / 31 / 36; 2304 x 768, 509 tokens 34 / 25 / 20.
+struct Tile {
+    int ft, fn;
+};
+
+Tile choose_tile(int64_t T, int64_t M, int64_t N) {
+    const double stages = (double)((M + kStageK - 1) / kStageK);
+    auto count = [&](int tt, int nn) { return (double)((T + tt - 1) / tt) * (double)((N + nn - 1) / nn) / 256.0; };  // per unit
+    const double a = count(128, 256), b = count(128, 128), c = count(64, 128);
+    const double ta = __builtin_ceil(a) * (0.70 * stages + 9.0);
+    const double tb = (b <= 1.0 ? 0.46 : 0.515 * (b < 1.8 ? 1.8 : b)) * stages + 7.0;
+    const double tc = (c <= 1.0 ? 0.36 : 0.31 * (c < 2.0 ? 2.0 : c)) * stages + 6.0;
+    if (ta <= tb && ta <= tc) return {4, 2};
+    return tb <= tc ? Tile{4, 1} : Tile{2, 1};
+}
+
+size_t expanded_bytes(int64_t M, int64_t N) {
+    return (size_t)((N + kColPad - 1) / kColPad * kColPad) * (size_t)((M + kStageK - 1) / kStageK * kStageK) * 2;
+}
+
+struct Args {
+    const uint16_t *U;
+    int64_t T;
+    int32_t M, N, B, R;
+    const int32_t *blk_cnt, *blk_ptr, *col_idx;
+    const uint16_t *vals;
+    const void *bias;
+    void *Z, *ws;
+    hipStream_t s;
+};
+
+template <int DT, int FT, int FN>
+int launch_tiles(const Args &a, int frags_m) {
+    constexpr size_t lds = tile_lds<FT, FN>();
+    auto k = tile_kernel<DT, FT, FN>;
+    if (lds > 65536) {  // (asking again is harmless)
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) {
+            set_last_hip_error((int)e);
+            return BSP_ERR_HIP;
+        }
+    }
+    const int64_t tiles = (a.T + 32 * FT - 1) / (32 * FT), ranges = (a.N + 128 * FN - 1) / (128 * FN);
+    const int64_t wgs = (tiles + 7) / 8 * 8 * ranges;  // whole rounds of the 8 XCDs
+    if (wgs >= ((int64_t)1 << 31)) return BSP_ERR_SHAPE;
+    k<<<dim3((unsigned)wgs), kThreadsX, lds, a.s>>>(a.U, a.T, a.M, a.N, a.B, a.R, frags_m, (const uint8_t *)a.ws, a.blk_cnt,
+                                                    a.blk_ptr, a.col_idx, a.vals, a.bias, a.Z);
+    return BSP_OK;
+}
+
+template <int DT>
+int launch_all(const Args &a) {
+    const Tile c = choose_tile(a.T, a.M, a.N);
+    const int npad = (a.N + kColPad - 1) / kColPad * kColPad, frags_m = (a.M + kStageK - 1) / kStageK * 4;
+    expand_kernel<<<dim3((unsigned)a.B, (unsigned)(npad / kColPad), (unsigned)((a.R + 15) / 16)), kThreadsX, 0, a.s>>>(
+        a.R, a.B, frags_m, a.blk_cnt, a.blk_ptr, a.col_idx, a.vals, (uint8_t *)a.ws);
+    if (c.ft == 2) return launch_tiles<DT, 2, 1>(a, frags_m);
+    return c.fn == 2 ? launch_tiles<DT, 4, 2>(a, frags_m) : launch_tiles<DT, 4, 1>(a, frags_m);
+}
+
+}  // namespace
+
+// (a tile's rows of U are addressed with 32-bit byte offsets)
+bool linear_t_expand_supported(int udt, int64_t M, int32_t R) {
+    return udt != BSP_F32 && R % 8 == 0 && M < ((int64_t)1 << 23);
+}
+
+size_t linear_t_expand_bytes(int64_t M, int64_t N) { return expanded_bytes(M, N); }
+
+int linear_t_expand(const void *U, int udt, int64_t T, int64_t M, int64_t N, int32_t R, const int32_t *blk_cnt,
+                    const int32_t *blk_ptr, const int32_t *col_idx, const void *vals, const void *bias, void *Z,
+                    void *ws, hipStream_t s) {
+    const Args a = {(const uint16_t *)U, T, (int32_t)M, (int32_t)N, (int32_t)(M / R), R, blk_cnt, blk_ptr, col_idx,
+                    (const uint16_t *)vals, bias, Z, ws, s};
+    return udt == BSP_BF16 ? launch_all<BSP_BF16>(a) : launch_all<BSP_F16>(a);
+}
+
+}  // namespace bsp

@@ -3,6 +3,8 @@
 Bars: bit-exact for sums of squares, norms, reweighting factors, gradients, masks and the
 compact storage; for Y, |y - y_oracle| <= tol * (|y_oracle| + rms(y_oracle)) with tol = 2e-2
 for bf16 / fp16 and 1e-5 for fp32."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -676,6 +678,36 @@ def test_linear_transposed_is_the_adjoint_of_the_layer_and_skips_pads():
     fin = np.isfinite(Zi_ref)
     assert fin[3].sum() > 0 and (~fin[3]).sum() > 0
     assert_y_close(np.where(fin, Zi, 0.0), np.where(fin, Zi_ref, 0.0), "bf16")
+
+
+@pytest.mark.parametrize("dtype,R,T,M,N,p_keep,k_align", [
+    ("bf16", 16, 1, 16, 8, 0.5, 32), ("bf16", 8, 64, 64, 128, 0.3, 1), ("f16", 8, 65, 72, 129, 0.3, 8),
+    ("bf16", 24, 63, 264, 255, 0.9, 16), ("f16", 64, 129, 192, 257, 0.2, 32),   # 64 x 128 tiles and their edges
+    ("bf16", 8, 8001, 136, 2001, 0.2, 32),                                      # 128 x 128, rows past the last stage
+    ("f16", 16, 8190, 1008, 1000, 0.2, 32)])                                    # 128 x 256
+def test_linear_transposed_expanded_tiles(dtype, R, T, M, N, p_keep, k_align):
+    """The dense product on the expanded matrix at the edges of its tiles and stages; an infinite input in the last
+    token reaches the kept columns alone; and the call without scratch memory gives the same sums."""
+    U = wl.normal(R * 91 + T, (T, M), 1.0, dtype)
+    U[T - 1, M - 3] = np.inf
+    W = wl.normal(R * 92 + T, (M, N), 0.02, dtype)
+    zb = wl.normal(R * 93 + T, (N,), 0.5, dtype)
+    keep = wl.bernoulli_keep_mask(T + N + 9, M // R, N, p_keep)
+    p_ref = orc.pack(W, R, keep, k_align, CODE[dtype])
+    p = bsp.bsp_pack(dev(W, dtype), R, torch.from_numpy(keep).cuda(), k_align)
+    Ud, bd = dev(U, dtype), dev(zb, dtype)
+    Z = bsp.bsp_linear_transposed(Ud, p, bd)
+    Zs = torch.empty_like(Z)
+    at = [ctypes.c_void_p(x.data_ptr()) for x in (p.blk_cnt, p.blk_ptr, p.col_idx, p.vals, bd, Zs)]
+    assert bsp.lib().bsp_linear_transposed(ctypes.c_void_p(Ud.data_ptr()), CODE[dtype], T, M, N, R, k_align, *at, None) == 0
+    torch.cuda.synchronize()
+    for t0, t1 in ((0, min(T, 40)), (max(0, T - 70), T)):
+        ref, _ = orc.linear_t_packed(U, p_ref, zb, zdt=CODE[dtype], t0=t0, t1=t1, n_threads=16)
+        ref = ref[t0:t1]
+        fin = np.isfinite(ref)
+        for out in (host(Z)[t0:t1], host(Zs)[t0:t1]):
+            assert np.array_equal(np.isnan(out), np.isnan(ref)) and np.array_equal(np.isinf(out), np.isinf(ref))
+            assert_y_close(np.where(fin, out, 0.0), np.where(fin, ref, 0.0), dtype)
 
 
 @pytest.mark.parametrize("C", [16, 32])
