@@ -28,7 +28,7 @@
 namespace bsp {
 namespace {
 
-constexpr int kThreads = 256;
+constexpr int kThreads = 512;
 constexpr int kMaxKp = 4096 + 32;
 constexpr int kMaxChunk = 1024 + 32;  // kept columns of one row-block inside one column chunk, padded
 
@@ -97,7 +97,7 @@ __device__ inline int plan_entry_steps(const PlanShape &P, int w, int e) {
     const int eg = e / (P.nchunks * P.nacc), q = (e / P.nacc) % P.nchunks;
     const int64_t b = plan_block(eg, w, e % P.nacc, P.waves, P.nacc, P.paired != 0);
     // (chunked plans that give every run a step give one to the runs past the layer's last row-block too, so
-    // that all streams of a group have the same shape; their step of zero weights is written by the scan)
+    // that all streams of a group have the same shape; a workgroup of the fill launch writes its zero weights)
     if (b >= P.B) return (P.chunked() && P.min_one) ? 1 : 0;
     // steps of a stored row-block (zero for an empty or malformed one: the same validity test as the count
     // and fill kernels make)
@@ -136,11 +136,10 @@ __device__ inline int plan_start(const PlanShape &P, int ew, int ee) {
 }
 
 // The table of the streams, by one workgroup (its wavefronts take the streams in turn): wptr[w][e] = first step of
-// entry e of stream w, wptr[w][E] = end of stream w; the zero steps of runs past the layer's end; valid offsets for
-// the steps a layer kernel reads past the end of the last stream.
-__device__ inline void plan_write_table(const PlanShape &P, int32_t nfrag, int64_t cap_steps, int32_t slack_steps,
-                                        int32_t *__restrict__ wptr, uint32_t *__restrict__ wfrag,
-                                        uint32_t *__restrict__ xoff) {
+// entry e of stream w, wptr[w][E] = end of stream w; valid offsets for the steps a layer kernel reads past the end of
+// the last stream.
+__device__ inline void plan_write_table(const PlanShape &P, int64_t cap_steps, int32_t slack_steps,
+                                        int32_t *__restrict__ wptr, uint32_t *__restrict__ xoff) {
     __shared__ int totals[kPlanWavesWide];
     const int waves = P.waves, nw = blockDim.x >> 6;  // streams of the plan, wavefronts of this workgroup
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
@@ -171,20 +170,6 @@ __device__ inline void plan_write_table(const PlanShape &P, int32_t nfrag, int64
         int wbase = 0;
         for (int k = 0; k < w; ++k) wbase += totals[k];
         for (int e = lane; e <= E; e += 64) mine[e] += wbase;
-        if (P.chunked() && P.min_one) {
-            // (runs past the layer's end can only be in the last group: its entries close the stream)
-            for (int e = max(0, E - P.nchunks * P.nacc); e < E; ++e) {  // uniform over the wavefront
-                const int eg = e / (P.nchunks * P.nacc);
-                if (plan_block(eg, w, e % P.nacc, waves, P.nacc, P.paired != 0) < P.B) continue;
-                // where the entry starts: the stream's base and the steps of its entries before it (a handful)
-                int64_t gs = wbase;
-                for (int k = 0; k < e; ++k) gs += plan_entry_steps(P, w, k);
-                if (gs < 0 || gs + 1 > cap_steps) continue;
-                for (int f = 0; f < nfrag; ++f)
-                    *reinterpret_cast<uint4 *>(wfrag + (gs * nfrag + f) * 256 + lane * 4) = make_uint4(0u, 0u, 0u, 0u);
-                if (lane < 16) xoff[gs * 16 + lane] = 0u;
-            }
-        }
         // the layer kernel reads a few steps past the end of the last stream: give those steps the
         // LDS offset 0 (their values are never used, but the addresses must be valid)
         if (w == waves - 1) {
@@ -196,7 +181,9 @@ __device__ inline void plan_write_table(const PlanShape &P, int32_t nfrag, int64
 }
 
 // One workgroup per (block of the plan, column chunk): order the chunk's kept columns and write its steps; one more
-// workgroup behind them writes the table of the streams.  virt: the block is made of two stored row-blocks of 8 rows;
+// workgroup behind them writes the table of the streams.  Chunked plans that give every run a step have workgroups
+// for the runs of the last group past the layer's last row-block too.  (The table's workgroup used to write those steps,
+// finding each one's place by a serial walk over its stream: 176 us of a 768 x 3072 layer's plan, now 14.)  virt: the block is made of two stored row-blocks of 8 rows;
 // its kept columns are the union of theirs, and a step's fragment holds the first one's weights in rows 0-7 and the
 // second one's in rows 8-15 (zeros where only the other one keeps the column).  split > 1: the block is a 16-row slab
 // of the stored row-block pb / split: that block's columns, the slab's rows of its panel.
@@ -226,7 +213,7 @@ __global__ __launch_bounds__(kThreads) void plan_fill_kernel(int32_t R, int32_t 
     P.split = split;
     P.waves = waves;
     if (blockIdx.x == gridDim.x - 1) {  // the workgroup behind the row-blocks writes the table of the streams
-        if (blockIdx.y == 0) plan_write_table(P, nfrag, cap_steps, slack_steps, wptr, wfrag, xoff);
+        if (blockIdx.y == 0) plan_write_table(P, cap_steps, slack_steps, wptr, xoff);
         return;
     }
     const int64_t pb = blockIdx.x;  // the plan's block
@@ -242,7 +229,7 @@ __global__ __launch_bounds__(kThreads) void plan_fill_kernel(int32_t R, int32_t 
     // the stored blocks (a malformed one counts as empty)
     int base[2] = {0, 0}, kp[2] = {0, 0}, kb[2] = {0, 0};
     bool ok[2] = {false, false};
-    for (int j = 0; j < nsrc; ++j) {
+    for (int j = 0; pb < B && j < nsrc; ++j) {  // (a run past the layer's last row-block keeps nothing)
         const int64_t sb = virt ? 2 * pb + j : pb / split;
         base[j] = blk_ptr[sb];
         kp[j] = blk_ptr[sb + 1] - base[j];
@@ -504,7 +491,8 @@ extern "C" int bsp_linear_plan(int vdt, int64_t M, int64_t N, int32_t R, int32_t
     // adding up the step counts before it, and one more that writes the table of the streams.
     // a row-block keeps at most N columns, padded to the alignment (at most 64)
     const int32_t cols_cap = (int32_t)(N + 64 < kMaxKp ? (N + 64 + 7) / 8 * 8 : kMaxKp);
-    plan_fill_kernel<<<dim3((unsigned)B + 1, (unsigned)ch.n), kThreads, (size_t)cols_cap * 2 * (virt ? 2 : 1), s>>>(
+    const int64_t filled = ch.n > 1 && min_one ? L.NG * waves * nacc : B;
+    plan_fill_kernel<<<dim3((unsigned)filled + 1, (unsigned)ch.n), kThreads, (size_t)cols_cap * 2 * (virt ? 2 : 1), s>>>(
         R, nf, (int32_t)L.NG, nacc, ch.shift, ch.n, blk_cnt, blk_ptr, col_idx, (const uint16_t *)vals, capacity_cols,
         (int64_t)L.steps, wptr, wfrag, xoff, cols_cap, waves, paired, min_one, virt ? 1 : 0, split, (int32_t)B,
         counted ? steps_bq : nullptr, plan_slack_steps());
