@@ -107,11 +107,13 @@ def _ptr(t: Optional[torch.Tensor], dtype=None):
         raise ValueError("tensor must be a contiguous GPU tensor")
     if dtype is not None and t.dtype != dtype:
         raise ValueError(f"expected dtype {dtype}, got {t.dtype}")
-    return C.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    """The current stream of the current device as an integer.  (torch.cuda.current_stream() builds a Stream object for
+    it: 2.8 of the 9.9 us that a call of bsp_linear_planned took on the host; this takes 0.1.)"""
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _check(st: int, where: str):
