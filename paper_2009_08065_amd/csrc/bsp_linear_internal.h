@@ -14,6 +14,7 @@ struct TiledArgs {
     const uint16_t *X;
     int64_t T, M, N, B;
     int32_t R;
+    int32_t stored_R;         // planned source: rows of the storage's row-blocks (R: of the plan's)
     int32_t npad;             // filled by the launcher: N rounded up to 256 columns
     const int32_t *blk_ptr;
     const int32_t *col_idx;   // canonical source
@@ -37,6 +38,8 @@ int launch_linear_tiled(const TiledArgs &args, bool plan, hipStream_t s);
 int launch_linear_steploop16(const TiledArgs &args, int64_t max_step, hipStream_t s);
 // The same for R = 16 and wider layers (up to 4096 input columns), whose plans are cut into chunks of 512 columns.
 int launch_linear_stream16(const TiledArgs &args, int64_t max_step, hipStream_t s);
+// The kernel for few tokens, same plans: true when it is the faster one for this call and has been launched (status in st).
+bool launch_linear_small16(const TiledArgs &args, int64_t max_step, hipStream_t s, int &st);
 // Column chunks of a plan: layers with more than 1024 (padded) input columns are cut into chunks of
 // 1024 columns, the width of X that fits in LDS next to 64 tokens; narrower layers are one chunk.
 // R = 16: chunks of 512 columns, two of which are in LDS at a time -- one being used, one being filled.  Layers of

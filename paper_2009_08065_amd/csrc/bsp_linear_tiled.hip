@@ -1003,6 +1003,10 @@ int launch_planned(const TiledArgs &a, hipStream_t s) {
                              : 0;
     const int64_t max_step = a.plan_steps - plan_slack_steps();
     if (max_step < 0 || max_step > INT32_MAX) return BSP_ERR_CAPACITY;
+    if constexpr (NFRAG == 1) {
+        int st = BSP_OK;
+        if (a.R == 16 && launch_linear_small16(a, max_step, s, st)) return st;
+    }
     if (chunked) {
         if constexpr (NFRAG == 1) {  // R = 16: the kernel that streams X through LDS beside the products
             if (a.R == 16) return launch_linear_stream16(a, max_step, s);

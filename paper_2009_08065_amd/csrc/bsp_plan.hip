@@ -522,7 +522,7 @@ extern "C" int bsp_linear_planned_fused(const void *X, int xdt, int64_t T, int64
     a.X = (const uint16_t *)X;
     // (pairs of 8-row blocks, slabs of 32-, 48- and 64-row blocks: the plan is the one of blocks of 16 rows)
     const int32_t Re = plan_block_rows(R, M);
-    a.T = T; a.M = M; a.N = N; a.B = M / Re; a.R = Re;
+    a.T = T; a.M = M; a.N = N; a.B = M / Re; a.R = Re; a.stored_R = R;
     a.wptr = (const int32_t *)plan;
     a.wfrag = (const uint8_t *)plan + L.wptr_bytes;
     a.xoff = (const uint32_t *)((const uint8_t *)plan + L.wptr_bytes + L.wfrag_bytes);

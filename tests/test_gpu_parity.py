@@ -559,6 +559,40 @@ def test_linear_fused_epilogue(dtype, R, T, M, N, act, with_res):
         assert_y_close(host(Y), Y_ref, dtype)
 
 
+@pytest.mark.parametrize("dtype,R,M,N,act,with_res", [
+    ("bf16", 16, 592, 512, bsp.ACT_NONE, False), ("f16", 16, 1104, 1000, bsp.ACT_GELU, False),   # one chunk: stores block by block
+    ("bf16", 16, 304, 1536, bsp.ACT_GELU, True), ("f16", 16, 528, 776, bsp.ACT_NONE, True),     # chunks: stores at its end
+    ("bf16", 8, 336, 800, bsp.ACT_NONE, False), ("bf16", 8, 272, 1544, bsp.ACT_NONE, True),     # unions of 8-row blocks
+    ("bf16", 32, 480, 640, bsp.ACT_GELU, False), ("f16", 64, 384, 2600, bsp.ACT_GELU, True),   # 16-row slabs
+    ("bf16", 16, 800, 2560, bsp.ACT_NONE, True)])                                               # several blocks per wavefront
+def test_linear_planned_few_and_many_tokens(dtype, R, M, N, act, with_res):
+    """The same rows as a call of their own (the kernel for few tokens: one row-block or several per workgroup, shared by wavefronts or
+    not, ragged token tiles) and repeated to a large ragged batch (the kernels for many tokens)."""
+    T0 = 139
+    d = wl.layer(7400 + M + N, T0, M, N, dtype)
+    keep = wl.bernoulli_keep_mask(7401 + M, M // R, N, 0.25)
+    keep[0, :] = 0
+    keep[2, :] = 1
+    keep[M // R - 1, N // 3:] = 0                        # the last block keeps nothing of the last chunks
+    res = wl.layer(7402 + M, T0, 16, M, dtype)["X"] if with_res else None
+    p_ref = orc.pack(d["W"], R, keep, 32, CODE[dtype])
+    p = bsp.bsp_pack(dev(d["W"], dtype), R, torch.from_numpy(keep).cuda(), 32)
+    plan, bias, Xd = bsp.bsp_linear_plan(p), dev(d["bias"], dtype), dev(d["X"], dtype)
+    code = orc.ACT_GELU if act else orc.ACT_NONE
+    Y_ref, _ = orc.linear_packed_fused(d["X"], p_ref, d["bias"], act=code, residual=res, ydt=CODE[dtype], n_threads=16)
+    rd = dev(res, dtype) if with_res else None
+    for T in (1, 5, 16, 70, T0):
+        Y = bsp.bsp_linear_planned_fused(Xd[:T].contiguous(), p, plan, bias, act=act,
+                                         residual=rd[:T].contiguous() if with_res else None)
+        assert_y_close(host(Y), Y_ref[:T], dtype)
+    for reps in (4, 11, 37):
+        Y = bsp.bsp_linear_planned_fused(Xd.repeat(reps, 1), p, plan, bias, act=act,
+                                         residual=rd.repeat(reps, 1) if with_res else None)
+        Y = host(Y).reshape(reps, T0, M)
+        for i in range(reps):
+            assert_y_close(Y[i], Y_ref, dtype)
+
+
 def test_linear_fused_epilogue_refuses_what_is_not_fused():
     """Row-blocks of other heights, and a residual for a layer whose kernel stores block by block: an error and
     nothing written."""
