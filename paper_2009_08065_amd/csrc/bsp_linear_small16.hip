@@ -74,19 +74,18 @@ __device__ __forceinline__ void small_copy_in(const uint16_t *__restrict__ X, in
     }
 }
 
-// GELU as in the kernel for narrow layers: erf by 7.1.26 of Abramowitz and Stegun, |v| (1 + erf(|v| / sqrt 2)) / 2 =
-// |v| - |v| h with h = poly(t) exp(-v^2 / 2) / 2, and y = max(v, 0) - |v| h.
-__device__ __forceinline__ float gelu_as(float v) {
-    const float t = __builtin_amdgcn_rcpf(__builtin_fmaf(__builtin_fabsf(v), 0.23164189f, 1.0f));
-    const float u = v * 0.84932180f;  // exp(-v^2 / 2) = 2^(-u^2)
-    const float e = __builtin_amdgcn_exp2f(-(u * u));
-    float p = 0.530702715f;
-    p = __builtin_fmaf(p, t, -0.726576014f);
-    p = __builtin_fmaf(p, t, 0.710706871f);
-    p = __builtin_fmaf(p, t, -0.142248368f);
-    p = __builtin_fmaf(p, t, 0.127414796f);
-    const float h = p * t * e;
-    return __builtin_fmaf(-__builtin_fabsf(v), h, __builtin_fmaxf(v, 0.0f));
+// GELU as in the kernel for narrow layers: y = max(v, 0) - |v| 2^p(|v|), p a fit of log2(erfc(a / sqrt 2) / 2).
+__device__ __forceinline__ float gelu_fit(float v) {
+    const float a = __builtin_fabsf(v);
+    float p = __builtin_fmaf(a, -0x1.740ed2p-19f, 0x1.43f96p-15f);
+    p = __builtin_fmaf(a, p, -0x1.7ed472p-13f);
+    p = __builtin_fmaf(a, p, -0x1.31e992p-13f);
+    p = __builtin_fmaf(a, p, 0x1.cfb2bap-8f);
+    p = __builtin_fmaf(a, p, -0x1.ae1f06p-5f);
+    p = __builtin_fmaf(a, p, -0x1.d639dp-2f);
+    p = __builtin_fmaf(a, p, -0x1.26aedep+0f);
+    p = __builtin_fmaf(a, p, -1.0f);
+    return __builtin_fmaf(-a, __builtin_amdgcn_exp2f(p), __builtin_fmaxf(v, 0.0f));
 }
 
 template <int DT, int NSUB, int NW>
@@ -173,7 +172,7 @@ __global__ __launch_bounds__(NW * 64) void linear_small16_kernel(const uint16_t 
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             y[v] = s[v] + bv[v];
-            if (act == BSP_ACT_GELU) y[v] = gelu_as(y[v]);
+            if (act == BSP_ACT_GELU) y[v] = gelu_fit(y[v]);
             if (residual) {
                 if constexpr (DT == BSP_BF16) y[v] += __uint_as_float(h[v] << 16);
                 else y[v] += (float)__builtin_bit_cast(_Float16, (uint16_t)h[v]);

@@ -593,6 +593,26 @@ def test_linear_planned_few_and_many_tokens(dtype, R, M, N, act, with_res):
             assert_y_close(Y[i], Y_ref, dtype)
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("T", [16, 8192])
+def test_gelu_over_its_range(dtype, T):
+    """GELU of -9 .. 9 and far outside, in the kernel for few tokens and the one for many: zero weights, so the sums are
+    the biases.  Bound: one rounding (half a unit in the last place; of fp16's subnormals below 2^-14), and the
+    approximation's error of 1.5e-7 |v|."""
+    M, N = 1024, 64
+    v = np.concatenate([np.linspace(-9.0, 9.0, M - 4), [-60.0, 60.0, -1e4, 1e4]]).astype(np.float32)
+    v = host(dev(v, dtype)).astype(np.float64)
+    keep = np.zeros((M // 16, N), np.uint8)
+    keep[:, 3] = 1
+    p = bsp.bsp_pack(torch.zeros((M, N), dtype=TDT[dtype], device="cuda"), 16, torch.from_numpy(keep).cuda(), 32)
+    X = torch.ones((T, N), dtype=TDT[dtype], device="cuda")
+    Y = bsp.bsp_linear_planned_fused(X, p, bsp.bsp_linear_plan(p), dev(v.astype(np.float32), dtype), act=bsp.ACT_GELU)
+    ref = orc.epilogue(v, orc.ACT_GELU)[1]
+    Y = host(Y).astype(np.float64)
+    assert np.array_equal(Y, np.broadcast_to(Y[0], Y.shape))
+    assert np.all(np.abs(Y[0] - ref) <= ULP[dtype] / 2 * np.abs(ref) + 2.0 ** -25 * (dtype == "f16") + 1.5e-7 * np.abs(v))
+
+
 def test_linear_fused_epilogue_refuses_what_is_not_fused():
     """Row-blocks of other heights, and a residual for a layer whose kernel stores block by block: an error and
     nothing written."""
