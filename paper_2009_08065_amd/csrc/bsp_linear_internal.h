@@ -121,6 +121,30 @@ inline int64_t plan_groups(int64_t B, int waves, int nacc, bool paired) {
     if (paired) return 2 * ((B + 4 * waves - 1) / (4 * waves));
     return (B + (int64_t)waves * nacc - 1) / ((int64_t)waves * nacc);
 }
+// Steps of a row-block of the plan, over all its chunks, by the caller's bound on the kept columns: those of its stored
+// row-block, or of the union of two that are kept independently.
+inline double plan_steps(const TiledArgs &a) {
+    double cols = (double)a.capacity_cols / (double)(a.M / a.stored_R);
+    if (a.stored_R < a.R) cols = 2.0 * cols - (cols < (double)a.N ? cols * cols / (double)a.N : cols);
+    return cols / 32.0 + 0.5 * plan_chunks(a.N, a.R, a.M).n;
+}
+// Groups of the plan that a workgroup of the kernel for narrow layers walks.  A workgroup fills a compute unit, so
+// what counts is the rounds of 256 workgroups that a launch takes, times a workgroup's copy-in and walk
+// (microseconds fitted to measurements).  Enough strips to reach 256 workgroups was the rule once: 65 token tiles of a
+// 4096 x 1024 layer were 260 workgroups in two rounds, 68 us at 1.43x, and are 195 in one, 46.
+inline double steploop_walk_us(int64_t tiles, int64_t NG, int64_t gps, int64_t N, double steps) {
+    const int64_t wgs = tiles * ((NG + gps - 1) / gps);
+    return (double)((wgs + 255) / 256) * (0.0016 * (double)N + 0.42 * steps * (double)gps);
+}
+inline int64_t steploop_groups(int64_t tiles, int64_t NG, int64_t N, double steps) {
+    // (the fp32 bias of a strip's quads fills what LDS the tile leaves: 4 KiB per two groups, and a strip of gps groups
+    // touches at most gps / 2 + 1 of them)
+    constexpr int64_t max_gps = 14;
+    int64_t best = NG < max_gps ? NG : max_gps;
+    for (int64_t gps = best - 1; gps >= 1; --gps)
+        if (steploop_walk_us(tiles, NG, gps, N, steps) < steploop_walk_us(tiles, NG, best, N, steps)) best = gps;
+    return best;
+}
 // Steps the planned kernel may read past the last step of the storage (values unused).
 int plan_slack_steps();
 

@@ -310,12 +310,8 @@ double estimate_many(const TiledArgs &a, const SmPlan &P, double steps) {
         const double rounds = __builtin_ceil((double)(tiles * P.NG) / 256.0);
         return 5.0 + rounds * (0.4 + 1.5 * P.nq + 0.35 * steps);
     }
-    int64_t strips = (256 + tiles - 1) / tiles;
-    if (strips > P.NG) strips = P.NG;
-    const int64_t gps = (P.NG + strips - 1) / strips;
-    strips = (P.NG + gps - 1) / gps;
-    const double rounds = __builtin_ceil((double)(tiles * strips) / 256.0);
-    return 4.5 + rounds * (0.0016 * (double)a.N + 0.42 * steps * (double)gps);
+    const int64_t gps = steploop_groups(tiles, P.NG, a.N, steps);
+    return 4.5 + steploop_walk_us(tiles, P.NG, gps, a.N, steps);
 }
 
 struct SmShape {
@@ -357,10 +353,7 @@ bool launch_linear_small16(const TiledArgs &a, int64_t max_step, hipStream_t s, 
     P.NG = (int32_t)plan_groups(a.B, P.waves, P.nacc, P.paired != 0);
     P.nq = ch.n;
     P.max_step = (int32_t)max_step;
-    // kept columns of a row-block of the plan: of its stored row-block, or of the union of two (kept independently)
-    double cols = (double)a.capacity_cols / (double)(a.M / a.stored_R);
-    if (a.stored_R < a.R) cols = 2.0 * cols - (cols < (double)a.N ? cols * cols / (double)a.N : cols);
-    const double steps = cols / 32.0 + 0.5 * ch.n;
+    const double steps = plan_steps(a);
 
     SmShape best = {0, 0, 0};
     double best_us = 0.85 * estimate_many(a, P, steps);  // (the estimates' spread: near a tie the other kernels stay)

@@ -162,7 +162,7 @@ namespace {
     "v_fmaak_f32 v70, v68, v70, 0xbf800000\n v_exp_f32 v70, v70\n"                                 \
     "v_max_f32 " V ", 0, " V "\n v_fma_f32 " V ", -v68, v70, " V "\n"
 #define SL_GELU16                                                                                     \
-    "s_mov_b32 s86, 0x7fffffff\n s_mov_b32 s87, 0x3ea7ba05\n"                                         \
+    "s_mov_b32 s87, 0xb63a0769\n v_mov_b32 v75, 0x3821fcb0\n"                                         \
     SL_GELU1("v0") SL_GELU1("v1") SL_GELU1("v2") SL_GELU1("v3") SL_GELU1("v4") SL_GELU1("v5")         \
     SL_GELU1("v6") SL_GELU1("v7") SL_GELU1("v8") SL_GELU1("v9") SL_GELU1("v10") SL_GELU1("v11")       \
     SL_GELU1("v12") SL_GELU1("v13") SL_GELU1("v14") SL_GELU1("v15")
@@ -404,15 +404,8 @@ __global__ __launch_bounds__(kSlWaves * 64) void linear_steploop16_kernel(
 int launch_linear_steploop16(const TiledArgs &a, int64_t max_step, hipStream_t s) {
     const int64_t NG = plan_groups(a.B, kSlWaves, kSlNacc, true);
     const int64_t ntiles = (a.T + 63) / 64;
-    int64_t nstrips = (256 + ntiles - 1) / ntiles;  // enough strips to give every compute unit a workgroup
-    if (nstrips > NG) nstrips = NG;
-    if (nstrips < 1) nstrips = 1;
-    int64_t gps = (NG + nstrips - 1) / nstrips;
-    // the fp32 bias of the strip's quads fills what LDS the tile leaves: 4 KiB per two groups, and a strip of gps
-    // groups touches at most gps / 2 + 1 of them
-    const int64_t max_gps = 14;
-    if (gps > max_gps) gps = max_gps;
-    nstrips = (NG + gps - 1) / gps;
+    const int64_t gps = steploop_groups(ntiles, NG, a.N, plan_steps(a));
+    const int64_t nstrips = (NG + gps - 1) / gps;
     if (ntiles * nstrips >= ((int64_t)1 << 31)) return BSP_ERR_SHAPE;
     const size_t lds = kXTileBytes + (size_t)(gps / 2 + 1) * (4 * kSlWaves * 16 * 4);
     auto go = [&](auto kern, size_t &configured) {
