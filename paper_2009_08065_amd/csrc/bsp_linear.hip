@@ -265,6 +265,9 @@ extern "C" int bsp_linear(const void *X, int xdt, int64_t T, int64_t M, int64_t 
     } else if (xdt == BSP_F32) {
         const int64_t tiles16 = (T + 15) / 16;
         if (tiles16 >= ((int64_t)1 << 31)) return BSP_ERR_SHAPE;
+        if (linear_f32_tile_supported(N, k_align, col_idx, (const float *)vals))
+            return launch_linear_f32_tile((const float *)X, T, M, N, R, blk_ptr, col_idx, (const float *)vals,
+                                          (const float *)bias, (float *)Y, s);
         linear_f32_mfma_kernel<<<dim3((unsigned)tiles16, (unsigned)B, 1), kThreads, 0, s>>>(
             (const float *)X, T, M, N, R, blk_ptr, col_idx, (const float *)vals, (const float *)bias, (float *)Y);
     } else {

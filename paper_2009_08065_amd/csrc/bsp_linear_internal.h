@@ -165,6 +165,12 @@ __host__ __device__ inline uint32_t lds_col_offset4(uint32_t c, uint32_t p) {
 // LDS bank group (8 banks of 4 bytes = one 32-byte row) that column c lands in.
 __host__ __device__ inline uint32_t lds_bank_group(uint32_t c) { return (c >> 2) & 7u; }
 
+// The layer in single precision on its compact storage, from a tile of X in LDS (bsp_linear_f32.hip): whether these
+// arguments can take it, and its launch.  No argument checks of its own.
+bool linear_f32_tile_supported(int64_t N, int32_t k_align, const int32_t *col_idx, const float *vals);
+int launch_linear_f32_tile(const float *X, int64_t T, int64_t M, int64_t N, int32_t R, const int32_t *blk_ptr,
+                           const int32_t *col_idx, const float *vals, const float *bias, float *Y, hipStream_t s);
+
 // The transposed product as a dense one on the expanded matrix (bsp_linear_t_expand.hip), for 16-bit types: whether
 // these arguments can take it, the workspace it needs, and its launch.  No argument checks of its own.
 bool linear_t_expand_supported(int udt, int64_t M, int32_t R);

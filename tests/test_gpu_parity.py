@@ -593,6 +593,26 @@ def test_linear_planned_few_and_many_tokens(dtype, R, M, N, act, with_res):
             assert_y_close(Y[i], Y_ref, dtype)
 
 
+@pytest.mark.parametrize("R,k_align,T,M,N", [
+    (16, 32, 128, 768, 768), (16, 8, 1, 48, 20), (1, 8, 17, 33, 64), (8, 16, 300, 1024, 256), (24, 8, 47, 120, 388),
+    (64, 32, 130, 192, 1024), (5, 64, 31, 35, 100), (16, 32, 1100, 2304, 260),   # 16 units per workgroup
+    (16, 32, 40, 64, 2556), (16, 32, 40, 64, 2560), (16, 1, 40, 64, 512), (16, 32, 40, 64, 510)])  # the last three: direct gather
+def test_linear_f32_tile_and_direct(R, k_align, T, M, N):
+    """Both single-precision kernels on the compact storage: ragged tiles, slabs that are not full, an empty and a full
+    row-block, and an infinite input that only a pruned column would meet."""
+    d = wl.layer(7700 + M + N, T, M, N, "f32")
+    keep = wl.bernoulli_keep_mask(7701 + M, M // R, N, 0.4)
+    keep[0, :] = 0
+    keep[-1, :] = 1
+    X = d["X"].copy()
+    run_layer(X, d["W"], d["bias"], R, keep, k_align, "f32")
+    keep[:, N // 2] = 0
+    p = bsp.bsp_pack(dev(d["W"]), R, torch.from_numpy(keep).cuda(), k_align)
+    clean = bsp.bsp_linear(dev(X), p, dev(d["bias"]))
+    X[T // 2, N // 2] = np.inf
+    assert torch.equal(bsp.bsp_linear(dev(X), p, dev(d["bias"])), clean)
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 @pytest.mark.parametrize("T", [16, 8192])
 def test_gelu_over_its_range(dtype, T):
