@@ -128,13 +128,35 @@ inline double plan_steps(const TiledArgs &a) {
     if (a.stored_R < a.R) cols = 2.0 * cols - (cols < (double)a.N ? cols * cols / (double)a.N : cols);
     return cols / 32.0 + 0.5 * plan_chunks(a.N, a.R, a.M).n;
 }
+// Workgroups of the kernels for many tokens: `units` per token tile.  Workgroup ids go round the 8 XCDs, each with an L2 and
+// 32 compute units of its own, so the units of a tile, which read the same rows of X, take ids of one remainder modulo 8
+// (with less than 8 tiles they spread over all XCDs).  When the units of 25 or 33
+// tiles went to all XCDs, X came from memory eight times: 1024 x 4096 at 1.43x, 1537 tokens 49.8 us, now 44.1;
+// 768 x 3072 in 8-row blocks at 3x, 1537 tokens 31.5 and 27.9.
+__host__ __device__ inline int64_t tile_workgroups(int64_t tiles, int64_t units) {
+    return (tiles >= 8 ? (tiles + 7) / 8 * 8 : tiles) * units;
+}
+__device__ inline void tile_place(uint32_t id, int32_t tiles, int32_t units, int32_t &tile, int32_t &unit) {
+    const uint32_t u = (uint32_t)units;
+    if (tiles >= 8) {
+        const uint32_t at = id >> 3, rows = ((uint32_t)tiles + 7u) >> 3;
+        tile = (int32_t)(at % rows * 8u + (id & 7u));  // (may lie past the last tile)
+        unit = (int32_t)(at / rows);
+    } else {
+        tile = (int32_t)(id / u);
+        unit = (int32_t)(id % u);
+    }
+}
+// Rounds of such a launch whose workgroups fill a compute unit each.
+inline int64_t tile_rounds(int64_t tiles, int64_t units) {
+    return tiles >= 8 ? ((tiles + 7) / 8 * units + 31) / 32 : (tiles * units + 255) / 256;
+}
 // Groups of the plan that a workgroup of the kernel for narrow layers walks.  A workgroup fills a compute unit, so
-// what counts is the rounds of 256 workgroups that a launch takes, times a workgroup's copy-in and walk
+// what counts is the rounds that a launch takes, times a workgroup's copy-in and walk
 // (microseconds fitted to measurements).  Enough strips to reach 256 workgroups was the rule once: 65 token tiles of a
 // 4096 x 1024 layer were 260 workgroups in two rounds, 68 us at 1.43x, and are 195 in one, 46.
 inline double steploop_walk_us(int64_t tiles, int64_t NG, int64_t gps, int64_t N, double steps) {
-    const int64_t wgs = tiles * ((NG + gps - 1) / gps);
-    return (double)((wgs + 255) / 256) * (0.0016 * (double)N + 0.42 * steps * (double)gps);
+    return (double)tile_rounds(tiles, (NG + gps - 1) / gps) * (0.0016 * (double)N + 0.42 * steps * (double)gps);
 }
 inline int64_t steploop_groups(int64_t tiles, int64_t NG, int64_t N, double steps) {
     // (the fp32 bias of a strip's quads fills what LDS the tile leaves: 4 KiB per two groups, and a strip of gps groups
@@ -143,6 +165,22 @@ inline int64_t steploop_groups(int64_t tiles, int64_t NG, int64_t N, double step
     int64_t best = NG < max_gps ? NG : max_gps;
     for (int64_t gps = best - 1; gps >= 1; --gps)
         if (steploop_walk_us(tiles, NG, gps, N, steps) < steploop_walk_us(tiles, NG, best, N, steps)) best = gps;
+    return best;
+}
+// The kernel that streams X: how many of a group's eight streams a workgroup takes, one per computing wavefront.  With
+// fewer of them a wavefront's steps come sooner (0.82 and 0.76 of the time with 4 and 2), so a launch that fits one round
+// of 256 workgroups that way is shorter; a second round costs more than that.  Measured with 8 / 4 / 2, us: 1024 x 4096 at
+// 5x, 2048 tokens 27.7 / 21.9 / 20.5, 4096 tokens 28.6 / 23.6 / 39 (2 rounds), 8192 tokens 32 / 46 / 83; at 1.43x, 4096
+// tokens 55.6 / 47.0 / 83; 2048 x 1536 at 3x, 1024 tokens 16.7 / 12.2 / 11.1; 768 x 768 in 8-row blocks at 3x, 4099 tokens
+// 15.2 / 12.6 / 23.8.
+inline double stream_load(int64_t tiles, int64_t B, int waves) {
+    const int64_t streams = (B + 3) / 4;
+    return (double)tile_rounds(tiles, (streams + waves - 1) / waves) * (waves == 8 ? 1.0 : (waves == 4 ? 0.82 : 0.76));
+}
+inline int stream_waves(int64_t tiles, int64_t B) {
+    int best = 8;
+    for (int w = 4; w >= 2; w /= 2)
+        if (stream_load(tiles, B, w) < stream_load(tiles, B, best)) best = w;
     return best;
 }
 // Steps the planned kernel may read past the last step of the storage (values unused).

@@ -307,8 +307,7 @@ namespace {
 double estimate_many(const TiledArgs &a, const SmPlan &P, double steps) {
     const int64_t tiles = (a.T + 63) / 64;
     if (P.nq > 1) {
-        const double rounds = __builtin_ceil((double)(tiles * P.NG) / 256.0);
-        return 5.0 + rounds * (0.4 + 1.5 * P.nq + 0.35 * steps);
+        return 5.0 + stream_load(tiles, a.B, stream_waves(tiles, a.B)) * (0.4 + 1.5 * P.nq + 0.35 * steps);
     }
     const int64_t gps = steploop_groups(tiles, P.NG, a.N, steps);
     return 4.5 + steploop_walk_us(tiles, P.NG, gps, a.N, steps);

@@ -334,7 +334,9 @@ __global__ __launch_bounds__(kSlWaves * 64) void linear_steploop16_kernel(
     const uint16_t *__restrict__ X, int64_t T, int64_t M, int64_t N, int32_t npad, const int32_t *__restrict__ wptr,
     const uint8_t *__restrict__ wfrag, const uint8_t *__restrict__ xoff, const void *__restrict__ bias,
     void *__restrict__ Y, int32_t ntiles, int32_t groups_per_strip, int32_t NG, int32_t B, int32_t max_step) {
-    const int tile = blockIdx.x % ntiles, strip = blockIdx.x / ntiles;
+    int32_t tile, strip;
+    tile_place(blockIdx.x, ntiles, (NG + groups_per_strip - 1) / groups_per_strip, tile, strip);
+    if (tile >= ntiles) return;
     const int64_t t0 = (int64_t)tile * 64;
     const int g0 = strip * groups_per_strip;
     const int ng = min(groups_per_strip, NG - g0);
@@ -406,12 +408,13 @@ int launch_linear_steploop16(const TiledArgs &a, int64_t max_step, hipStream_t s
     const int64_t ntiles = (a.T + 63) / 64;
     const int64_t gps = steploop_groups(ntiles, NG, a.N, plan_steps(a));
     const int64_t nstrips = (NG + gps - 1) / gps;
-    if (ntiles * nstrips >= ((int64_t)1 << 31)) return BSP_ERR_SHAPE;
+    const int64_t wgs = tile_workgroups(ntiles, nstrips);
+    if (wgs >= ((int64_t)1 << 31)) return BSP_ERR_SHAPE;
     const size_t lds = kXTileBytes + (size_t)(gps / 2 + 1) * (4 * kSlWaves * 16 * 4);
     auto go = [&](auto kern, size_t &configured) {
         int st = raise_lds_limit(kern, lds, configured);
         if (st != BSP_OK) return st;
-        kern<<<dim3((unsigned)(ntiles * nstrips)), dim3(kSlWaves * 64), lds, s>>>(
+        kern<<<dim3((unsigned)wgs), dim3(kSlWaves * 64), lds, s>>>(
             a.X, a.T, a.M, a.N, a.npad, a.wptr, (const uint8_t *)a.wfrag, (const uint8_t *)a.xoff, a.bias, a.Y,
             (int32_t)ntiles, (int32_t)gps, (int32_t)NG, (int32_t)a.B, (int32_t)max_step);
         return check_launch();

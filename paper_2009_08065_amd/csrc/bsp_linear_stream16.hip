@@ -1,7 +1,8 @@
 // The layer kernel for row-blocks of 16 rows and layers of more than 1024 input columns (Sec. 3.1, Sec. 4.4),
 // bf16 / fp16 on gfx950: the X tile streams through LDS in chunks of 512 columns while the products run.
 //
-// A workgroup owns 64 tokens and 32 row-blocks (a group of the plan).  Eight wavefronts compute: each keeps the
+// A workgroup owns 64 tokens and 32 row-blocks (a group of the plan; 16 or 8 where that leaves compute units idle, see
+// stream_waves).  Eight wavefronts (4, 2) compute: each keeps the
 // accumulators of four consecutive row-blocks (128 bytes of a token's output row) across all column chunks and
 // walks, chunk by chunk, the steps of its blocks inside the chunk -- the step loop of the kernel for narrow layers
 // (assembly: operand ring of four steps, hand-counted waits, X fragments of the next step requested between the
@@ -29,7 +30,6 @@ namespace {
 
 constexpr int kStComputeWaves = 8;
 constexpr int kStLoadWaves = 8;
-constexpr int kStThreads = (kStComputeWaves + kStLoadWaves) * 64;
 constexpr int kStNacc = 4;
 constexpr int kStChunk = 512;  // columns
 
@@ -257,20 +257,24 @@ __device__ __forceinline__ void copy_chunks(const uint16_t *__restrict__ X, int6
     }
 }
 
-template <int DT, int ACT, bool RESIDUAL>
-__global__ __launch_bounds__(kStThreads) void linear_stream16_kernel(
+template <int DT, int ACT, bool RESIDUAL, int CW>
+__global__ __launch_bounds__((CW + kStLoadWaves) * 64) void linear_stream16_kernel(
     const uint16_t *__restrict__ X, int64_t T, int64_t M, int64_t N, int32_t npad, const int32_t *__restrict__ wptr,
     const uint8_t *__restrict__ wfrag, const uint8_t *__restrict__ xoff, const void *__restrict__ bias,
     void *__restrict__ Y, int32_t ntiles, int32_t NG, int32_t B, int32_t nq, int32_t max_step,
     const uint16_t *__restrict__ residual) {
-    const int tile = blockIdx.x % ntiles, g = blockIdx.x / ntiles;
+    // the workgroup's streams: CW of the group's eight
+    int32_t tile, unit;
+    tile_place(blockIdx.x, ntiles, ((B + kStNacc - 1) / kStNacc + CW - 1) / CW, tile, unit);
+    if (tile >= ntiles) return;
+    const int first_stream = unit * CW, g = first_stream / kStComputeWaves;
     const int64_t t0 = (int64_t)tile * 64;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
 
-    if (wave >= kStComputeWaves) {
+    if (wave >= CW) {
         // ---- the copying wavefronts: chunk k into half k % 2, handed over by barrier k ----
-        const int j = (int)threadIdx.x - kStComputeWaves * 64;
+        const int j = (int)threadIdx.x - CW * 64;
         // whole tiles of layers whose rows are whole 16-byte pieces take the copy without bounds tests (uniform)
         if (t0 + 64 <= T && (N & 7) == 0) copy_chunks<ChunkRegs16>(X, T, N, npad, nq, t0, j);
         else copy_chunks<ChunkRegs>(X, T, N, npad, nq, t0, j);
@@ -279,11 +283,12 @@ __global__ __launch_bounds__(kStThreads) void linear_stream16_kernel(
 
     // ---- the multiplying wavefronts ----
     const int l16 = lane & 15, G = lane >> 4;
-    const int64_t b0 = ((int64_t)g * kStComputeWaves + wave) * kStNacc;  // first row-block of the wavefront's run
+    const int64_t b0 = ((int64_t)first_stream + wave) * kStNacc;  // first row-block of the wavefront's run
     // step counts of the wavefront's runs, chunk by chunk, kept inside the plan whatever it holds; a run has
     // at least one step (runs of row-blocks past the end of the layer too: their products are never stored)
     // (a stream holds a group's runs chunk after chunk, then the next group's: entry (g * nq + q) * 4 + i)
-    const int32_t *my = wptr + (int64_t)wave * ((int64_t)nq * NG * kStNacc + 1) + (int64_t)g * nq * kStNacc;
+    const int32_t *my = wptr + (int64_t)((first_stream + wave) % kStComputeWaves) * ((int64_t)nq * NG * kStNacc + 1) +
+                        (int64_t)g * nq * kStNacc;
     uint64_t cnt[4] = {0, 0, 0, 0};
     const int first = min(max(my[0], 0), max_step);
     int cur = first;
@@ -417,19 +422,27 @@ int launch_linear_stream16(const TiledArgs &a, int64_t max_step, hipStream_t s) 
     const PlanChunks ch = plan_chunks(a.N, a.R, a.M);
     const int64_t NG = plan_groups(a.B, kStComputeWaves, kStNacc, false);
     const int64_t ntiles = (a.T + 63) / 64;
-    if (ntiles * NG >= ((int64_t)1 << 31) || ch.n > kPlanMaxChunks) return BSP_ERR_SHAPE;
+    const int64_t streams = (a.B + kStNacc - 1) / kStNacc;
+    const int cw = stream_waves(ntiles, a.B);
+    const int64_t wgs = tile_workgroups(ntiles, (streams + cw - 1) / cw);
+    if (wgs >= ((int64_t)1 << 31) || ch.n > kPlanMaxChunks) return BSP_ERR_SHAPE;
     if (a.act != BSP_ACT_NONE && a.act != BSP_ACT_GELU) return BSP_ERR_SHAPE;
     if (a.residual && !aligned(a.residual, 8)) return BSP_ERR_SHAPE;
     const size_t lds = kXTileBytes;
-    auto go = [&](auto dt, auto act, auto res) {
-        auto kern = linear_stream16_kernel<decltype(dt)::value, decltype(act)::value, decltype(res)::value>;
+    auto launch = [&](auto dt, auto act, auto res, auto waves) {
+        auto kern = linear_stream16_kernel<decltype(dt)::value, decltype(act)::value, decltype(res)::value, decltype(waves)::value>;
         static thread_local size_t configured = 0;  // (of this kernel: the closure is instantiated per kernel)
         int st = raise_lds_limit(kern, lds, configured);
         if (st != BSP_OK) return st;
-        kern<<<dim3((unsigned)(ntiles * NG)), dim3(kStThreads), lds, s>>>(
+        kern<<<dim3((unsigned)wgs), dim3((decltype(waves)::value + kStLoadWaves) * 64), lds, s>>>(
             a.X, a.T, a.M, a.N, a.npad, a.wptr, (const uint8_t *)a.wfrag, (const uint8_t *)a.xoff, a.bias, a.Y,
             (int32_t)ntiles, (int32_t)NG, (int32_t)a.B, ch.n, (int32_t)max_step, (const uint16_t *)a.residual);
         return check_launch();
+    };
+    auto go = [&](auto dt, auto act, auto res) {
+        if (cw == 8) return launch(dt, act, res, std::integral_constant<int, 8>{});
+        if (cw == 4) return launch(dt, act, res, std::integral_constant<int, 4>{});
+        return launch(dt, act, res, std::integral_constant<int, 2>{});
     };
     auto with = [&](auto dt) {
         using None = std::integral_constant<int, BSP_ACT_NONE>;
