@@ -218,6 +218,19 @@ int bsp_linear(const void *X, int xdt, int64_t T, int64_t M, int64_t N, int32_t 
                const int32_t *blk_cnt, const int32_t *blk_ptr, const int32_t *col_idx, const void *vals,
                const void *bias, void *Y, void *stream);
 
+/* The same call with scratch memory for layers that keep much (low compression, many tokens): the storage is expanded
+ * into ws and multiplied densely (16-bit types, k_align % 32 == 0; fp32 sums, one rounding).  Pruned positions still meet
+ * nothing: a token whose sums are not finite is computed again from the storage alone.
+ * bsp_linear_workspace_bytes: the bytes this takes for a storage of up to capacity_cols padded kept columns, or 0 where
+ * bsp_linear itself is the faster one; then, or with ws == NULL, the call is bsp_linear.  ws: 256-byte aligned, undefined
+ * before and after; calls that may overlap need one each.  Errors as bsp_linear, and BSP_ERR_CAPACITY (ws_bytes too
+ * small), BSP_ERR_SHAPE (ws alignment). */
+size_t bsp_linear_workspace_bytes(int xdt, int64_t T, int64_t M, int64_t N, int32_t R, int32_t k_align,
+                                  int64_t capacity_cols);
+int bsp_linear_ws(const void *X, int xdt, int64_t T, int64_t M, int64_t N, int32_t R, int32_t k_align,
+                  const int32_t *blk_cnt, const int32_t *blk_ptr, const int32_t *col_idx, const void *vals,
+                  const void *bias, void *Y, void *ws, size_t ws_bytes, void *stream);
+
 /* ---- the transposed product of the pruned layer (Sec. 3.1: with Wp the matrix after Alg. 1
  * the layer is Y = X Wp^T + bias, so the gradient with respect to its input is dX = dY Wp;
  * the same product is the layer itself when the pruned groups are row segments of column

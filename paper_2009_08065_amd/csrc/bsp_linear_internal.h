@@ -217,4 +217,12 @@ int linear_t_expand(const void *U, int udt, int64_t T, int64_t M, int64_t N, int
                     const int32_t *blk_ptr, const int32_t *col_idx, const void *vals, const void *bias, void *Z,
                     void *ws, hipStream_t s);
 
+// The layer as a dense product on the expanded matrix (same file), for 16-bit types, N % 8 == 0, X aligned to 16 bytes:
+// the workspace it needs, whether it is the faster one for these sizes, and its launch.  No argument checks of its own.
+size_t linear_expand_bytes(int64_t M, int64_t N);
+bool linear_expand_pays(int64_t T, int64_t M, int64_t N, int32_t R, int64_t capacity_cols);
+int linear_expand(const void *X, int xdt, int64_t T, int64_t M, int64_t N, int32_t R, const int32_t *blk_cnt,
+                  const int32_t *blk_ptr, const int32_t *col_idx, const void *vals, const void *bias, void *Y, void *ws,
+                  hipStream_t s);
+
 }  // namespace bsp

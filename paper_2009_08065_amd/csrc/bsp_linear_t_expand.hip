@@ -18,6 +18,9 @@
 #include "bsp_linear_internal.h"
 #include "bsp_mfma_device.h"
 
+// The layer itself on its compact storage (bsp_linear_ws) is the same product with the roles of rows and columns changed:
+// Y = X Wp^T, expanded by expand_rows_kernel, for layers that keep so much that the gather of their columns costs more than
+// multiplying the zeros (linear_expand_pays).
 namespace bsp {
 namespace {
 
@@ -85,6 +88,43 @@ __global__ __launch_bounds__(kThreadsX) void expand_kernel(int32_t R, int32_t B,
             *reinterpret_cast<uint4 *>(column + (int64_t)(o >> 1) * kFrag + ((o & 1) << 9)) = make_uint4(0u, 0u, 0u, 0u);
 }
 
+// The same for Wp itself: operand (m / 32, n / 16), lane l of it row m % 32 = l % 32, columns 8 (l / 32) .. + 7 of the 16.
+// One workgroup per row-block, 256 columns and 16 of its rows; row-blocks past the last write the zero rows that fill
+// the last tile.
+__global__ __launch_bounds__(kThreadsX) void expand_rows_kernel(int32_t R, int32_t B, int32_t rows_pad, int32_t frags_n,
+                                                                const int32_t *__restrict__ blk_cnt,
+                                                                const int32_t *__restrict__ blk_ptr,
+                                                                const int32_t *__restrict__ col_idx,
+                                                                const uint16_t *__restrict__ vals, uint8_t *__restrict__ out) {
+    __shared__ int32_t place[kColPad];
+    const int tid = threadIdx.x, b = blockIdx.x, c0 = blockIdx.y * kColPad, r0 = blockIdx.z * 16;
+    place[tid] = -1;
+    const int64_t base = b < B ? blk_ptr[b] : 0;
+    const int kp = b < B ? (int)(blk_ptr[b + 1] - base) : 0, k = b < B ? blk_cnt[b] : 0;
+    __syncthreads();
+    for (int p = tid; p < k; p += kThreadsX) {
+        const int c = col_idx[base + p] - c0;
+        if ((unsigned)c < (unsigned)kColPad) place[c] = p;
+    }
+    __syncthreads();
+    const int r = r0 + (tid & 15), m = b * R + r;
+    if (r >= R || m >= rows_pad) return;
+    const uint16_t *v = vals + ((int64_t)R * base + (int64_t)r * kp);
+    uint8_t *row = out + (int64_t)(m >> 5) * frags_n * kFrag + (m & 31) * 16;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const int o = (tid >> 4) + 16 * j, n8 = (c0 >> 3) + o;  // 8 columns
+        if (n8 >= 2 * frags_n) break;
+        uint32_t d[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int p = place[8 * o + i];
+            if (p >= 0) d[i >> 1] |= (uint32_t)v[p] << (16 * (i & 1));
+        }
+        *reinterpret_cast<uint4 *>(row + (int64_t)(n8 >> 1) * kFrag + ((n8 & 1) << 9)) = make_uint4(d[0], d[1], d[2], d[3]);
+    }
+}
+
 // One token's sums over the kept positions alone, for columns cr0 .. cr0 + ncol - 1, into row[] (every thread of
 // the workgroup calls it; sums: ncol floats of LDS).
 template <int DT>
@@ -115,6 +155,24 @@ __device__ __forceinline__ void recompute_token(const uint16_t *__restrict__ u, 
     __syncthreads();
 }
 
+// The same for the layer: rows cr0 .. cr0 + ncol - 1 of Wp, a thread per row.
+template <int DT>
+__device__ __forceinline__ void recompute_rows(const uint16_t *__restrict__ x, int32_t R, const int32_t *__restrict__ blk_cnt,
+                                               const int32_t *__restrict__ blk_ptr, const int32_t *__restrict__ col_idx,
+                                               const uint16_t *__restrict__ vals, const void *__restrict__ bias, int cr0,
+                                               int ncol, uint16_t *row) {
+    for (int c = threadIdx.x; c < ncol; c += kThreadsX) {
+        const int b = (cr0 + c) / R, r = (cr0 + c) % R;
+        const int64_t base = blk_ptr[b];
+        const int kp = (int)(blk_ptr[b + 1] - base), k = blk_cnt[b];
+        float acc = 0.0f;
+        for (int p = 0; p < k; ++p)
+            acc = __builtin_fmaf(elem<DT>::load(x, col_idx[base + p]), elem<DT>::load(vals, R * base + (int64_t)r * kp + p), acc);
+        row[c] = (uint16_t)elem<DT>::bits(acc + (bias ? elem<DT>::load(bias, cr0 + c) : 0.0f));
+    }
+    __syncthreads();
+}
+
 // ---------------------------------------------------------------------------------------
 // The product.  A workgroup of 4 wavefronts owns 32 FT tokens x 128 FN columns and walks the rows in stages of 64.  U
 // goes through LDS ([token][64], 128 bytes per row, 16-byte pieces rotated so that the operand reads meet all
@@ -126,7 +184,8 @@ __device__ __forceinline__ void recompute_token(const uint16_t *__restrict__ u, 
 // cores busy (57 us, 1.2 PFLOP/s of dense work); with the loads of a stage issued in a row it was 2020, with 2-way bank
 // conflicts in the operand reads and the weights one stage ahead 2300.
 // ---------------------------------------------------------------------------------------
-template <int DT, int FT, int FN>
+// ROWS: the operands are Wp's rows (the layer), U is X and M, N are the layer's columns and rows.
+template <int DT, int FT, int FN, bool ROWS>
 __global__ __launch_bounds__(kThreadsX, 1) void tile_kernel(
     const uint16_t *__restrict__ U, int64_t T, int32_t M, int32_t N, int32_t B, int32_t R, int32_t frags_m,
     const uint8_t *__restrict__ W, const int32_t *__restrict__ blk_cnt,
@@ -284,7 +343,11 @@ __global__ __launch_bounds__(kThreadsX, 1) void tile_kernel(
         while (todo) {
             const int tok = 32 * t + __builtin_ctz(todo);
             todo &= todo - 1;
-            if (tok < left)
+            if constexpr (ROWS) {
+                if (tok < left)
+                    recompute_rows<DT>(U + (t0 + tok) * M, R, blk_cnt, blk_ptr, col_idx, vals, bias, cr0, ncol,
+                                       reinterpret_cast<uint16_t *>(tile + tok * kPitch));
+            } else if (tok < left)
                 recompute_token<DT>(U + (t0 + tok) * M, B, R, blk_cnt, blk_ptr, col_idx, vals, bias, cr0, ncol, sums,
                                     reinterpret_cast<uint16_t *>(tile + tok * kPitch));
         }
@@ -322,13 +385,14 @@ struct Tile {
     int ft, fn;
 };
 
-Tile choose_tile(int64_t T, int64_t M, int64_t N) {
+Tile choose_tile(int64_t T, int64_t M, int64_t N, double *us = nullptr) {
     const double stages = (double)((M + kStageK - 1) / kStageK);
     auto count = [&](int tt, int nn) { return (double)((T + tt - 1) / tt) * (double)((N + nn - 1) / nn) / 256.0; };  // per unit
     const double a = count(128, 256), b = count(128, 128), c = count(64, 128);
     const double ta = __builtin_ceil(a) * (0.70 * stages + 9.0);
     const double tb = (b <= 1.0 ? 0.46 : 0.515 * (b < 1.8 ? 1.8 : b)) * stages + 7.0;
     const double tc = (c <= 1.0 ? 0.36 : 0.31 * (c < 2.0 ? 2.0 : c)) * stages + 6.0;
+    if (us) *us = ta < tb ? (ta < tc ? ta : tc) : (tb < tc ? tb : tc);
     if (ta <= tb && ta <= tc) return {4, 2};
     return tb <= tc ? Tile{4, 1} : Tile{2, 1};
 }
@@ -348,10 +412,10 @@ struct Args {
     hipStream_t s;
 };
 
-template <int DT, int FT, int FN>
+template <int DT, int FT, int FN, bool ROWS>
 int launch_tiles(const Args &a, int frags_m) {
     constexpr size_t lds = tile_lds<FT, FN>();
-    auto k = tile_kernel<DT, FT, FN>;
+    auto k = tile_kernel<DT, FT, FN, ROWS>;
     if (lds > 65536) {  // (asking again is harmless)
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) {
@@ -367,14 +431,18 @@ int launch_tiles(const Args &a, int frags_m) {
     return BSP_OK;
 }
 
-template <int DT>
+template <int DT, bool ROWS>
 int launch_all(const Args &a) {
     const Tile c = choose_tile(a.T, a.M, a.N);
     const int npad = (a.N + kColPad - 1) / kColPad * kColPad, frags_m = (a.M + kStageK - 1) / kStageK * 4;
-    expand_kernel<<<dim3((unsigned)a.B, (unsigned)(npad / kColPad), (unsigned)((a.R + 15) / 16)), kThreadsX, 0, a.s>>>(
-        a.R, a.B, frags_m, a.blk_cnt, a.blk_ptr, a.col_idx, a.vals, (uint8_t *)a.ws);
-    if (c.ft == 2) return launch_tiles<DT, 2, 1>(a, frags_m);
-    return c.fn == 2 ? launch_tiles<DT, 4, 2>(a, frags_m) : launch_tiles<DT, 4, 1>(a, frags_m);
+    if constexpr (ROWS)
+        expand_rows_kernel<<<dim3((unsigned)((npad + a.R - 1) / a.R), (unsigned)((a.M + kColPad - 1) / kColPad), (unsigned)((a.R + 15) / 16)), kThreadsX, 0, a.s>>>(
+            a.R, a.B, npad, frags_m, a.blk_cnt, a.blk_ptr, a.col_idx, a.vals, (uint8_t *)a.ws);
+    else
+        expand_kernel<<<dim3((unsigned)a.B, (unsigned)(npad / kColPad), (unsigned)((a.R + 15) / 16)), kThreadsX, 0, a.s>>>(
+            a.R, a.B, frags_m, a.blk_cnt, a.blk_ptr, a.col_idx, a.vals, (uint8_t *)a.ws);
+    if (c.ft == 2) return launch_tiles<DT, 2, 1, ROWS>(a, frags_m);
+    return c.fn == 2 ? launch_tiles<DT, 4, 2, ROWS>(a, frags_m) : launch_tiles<DT, 4, 1, ROWS>(a, frags_m);
 }
 
 }  // namespace
@@ -391,7 +459,32 @@ int linear_t_expand(const void *U, int udt, int64_t T, int64_t M, int64_t N, int
                     void *ws, hipStream_t s) {
     const Args a = {(const uint16_t *)U, T, (int32_t)M, (int32_t)N, (int32_t)(M / R), R, blk_cnt, blk_ptr, col_idx,
                     (const uint16_t *)vals, bias, Z, ws, s};
-    return udt == BSP_BF16 ? launch_all<BSP_BF16>(a) : launch_all<BSP_F16>(a);
+    return udt == BSP_BF16 ? launch_all<BSP_BF16, false>(a) : launch_all<BSP_F16, false>(a);
+}
+
+size_t linear_expand_bytes(int64_t M, int64_t N) { return expanded_bytes(N, M); }
+
+// Microseconds of both forms, fitted to 64 to 8192 tokens of 256 to 4096 rows and columns at 1.43x to 5x.  The gather takes
+// a step per 32 kept columns of a row-block and token tile, and its tiles shrink with the layer's width (64 tokens up to
+// 1024 columns, 16 up to 4096); the dense form an expansion, its tiles and the output.  Measured, gather / dense: 1024 x 4096,
+// 8192 tokens, R = 16 at 1.43x 342 / 81, at 5x 115 / 72, 2048 tokens at 5x 41 / 34 (stays), 512 at 5x 19 / 32;
+// 4096 x 1024, 8192 tokens, R = 16 at 1.43x 125 / 107, at 3x 76 / 103, R = 8 at 2x 167 / 104; 3072 x 768, 4096 tokens at 3x
+// 29 / 46.
+bool linear_expand_pays(int64_t T, int64_t M, int64_t N, int32_t R, int64_t capacity_cols) {
+    const int64_t npad = (N + 255) / 256 * 256, tok = npad <= 1024 ? 64 : (npad <= 2048 ? 32 : 16);
+    const double per_step = (tok == 64 ? 0.040 : (tok == 32 ? 0.035 : 0.030)) * (R <= 16 ? 1.0 : (R <= 32 ? 2.1 : 4.0));
+    const double gather = 8.0 + per_step * (double)capacity_cols / 32.0 * (double)((T + tok - 1) / tok) / 256.0;
+    double tiles;
+    choose_tile(T, N, M, &tiles);
+    return 8.0 + tiles + (double)T * (double)M * 0.5e-6 < 0.9 * gather;
+}
+
+int linear_expand(const void *X, int xdt, int64_t T, int64_t M, int64_t N, int32_t R, const int32_t *blk_cnt,
+                  const int32_t *blk_ptr, const int32_t *col_idx, const void *vals, const void *bias, void *Y, void *ws,
+                  hipStream_t s) {
+    const Args a = {(const uint16_t *)X, T, (int32_t)N, (int32_t)M, (int32_t)(M / R), R, blk_cnt, blk_ptr, col_idx,
+                    (const uint16_t *)vals, bias, Y, ws, s};
+    return xdt == BSP_BF16 ? launch_all<BSP_BF16, true>(a) : launch_all<BSP_F16, true>(a);
 }
 
 }  // namespace bsp

@@ -613,6 +613,45 @@ def test_linear_f32_tile_and_direct(R, k_align, T, M, N):
     assert torch.equal(bsp.bsp_linear(dev(X), p, dev(d["bias"])), clean)
 
 
+@pytest.mark.parametrize("dtype,R,T,M,N", [
+    ("bf16", 16, 1, 16, 32), ("f16", 8, 130, 200, 520), ("bf16", 24, 67, 264, 1000), ("f16", 64, 200, 640, 2056),
+    ("bf16", 1, 70, 37, 264), ("bf16", 16, 2100, 1040, 776), ("f16", 32, 4200, 2080, 128), ("bf16", 16, 2048, 768, 3072)])
+def test_linear_expanded(dtype, R, T, M, N):
+    """The layer with a workspace (dense on the expanded storage): every tile shape, rows and columns that fill neither a
+    fragment nor a stage, an empty and a full row-block; a pruned column's infinite input
+    changes no other token's bits and leaves its own token right."""
+    d = wl.layer(7800 + M + N, T, M, N, dtype)
+    keep = wl.bernoulli_keep_mask(7801 + M, M // R, N, 0.6)
+    keep[0, :] = 0
+    keep[-1, :] = 1
+    keep[:, N // 2] = 0
+    p_ref = orc.pack(d["W"], R, keep, 32, CODE[dtype])
+    p = bsp.bsp_pack(dev(d["W"], dtype), R, torch.from_numpy(keep).cuda(), 32)
+    L = bsp.lib()
+    ws = torch.empty(8 * (M + 256) * (N + 256), dtype=torch.uint8, device="cuda")
+    bias = dev(d["bias"], dtype)
+
+    def run(X, ws_bytes):
+        Y = torch.full((T, M), 7.0, dtype=X.dtype, device="cuda")
+        at = [ctypes.c_void_p(t.data_ptr()) for t in (X, p.blk_cnt, p.blk_ptr, p.col_idx, p.vals, bias, Y, ws)]
+        st = L.bsp_linear_ws(at[0], CODE[dtype], T, M, N, R, 32, *at[1:], ws_bytes, ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+        return st, Y
+
+    X = dev(d["X"], dtype)
+    assert run(X, 64)[0] == 4                     # too small a workspace: refused, nothing written
+    st, Y = run(X, ws.numel())
+    assert st == 0
+    rows = [(0, T)] if T <= 512 else [(0, 40), (T // 2, T // 2 + 40), (T - 40, T)]
+    _check_y(host(Y), d["X"], p_ref, d["bias"], CODE[dtype], dtype, rows)
+    X[T // 2, N // 2] = float("inf")
+    st, Yi = run(X, ws.numel())
+    assert st == 0
+    keep_rows = torch.arange(T, device="cuda") != T // 2
+    assert torch.equal(Yi[keep_rows], Y[keep_rows])
+    Xr = d["X"][T // 2:T // 2 + 1]                # that token is computed from the storage, in another order of sums
+    _check_y(host(Yi[T // 2:T // 2 + 1]), Xr, p_ref, d["bias"], CODE[dtype], dtype, None)
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 @pytest.mark.parametrize("T", [16, 8192])
 def test_gelu_over_its_range(dtype, T):
