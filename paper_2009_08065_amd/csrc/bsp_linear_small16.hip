@@ -74,7 +74,8 @@ __device__ __forceinline__ void small_copy_in(const uint16_t *__restrict__ X, in
     }
 }
 
-// GELU as in the kernel for narrow layers: y = max(v, 0) - |v| 2^p(|v|), p a fit of log2(erfc(a / sqrt 2) / 2).
+// GELU as in the kernel for narrow layers: y = max(v, 0) - |v| 2^p(|v|), p a fit of log2(erfc(a / sqrt 2) / 2).  The factor
+// of 2^p is -|v|, bounded for positive v where 2^p is 0 long since: +inf gives +inf, -inf and NaN give NaN as in the exact form.
 __device__ __forceinline__ float gelu_fit(float v) {
     const float a = __builtin_fabsf(v);
     float p = __builtin_fmaf(a, -0x1.740ed2p-19f, 0x1.43f96p-15f);
@@ -85,7 +86,8 @@ __device__ __forceinline__ float gelu_fit(float v) {
     p = __builtin_fmaf(a, p, -0x1.d639dp-2f);
     p = __builtin_fmaf(a, p, -0x1.26aedep+0f);
     p = __builtin_fmaf(a, p, -1.0f);
-    return __builtin_fmaf(-a, __builtin_amdgcn_exp2f(p), __builtin_fmaxf(v, 0.0f));
+    const float m = __builtin_fminf(v, __builtin_fmaxf(-v, -16.0f));
+    return __builtin_fmaf(m, __builtin_amdgcn_exp2f(p), __builtin_fmaxf(v, 0.0f));
 }
 
 template <int DT, int NSUB, int NW>

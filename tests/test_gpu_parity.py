@@ -672,6 +672,31 @@ def test_gelu_over_its_range(dtype, T):
     assert np.all(np.abs(Y[0] - ref) <= ULP[dtype] / 2 * np.abs(ref) + 2.0 ** -25 * (dtype == "f16") + 1.5e-7 * np.abs(v))
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("T,N", [(16, 64), (16, 1536), (8192, 64), (8192, 1536)])
+def test_gelu_of_what_is_not_finite(dtype, T, N):
+    """Sums of +inf, -inf, NaN and close to the largest number, in the kernel for few tokens, the one for narrow layers and
+    the one that streams X: as the exact form gives them (zero weights, so the sums are the biases; finite results to one
+    rounding, as the values are far outside the curved part)."""
+    M = 1024
+    v = np.tile(np.array([np.inf, -np.inf, np.nan, 6e4 if dtype == "f16" else 3.3e38, 100.0, -100.0, 0.0, -6e4], np.float32), M // 8)
+    bias = dev(v, dtype)
+    keep = np.zeros((M // 16, N), np.uint8)
+    keep[:, 3] = 1
+    p = bsp.bsp_pack(torch.zeros((M, N), dtype=TDT[dtype], device="cuda"), 16, torch.from_numpy(keep).cuda(), 32)
+    X = torch.ones((T, N), dtype=TDT[dtype], device="cuda")
+    Y = host(bsp.bsp_linear_planned_fused(X, p, bsp.bsp_linear_plan(p), bias, act=bsp.ACT_GELU)).astype(np.float64)
+    v = host(bias).astype(np.float64)
+    with np.errstate(invalid="ignore"):
+        ref = orc.epilogue(v, orc.ACT_GELU)[1]
+    assert np.isposinf(ref[0]) and np.isnan(ref[1]) and np.isnan(ref[2])
+    ref = np.broadcast_to(ref, Y.shape)
+    assert np.array_equal(np.isnan(Y), np.isnan(ref)) and np.array_equal(np.isinf(Y), np.isinf(ref))
+    assert np.array_equal(Y[np.isinf(ref)], ref[np.isinf(ref)])
+    fin = np.isfinite(ref)
+    assert np.all(np.abs(Y[fin] - ref[fin]) <= ULP[dtype] / 2 * np.abs(ref[fin]))
+
+
 def test_linear_fused_epilogue_refuses_what_is_not_fused():
     """Row-blocks of other heights, and a residual for a layer whose kernel stores block by block: an error and
     nothing written."""
