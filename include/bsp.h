@@ -220,7 +220,8 @@ int bsp_linear(const void *X, int xdt, int64_t T, int64_t M, int64_t N, int32_t 
 
 /* The same call with scratch memory for layers that keep much (low compression, many tokens): the storage is expanded
  * into ws and multiplied densely (16-bit types, k_align % 32 == 0; fp32 sums, one rounding).  Pruned positions still meet
- * nothing: a token whose sums are not finite is computed again from the storage alone.
+ * nothing: tokens whose sums are not finite are multiplied again over the kept positions alone, at 2 to 7 times the
+ * call's usual time if all are.
  * bsp_linear_workspace_bytes: the bytes this takes for a storage of up to capacity_cols padded kept columns, or 0 where
  * bsp_linear itself is the faster one; then, or with ws == NULL, the call is bsp_linear.  ws: 256-byte aligned, undefined
  * before and after; calls that may overlap need one each.  Errors as bsp_linear, and BSP_ERR_CAPACITY (ws_bytes too
@@ -255,7 +256,8 @@ int bsp_linear_transposed(const void *U, int udt, int64_t T, int64_t M, int64_t 
 
 /* The same call with scratch memory, which makes it several times faster: for 16-bit types and R % 8 == 0 the storage
  * is expanded into ws and multiplied densely by the matrix cores (fp32 sums, one rounding).  Pruned positions still
- * meet nothing: a token whose sums are not finite is computed again from the storage alone.  ws: at least
+ * meet nothing: tokens whose sums are not finite are multiplied again over the kept positions alone, at 2 to 9 times the
+ * call's usual time if all are.  ws: at least
  * bsp_linear_transposed_workspace_bytes(...) bytes, 256-byte aligned, undefined before and after; calls that may
  * overlap need one each.
  * That query returns 0 where no scratch is used; with ws == NULL, or U not 16-byte aligned, the call is

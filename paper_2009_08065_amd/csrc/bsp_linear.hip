@@ -238,7 +238,7 @@ extern "C" size_t bsp_linear_workspace_bytes(int xdt, int64_t T, int64_t M, int6
                                              int64_t capacity_cols) {
     if (T <= 0 || M <= 0 || N <= 0 || R < 1 || R > 64 || M % R != 0 || capacity_cols <= 0) return 0;
     if (!tiled_supported(xdt, N, k_align) || M >= ((int64_t)1 << 23)) return 0;
-    return linear_expand_pays(T, M, N, R, capacity_cols) ? linear_expand_bytes(M, N) : 0;
+    return linear_expand_pays(T, M, N, R, capacity_cols) ? linear_expand_bytes(M, N, R) : 0;
 }
 
 extern "C" int bsp_linear_ws(const void *X, int xdt, int64_t T, int64_t M, int64_t N, int32_t R, int32_t k_align,
@@ -258,7 +258,7 @@ extern "C" int bsp_linear_ws(const void *X, int xdt, int64_t T, int64_t M, int64
     dim3 grid((unsigned)tok_tiles, (unsigned)B, 1);
     const bool mfma_ok = xdt != BSP_F32 && k_align % 32 == 0 && col_idx && vals && aligned(col_idx, 16);
     if (ws && mfma_ok && aligned(Y, 16) && tiled_supported(xdt, N, k_align) && M < ((int64_t)1 << 23)) {
-        if (ws_bytes < linear_expand_bytes(M, N)) return BSP_ERR_CAPACITY;
+        if (ws_bytes < linear_expand_bytes(M, N, R)) return BSP_ERR_CAPACITY;
         if (!aligned(ws, 256)) return BSP_ERR_SHAPE;
         const int st = linear_expand(X, xdt, T, M, N, R, blk_cnt, blk_ptr, col_idx, vals, bias, Y, ws, s);
         return st != BSP_OK ? st : check_launch();

@@ -212,14 +212,14 @@ int launch_linear_f32_tile(const float *X, int64_t T, int64_t M, int64_t N, int3
 // The transposed product as a dense one on the expanded matrix (bsp_linear_t_expand.hip), for 16-bit types: whether
 // these arguments can take it, the workspace it needs, and its launch.  No argument checks of its own.
 bool linear_t_expand_supported(int udt, int64_t M, int32_t R);
-size_t linear_t_expand_bytes(int64_t M, int64_t N);
+size_t linear_t_expand_bytes(int64_t M, int64_t N, int32_t R);
 int linear_t_expand(const void *U, int udt, int64_t T, int64_t M, int64_t N, int32_t R, const int32_t *blk_cnt,
                     const int32_t *blk_ptr, const int32_t *col_idx, const void *vals, const void *bias, void *Z,
                     void *ws, hipStream_t s);
 
 // The layer as a dense product on the expanded matrix (same file), for 16-bit types, N % 8 == 0, X aligned to 16 bytes:
 // the workspace it needs, whether it is the faster one for these sizes, and its launch.  No argument checks of its own.
-size_t linear_expand_bytes(int64_t M, int64_t N);
+size_t linear_expand_bytes(int64_t M, int64_t N, int32_t R);
 bool linear_expand_pays(int64_t T, int64_t M, int64_t N, int32_t R, int64_t capacity_cols);
 int linear_expand(const void *X, int xdt, int64_t T, int64_t M, int64_t N, int32_t R, const int32_t *blk_cnt,
                   const int32_t *blk_ptr, const int32_t *col_idx, const void *vals, const void *bias, void *Y, void *ws,

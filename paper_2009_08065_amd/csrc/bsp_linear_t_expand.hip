@@ -12,8 +12,9 @@
 // Two kernels: expand_kernel writes Wp as matrix-core operands, tile_kernel multiplies.
 //
 // A pruned weight must not meet U: 0 times an infinite input would be NaN.  Every column of a token with a
-// non-finite input gets a non-finite sum here, so sums that are all finite are the right ones, and a token with a
-// non-finite sum is computed again from the compact storage alone (recompute_token).
+// non-finite input gets a non-finite sum here, so sums that are all finite are the right ones.  The tokens with a
+// non-finite sum are multiplied again, each row-block's products by themselves, and only what the kept positions give is
+// taken (kept_sums); the expansion writes one bit per row-block and column for that.
 #include "bsp_common.h"
 #include "bsp_linear_internal.h"
 #include "bsp_mfma_device.h"
@@ -44,6 +45,14 @@ __device__ __forceinline__ f32x16 mfma32(uint4 a, uint4 b, f32x16 c) {
                                                       0, 0);
 }
 
+// Bit n of row b of `kept`: row-block b keeps column n; rows are whole groups of kColPad columns.  (The workgroup of 256
+// columns whose thread t holds column t's place, of the row-block's first slab.)
+__device__ __forceinline__ void write_kept(uint64_t *__restrict__ kept, int b, int place) {
+    const uint64_t bits = __ballot(place >= 0);
+    if (blockIdx.z == 0 && (threadIdx.x & 63) == 0)
+        kept[((int64_t)b * gridDim.y + blockIdx.y) * (kColPad / 64) + (threadIdx.x >> 6)] = bits;
+}
+
 // ---------------------------------------------------------------------------------------
 // Expansion.  The expanded matrix is stored as operands: fragment (n / 32, m / 16) at (n / 32) frags_m + m / 16, lane l
 // of it holding column n % 32 = l % 32, rows 8 (l / 32) .. + 7 of the 16.  One workgroup per row-block, 256 columns and
@@ -56,7 +65,8 @@ __global__ __launch_bounds__(kThreadsX) void expand_kernel(int32_t R, int32_t B,
                                                            const int32_t *__restrict__ blk_cnt,
                                                            const int32_t *__restrict__ blk_ptr,
                                                            const int32_t *__restrict__ col_idx,
-                                                           const uint16_t *__restrict__ vals, uint8_t *__restrict__ out) {
+                                                           const uint16_t *__restrict__ vals, uint8_t *__restrict__ out,
+                                                           uint64_t *__restrict__ kept) {
     __shared__ int32_t place[kColPad];
     const int tid = threadIdx.x, b = blockIdx.x, c0 = blockIdx.y * kColPad, r0 = blockIdx.z * 16;
     place[tid] = -1;
@@ -69,6 +79,7 @@ __global__ __launch_bounds__(kThreadsX) void expand_kernel(int32_t R, int32_t B,
     }
     __syncthreads();
     const int p = place[tid], n = c0 + tid;
+    write_kept(kept, b, p);
     const uint16_t *v = vals + ((int64_t)R * base + (int64_t)r0 * kp + (p < 0 ? 0 : p));
     uint8_t *column = out + (int64_t)(n >> 5) * frags_m * kFrag + (n & 31) * 16;
     const int o0 = (b * R + r0) >> 3;
@@ -95,7 +106,8 @@ __global__ __launch_bounds__(kThreadsX) void expand_rows_kernel(int32_t R, int32
                                                                 const int32_t *__restrict__ blk_cnt,
                                                                 const int32_t *__restrict__ blk_ptr,
                                                                 const int32_t *__restrict__ col_idx,
-                                                                const uint16_t *__restrict__ vals, uint8_t *__restrict__ out) {
+                                                                const uint16_t *__restrict__ vals, uint8_t *__restrict__ out,
+                                                                uint64_t *__restrict__ kept) {
     __shared__ int32_t place[kColPad];
     const int tid = threadIdx.x, b = blockIdx.x, c0 = blockIdx.y * kColPad, r0 = blockIdx.z * 16;
     place[tid] = -1;
@@ -107,6 +119,7 @@ __global__ __launch_bounds__(kThreadsX) void expand_rows_kernel(int32_t R, int32
         if ((unsigned)c < (unsigned)kColPad) place[c] = p;
     }
     __syncthreads();
+    if (b < B) write_kept(kept, b, place[tid]);
     const int r = r0 + (tid & 15), m = b * R + r;
     if (r >= R || m >= rows_pad) return;
     const uint16_t *v = vals + ((int64_t)R * base + (int64_t)r * kp);
@@ -125,52 +138,123 @@ __global__ __launch_bounds__(kThreadsX) void expand_rows_kernel(int32_t R, int32
     }
 }
 
-// One token's sums over the kept positions alone, for columns cr0 .. cr0 + ncol - 1, into row[] (every thread of
-// the workgroup calls it; sums: ncol floats of LDS).
-template <int DT>
-__device__ __forceinline__ void recompute_token(const uint16_t *__restrict__ u, int64_t B, int32_t R,
-                                                const int32_t *__restrict__ blk_cnt,
-                                                const int32_t *__restrict__ blk_ptr,
-                                                const int32_t *__restrict__ col_idx, const uint16_t *__restrict__ vals,
-                                                const void *__restrict__ bias, int cr0, int ncol, float *sums,
-                                                uint16_t *row) {
-    const int tid = threadIdx.x;
-    for (int c = tid; c < ncol; c += kThreadsX) sums[c] = 0.0f;
-    for (int64_t b = 0; b < B; ++b) {
-        __syncthreads();
-        const int64_t base = blk_ptr[b];
-        const int kp = (int)(blk_ptr[b + 1] - base), k = blk_cnt[b];
-        for (int p = tid; p < k; p += kThreadsX) {
-            const int c = col_idx[base + p] - cr0;
-            if ((unsigned)c >= (unsigned)ncol) continue;
-            float acc = 0.0f;
-            for (int r = 0; r < R; ++r)
-                acc = __builtin_fmaf(elem<DT>::load(u, b * R + r), elem<DT>::load(vals, R * base + (int64_t)r * kp + p), acc);
-            sums[c] += acc;  // the kept columns of a row-block are distinct
+// The wavefront's sums of 32 tokens over the kept positions alone, into acc (its FN pieces of 32 columns).  It costs a few times
+// the dense product, for every input alike: with every token of the batch not finite (an overflow in fp16 training), us, the kernel
+// on the storage / this: Z, 4096 x 1024, 8192 tokens, R = 16 at 5x 229 / 533 (61 where all sums are finite), 768 x 3072, 4096 tokens,
+// R = 8 at 2x 271 / 228; Y, 1024 x 4096, 8192 tokens, R = 16 at 5x 122 / 436, at 1.43x 349 / 456.  One such token: 170 and 163.
+// (Each token by itself from the storage, as it was, took 25 and 44 ms for whole batches of 4096 tokens.)
+//   Z = U Wp: the rows of a step of 16 belong to one row-block, or 8 and 8 to two (R % 8 == 0): each one's products start
+//   from zero and are added where the row-block keeps the column.
+//   Y = X Wp^T: two row-blocks at a time, X zeroed where each prunes the column; of the sums of 32 rows its own are taken.
+//   A row-block's pads are zero weights of its last kept column, and part of the layer's sum.
+// u: the lane's token's row.
+template <int DT, int FN, bool ROWS>
+__device__ __forceinline__ void kept_sums(const uint8_t *u, int32_t M, int32_t N, int32_t R, int32_t frags_m,
+                                          const uint8_t *wcol, int wcol0, const uint32_t *__restrict__ kept,
+                                          const int32_t *__restrict__ blk_cnt, const int32_t *__restrict__ blk_ptr,
+                                          const int32_t *__restrict__ col_idx, f32x16 (&acc)[FN]) {
+    constexpr int kDepth = ROWS ? 2 : 4;                 // steps whose operands are on their way (what the registers allow)
+    constexpr int kW = ROWS ? 1 : FN, kB = ROWS ? 2 : FN;  // of a step: weight operands, words of `kept`
+    const int lane = threadIdx.x & 63, kh = lane >> 5;
+    const int words = ((ROWS ? M : N) + kColPad - 1) / kColPad * (kColPad / 32);  // of a row of `kept`
+    const int steps = (M + 15) / 16;
+    // the row-block of rows 8 o .. 8 o + 7 (Z = U Wp: R % 8 == 0); exact below 2^28, and o is below 2^20
+    const uint32_t per_block = ROWS ? 1u : (0x80000000u + (uint32_t)(R >> 3) - 1u) / (uint32_t)(R >> 3);
+    auto block_of = [&](int o) { return (int)__umulhi(2u * (uint32_t)o, per_block); };
+    uint4 w[kDepth][kW], x[kDepth];
+    uint32_t bits[kDepth][kB];
+    // n0: first piece.  ROWS: row-blocks b and b2; else lanes 0 and 1 hold the words of the row-blocks of the step's halves
+    auto ask = [&](auto slot, int step, int n0, int b, int b2) {
+        constexpr int s = decltype(slot)::value;
+        const int f = step < steps ? step : steps - 1;
+#pragma unroll
+        for (int n = 0; n < kW; ++n) w[s][n] = *reinterpret_cast<const uint4 *>(wcol + ((int64_t)(n0 + n) * frags_m + f) * kFrag + lane * 16);
+        const int k = 16 * f + 8 * kh;  // past the last row: any value, zeroed below (M is a multiple of 8)
+        x[s] = *reinterpret_cast<const uint4 *>(u + 2 * (int64_t)(k < M ? k : M - 8));
+        if constexpr (ROWS) {
+            bits[s][0] = kept[(int64_t)b * words + (f >> 1)];
+            bits[s][1] = kept[(int64_t)b2 * words + (f >> 1)];
+        } else {
+            const int o = 2 * f + (lane & 1);
+            const uint32_t *row = kept + ((int64_t)block_of(8 * o < M ? o : 2 * f) * words + (wcol0 >> 5));
+#pragma unroll
+            for (int n = 0; n < FN; ++n) bits[s][n] = row[n];
         }
+    };
+    auto walk = [&](int n0, int b, int b2, auto use) {
+        static_for<0, kDepth>([&](auto j) { ask(j, j, n0, b, b2); });
+        int f0 = 0;
+        for (; f0 + kDepth <= steps; f0 += kDepth)
+            static_for<0, kDepth>([&](auto j) {
+                use(j, f0 + j);
+                ask(j, f0 + j + kDepth, n0, b, b2);
+                __builtin_amdgcn_sched_barrier(0);
+            });
+        static_for<0, kDepth - 1>([&](auto j) {
+            if (f0 + j < steps) use(j, f0 + j);  // uniform
+        });
+    };
+    auto bit = [](uint32_t v, int i) { return (uint32_t)((int32_t)(v << (31 - i)) >> 31); };  // all ones or zeros
+    auto both = [](uint4 v, const uint32_t (&mask)[4]) { return make_uint4(v.x & mask[0], v.y & mask[1], v.z & mask[2], v.w & mask[3]); };
+    auto clear = [](f32x16 &v) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) v[i] = 0.0f;
+    };
+    if constexpr (ROWS) {
+        static_for<0, FN>([&](auto piece) {
+            constexpr int n = decltype(piece)::value;
+            const int m0 = wcol0 + 32 * n, last = ((m0 + 32 < N ? m0 + 32 : N) - 1) / R;
+            for (int b = m0 / R; b <= last; b += 2) {  // uniform
+                const int block[2] = {b, b < last ? b + 1 : b};
+                f32x16 sum[2];
+                clear(sum[0]);
+                clear(sum[1]);
+                walk(n, block[0], block[1], [&](auto slot, int f) {
+                    constexpr int s = decltype(slot)::value;
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) {
+                        const uint32_t mine = 16 * f + 8 * kh < M ? bits[s][j] >> (16 * (f & 1) + 8 * kh) : 0u;
+                        uint32_t mask[4];
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) mask[i] = (bit(mine, 2 * i) & 0xffffu) | (bit(mine, 2 * i + 1) & 0xffff0000u);
+                        sum[j] = mfma32<DT>(w[s][0], both(x[s], mask), sum[j]);
+                    }
+                });
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    const int end = blk_ptr[block[j] + 1];
+                    const float pad = end - blk_ptr[block[j]] > blk_cnt[block[j]] ? 0.0f * elem<DT>::load(u, col_idx[end - 1]) : 0.0f;
+#pragma unroll
+                    for (int i = 0; i < 16; ++i)
+                        if ((uint32_t)(m0 + 8 * (i >> 2) + 4 * kh + (i & 3) - block[j] * R) < (uint32_t)R) acc[n][i] = sum[j][i] + pad;
+                }
+            }
+        });
+    } else {
+#pragma unroll
+        for (int n = 0; n < FN; ++n) clear(acc[n]);
+        walk(0, 0, 0, [&](auto slot, int f) {
+            constexpr int s = decltype(slot)::value;
+            const bool two = 16 * f + 8 < M;  // halves
+            const bool split = !two || block_of(2 * f) != block_of(2 * f + 1);
+            for (int h = 0; h < (split && two ? 2 : 1); ++h) {  // uniform
+                const uint32_t own = !split || kh == h ? ~0u : 0u;
+                const uint32_t mask[4] = {own, own, own, own};
+                f32x16 p[FN];
+#pragma unroll
+                for (int n = 0; n < FN; ++n) {
+                    clear(p[n]);
+                    p[n] = mfma32<DT>(both(w[s][n], mask), both(x[s], mask), p[n]);
+                }
+#pragma unroll
+                for (int n = 0; n < FN; ++n) {
+                    const uint32_t mine = __builtin_amdgcn_readlane(bits[s][n], h) >> (4 * kh);
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) acc[n][i] += __uint_as_float(__float_as_uint(p[n][i]) & bit(mine, 8 * (i >> 2) + (i & 3)));
+                }
+            }
+        });
     }
-    __syncthreads();
-    for (int c = tid; c < ncol; c += kThreadsX)
-        row[c] = (uint16_t)elem<DT>::bits(sums[c] + (bias ? elem<DT>::load(bias, cr0 + c) : 0.0f));
-    __syncthreads();
-}
-
-// The same for the layer: rows cr0 .. cr0 + ncol - 1 of Wp, a thread per row.
-template <int DT>
-__device__ __forceinline__ void recompute_rows(const uint16_t *__restrict__ x, int32_t R, const int32_t *__restrict__ blk_cnt,
-                                               const int32_t *__restrict__ blk_ptr, const int32_t *__restrict__ col_idx,
-                                               const uint16_t *__restrict__ vals, const void *__restrict__ bias, int cr0,
-                                               int ncol, uint16_t *row) {
-    for (int c = threadIdx.x; c < ncol; c += kThreadsX) {
-        const int b = (cr0 + c) / R, r = (cr0 + c) % R;
-        const int64_t base = blk_ptr[b];
-        const int kp = (int)(blk_ptr[b + 1] - base), k = blk_cnt[b];
-        float acc = 0.0f;
-        for (int p = 0; p < k; ++p)
-            acc = __builtin_fmaf(elem<DT>::load(x, col_idx[base + p]), elem<DT>::load(vals, R * base + (int64_t)r * kp + p), acc);
-        row[c] = (uint16_t)elem<DT>::bits(acc + (bias ? elem<DT>::load(bias, cr0 + c) : 0.0f));
-    }
-    __syncthreads();
 }
 
 // ---------------------------------------------------------------------------------------
@@ -185,12 +269,13 @@ __device__ __forceinline__ void recompute_rows(const uint16_t *__restrict__ x, i
 // conflicts in the operand reads and the weights one stage ahead 2300.
 // ---------------------------------------------------------------------------------------
 // ROWS: the operands are Wp's rows (the layer), U is X and M, N are the layer's columns and rows.
+// (the launch bounds: workgroups of a compute unit as the products' registers allow, whatever kept_sums would like)
 template <int DT, int FT, int FN, bool ROWS>
-__global__ __launch_bounds__(kThreadsX, 1) void tile_kernel(
-    const uint16_t *__restrict__ U, int64_t T, int32_t M, int32_t N, int32_t B, int32_t R, int32_t frags_m,
-    const uint8_t *__restrict__ W, const int32_t *__restrict__ blk_cnt,
-    const int32_t *__restrict__ blk_ptr, const int32_t *__restrict__ col_idx, const uint16_t *__restrict__ vals,
-    const void *__restrict__ bias, void *__restrict__ Z) {
+__global__ __launch_bounds__(kThreadsX, FN == 2 ? 1 : (FT == 4 ? 2 : 3)) void tile_kernel(
+    const uint16_t *__restrict__ U, int64_t T, int32_t M, int32_t N, int32_t R, int32_t frags_m,
+    const uint8_t *__restrict__ W, const uint32_t *__restrict__ kept, const int32_t *__restrict__ blk_cnt,
+    const int32_t *__restrict__ blk_ptr, const int32_t *__restrict__ col_idx, const void *__restrict__ bias,
+    void *__restrict__ Z) {
     constexpr int TT = 32 * FT, NN = 128 * FN;
     constexpr int kUBytes = TT * kRowBytes;
     constexpr int kPitch = NN * 2 + 16;  // bytes of a token's row in the output tile
@@ -312,46 +397,52 @@ __global__ __launch_bounds__(kThreadsX, 1) void tile_kernel(
     const int64_t left = T - t0;
     // Round into a token-major tile in LDS (the stages' memory), bias added in fp32, then write whole rows.
     uint8_t *tile = smem;
-    float *sums = reinterpret_cast<float *>(smem + TT * kPitch);
-    uint32_t *flags = reinterpret_cast<uint32_t *>(smem + TT * kPitch + NN * 4);  // one bit per token: non-finite sums
+    uint32_t *flags = reinterpret_cast<uint32_t *>(smem + TT * kPitch);  // one bit per token: non-finite sums
     const int ncol = N - cr0 < NN ? N - cr0 : NN;
+    const int wcol0 = cr0 + wave * FN * 32;  // the wavefront's first column
     if (tid < FT) flags[tid] = 0u;
     __syncthreads();
+    auto round_tokens = [&](int t, const f32x16 &v16, int n) {  // one piece of 32 tokens x 32 columns; NaN if a sum is not finite
+        float bad = 0.0f;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int c = wcol0 + n * 32 + 8 * q + 4 * kh;  // four consecutive columns of one token
+            float v[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                v[i] = v16[4 * q + i];
+                bad = __builtin_fmaf(v[i], 0.0f, bad);
+                if (bias) v[i] += elem<DT>::load(bias, c + i < N ? c + i : N - 1);
+            }
+            *reinterpret_cast<uint2 *>(tile + (32 * t + l32) * kPitch + (c - cr0) * 2) =
+                make_uint2(cvt_pk<DT>(v[0], v[1]), cvt_pk<DT>(v[2], v[3]));
+        }
+        return bad;
+    };
 #pragma unroll
     for (int t = 0; t < FT; ++t) {
-        const int tok = 32 * t + l32;
-        float bad = 0.0f;  // NaN once a sum is not finite
+        float bad = 0.0f;
 #pragma unroll
-        for (int n = 0; n < FN; ++n)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int c = (wave * FN + n) * 32 + 8 * q + 4 * kh;  // four consecutive columns of one token
-                float v[4];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    v[i] = acc[n][t][4 * q + i];
-                    bad = __builtin_fmaf(v[i], 0.0f, bad);
-                    if (bias) v[i] += elem<DT>::load(bias, cr0 + c + i < N ? cr0 + c + i : N - 1);
-                }
-                *reinterpret_cast<uint2 *>(tile + tok * kPitch + c * 2) = make_uint2(cvt_pk<DT>(v[0], v[1]), cvt_pk<DT>(v[2], v[3]));
-            }
+        for (int n = 0; n < FN; ++n) bad += round_tokens(t, acc[n][t], n);
         if (bad != 0.0f) atomicOr(&flags[t], 1u << l32);
     }
     __syncthreads();
-    for (int t = 0; t < FT; ++t) {
-        uint32_t todo = flags[t];  // uniform
-        while (todo) {
-            const int tok = 32 * t + __builtin_ctz(todo);
-            todo &= todo - 1;
-            if constexpr (ROWS) {
-                if (tok < left)
-                    recompute_rows<DT>(U + (t0 + tok) * M, R, blk_cnt, blk_ptr, col_idx, vals, bias, cr0, ncol,
-                                       reinterpret_cast<uint16_t *>(tile + tok * kPitch));
-            } else if (tok < left)
-                recompute_token<DT>(U + (t0 + tok) * M, B, R, blk_cnt, blk_ptr, col_idx, vals, bias, cr0, ncol, sums,
-                                    reinterpret_cast<uint16_t *>(tile + tok * kPitch));
-        }
+    uint32_t any = 0;
+#pragma unroll
+    for (int t = 0; t < FT; ++t) any |= flags[t];
+    any = __builtin_amdgcn_readfirstlane(any);
+    for (int t = 0; t < (any && wcol0 < N ? FT : 0); ++t) {  // (uniform in a wavefront; no barrier inside)
+        const uint32_t flagged = __builtin_amdgcn_readfirstlane(flags[t]);
+        if (!flagged) continue;
+        const int64_t row = 32 * t + l32 < left ? 32 * t + l32 : left - 1;
+        f32x16 sums[FN];
+        kept_sums<DT, FN, ROWS>(reinterpret_cast<const uint8_t *>(U + (t0 + row) * M), M, N, R, frags_m, wcol, wcol0, kept,
+                                blk_cnt, blk_ptr, col_idx, sums);
+        if ((flagged >> l32) & 1u)  // the others keep what they have
+#pragma unroll
+            for (int n = 0; n < FN; ++n) round_tokens(t, sums[n], n);
     }
+    if (any) __syncthreads();
     uint16_t *z = (uint16_t *)Z + t0 * N + cr0;
     if ((N & 7) == 0 && (reinterpret_cast<uintptr_t>(Z) & 15) == 0) {
         for (int i = tid; i < TT * (NN / 8); i += kThreadsX) {
@@ -371,7 +462,7 @@ __global__ __launch_bounds__(kThreadsX, 1) void tile_kernel(
 template <int FT, int FN>
 constexpr size_t tile_lds() {
     constexpr size_t stages = (size_t)kRing * 32 * FT * kRowBytes;
-    constexpr size_t out = (size_t)32 * FT * (128 * FN * 2 + 16) + 128 * FN * 4 + 4 * FT;
+    constexpr size_t out = (size_t)32 * FT * (128 * FN * 2 + 16) + 4 * FT;
     return stages > out ? stages : out;
 }
 
@@ -397,9 +488,11 @@ Tile choose_tile(int64_t T, int64_t M, int64_t N, double *us = nullptr) {
     return tb <= tc ? Tile{4, 1} : Tile{2, 1};
 }
 
+// The expanded matrix (N columns, M rows); behind it one bit per row-block and column of the pruned matrix.
 size_t expanded_bytes(int64_t M, int64_t N) {
     return (size_t)((N + kColPad - 1) / kColPad * kColPad) * (size_t)((M + kStageK - 1) / kStageK * kStageK) * 2;
 }
+size_t kept_bytes(int64_t B, int64_t cols) { return (size_t)B * (size_t)((cols + kColPad - 1) / kColPad) * (kColPad / 8); }
 
 struct Args {
     const uint16_t *U;
@@ -411,6 +504,8 @@ struct Args {
     void *Z, *ws;
     hipStream_t s;
 };
+
+uint32_t *kept_bits(const Args &a) { return (uint32_t *)((uint8_t *)a.ws + expanded_bytes(a.M, a.N)); }
 
 template <int DT, int FT, int FN, bool ROWS>
 int launch_tiles(const Args &a, int frags_m) {
@@ -426,8 +521,8 @@ int launch_tiles(const Args &a, int frags_m) {
     const int64_t tiles = (a.T + 32 * FT - 1) / (32 * FT), ranges = (a.N + 128 * FN - 1) / (128 * FN);
     const int64_t wgs = (tiles + 7) / 8 * 8 * ranges;  // whole rounds of the 8 XCDs
     if (wgs >= ((int64_t)1 << 31)) return BSP_ERR_SHAPE;
-    k<<<dim3((unsigned)wgs), kThreadsX, lds, a.s>>>(a.U, a.T, a.M, a.N, a.B, a.R, frags_m, (const uint8_t *)a.ws, a.blk_cnt,
-                                                    a.blk_ptr, a.col_idx, a.vals, a.bias, a.Z);
+    k<<<dim3((unsigned)wgs), kThreadsX, lds, a.s>>>(a.U, a.T, a.M, a.N, a.R, frags_m, (const uint8_t *)a.ws, kept_bits(a), a.blk_cnt,
+                                                    a.blk_ptr, a.col_idx, a.bias, a.Z);
     return BSP_OK;
 }
 
@@ -435,12 +530,13 @@ template <int DT, bool ROWS>
 int launch_all(const Args &a) {
     const Tile c = choose_tile(a.T, a.M, a.N);
     const int npad = (a.N + kColPad - 1) / kColPad * kColPad, frags_m = (a.M + kStageK - 1) / kStageK * 4;
+    uint64_t *kept = (uint64_t *)kept_bits(a);
     if constexpr (ROWS)
         expand_rows_kernel<<<dim3((unsigned)((npad + a.R - 1) / a.R), (unsigned)((a.M + kColPad - 1) / kColPad), (unsigned)((a.R + 15) / 16)), kThreadsX, 0, a.s>>>(
-            a.R, a.B, npad, frags_m, a.blk_cnt, a.blk_ptr, a.col_idx, a.vals, (uint8_t *)a.ws);
+            a.R, a.B, npad, frags_m, a.blk_cnt, a.blk_ptr, a.col_idx, a.vals, (uint8_t *)a.ws, kept);
     else
         expand_kernel<<<dim3((unsigned)a.B, (unsigned)(npad / kColPad), (unsigned)((a.R + 15) / 16)), kThreadsX, 0, a.s>>>(
-            a.R, a.B, frags_m, a.blk_cnt, a.blk_ptr, a.col_idx, a.vals, (uint8_t *)a.ws);
+            a.R, a.B, frags_m, a.blk_cnt, a.blk_ptr, a.col_idx, a.vals, (uint8_t *)a.ws, kept);
     if (c.ft == 2) return launch_tiles<DT, 2, 1, ROWS>(a, frags_m);
     return c.fn == 2 ? launch_tiles<DT, 4, 2, ROWS>(a, frags_m) : launch_tiles<DT, 4, 1, ROWS>(a, frags_m);
 }
@@ -452,7 +548,7 @@ bool linear_t_expand_supported(int udt, int64_t M, int32_t R) {
     return udt != BSP_F32 && R % 8 == 0 && M < ((int64_t)1 << 23);
 }
 
-size_t linear_t_expand_bytes(int64_t M, int64_t N) { return expanded_bytes(M, N); }
+size_t linear_t_expand_bytes(int64_t M, int64_t N, int32_t R) { return expanded_bytes(M, N) + kept_bytes(M / R, N); }
 
 int linear_t_expand(const void *U, int udt, int64_t T, int64_t M, int64_t N, int32_t R, const int32_t *blk_cnt,
                     const int32_t *blk_ptr, const int32_t *col_idx, const void *vals, const void *bias, void *Z,
@@ -462,7 +558,7 @@ int linear_t_expand(const void *U, int udt, int64_t T, int64_t M, int64_t N, int
     return udt == BSP_BF16 ? launch_all<BSP_BF16, false>(a) : launch_all<BSP_F16, false>(a);
 }
 
-size_t linear_expand_bytes(int64_t M, int64_t N) { return expanded_bytes(N, M); }
+size_t linear_expand_bytes(int64_t M, int64_t N, int32_t R) { return expanded_bytes(N, M) + kept_bytes(M / R, N); }
 
 // Microseconds of both forms, fitted to 64 to 8192 tokens of 256 to 4096 rows and columns at 1.43x to 5x.  The gather takes
 // a step per 32 kept columns of a row-block and token tile, and its tiles shrink with the layer's width (64 tokens up to

@@ -848,6 +848,94 @@ def test_linear_transposed_expanded_tiles(dtype, R, T, M, N, p_keep, k_align):
             assert_y_close(np.where(fin, out, 0.0), np.where(fin, ref, 0.0), dtype)
 
 
+def _spoil(A, what, seed):
+    """Non-finite inputs: every row with one or more of them, or a few rows at the edges of 32-row pieces and of the batch."""
+    rng = np.random.default_rng(seed)
+    T, K = A.shape
+    rows = np.arange(T) if what == "all" else np.unique(np.clip([0, 31, 32, 70, T - 2, T - 1], 0, T - 1))
+    for i, t in enumerate(rows):
+        A[t, rng.integers(0, K, 1 + i % 3)] = (np.inf, -np.inf, np.nan, np.inf)[i % 4]
+    return rows
+
+
+def _assert_like(out, ref, dtype):
+    """The same NaNs and infinities, and the finite values to the bar of assert_y_close."""
+    assert np.array_equal(np.isnan(out), np.isnan(ref))
+    assert np.array_equal(out[np.isinf(ref)], ref[np.isinf(ref)]) and np.array_equal(np.isinf(out), np.isinf(ref))
+    fin = np.isfinite(ref)
+    assert_y_close(np.where(fin, out, 0.0), np.where(fin, ref, 0.0), dtype)
+
+
+# row-blocks that share a step of 16 rows (8, 24, 40) or do not; every tile shape of the dense product; the layer's row-blocks
+# of one row, and of rows that cross the pieces of 32
+@pytest.mark.parametrize("what", ["all", "some", "weight"])
+@pytest.mark.parametrize("form,dtype,R,T,M,N", [
+    ("transposed", "bf16", 8, 75, 72, 129), ("transposed", "f16", 24, 131, 264, 520), ("transposed", "bf16", 40, 64, 200, 256),
+    ("transposed", "bf16", 16, 2600, 400, 2001), ("transposed", "f16", 64, 8190, 1024, 1000),
+    ("layer", "bf16", 16, 75, 272, 264), ("layer", "f16", 1, 70, 37, 520), ("layer", "bf16", 24, 131, 264, 1000),
+    ("layer", "f16", 5, 33, 35, 72), ("layer", "bf16", 64, 2100, 1024, 776), ("layer", "f16", 32, 4200, 2080, 136)])
+def test_expanded_of_what_is_not_finite(form, dtype, R, T, M, N, what):
+    """The dense products on the expanded matrix, where many sums are not finite: the pattern and the finite values are the
+    oracle's, which multiplies kept positions alone; rows without such an input keep their bits."""
+    K, O = (M, N) if form == "transposed" else (N, M)
+    X = wl.normal(R * 94 + T, (T, K), 1.0, dtype)
+    W = wl.normal(R * 95 + T, (M, N), 0.02, dtype)
+    bias = wl.normal(R * 96 + T, (O,), 0.5, dtype)
+    keep = wl.bernoulli_keep_mask(T + N + 10, M // R, N, 0.4)
+    keep[0, :] = 0 if M // R > 2 else 1
+    ws = torch.empty(4 * (M + 256) * (N + 256), dtype=torch.uint8, device="cuda")
+
+    def run(X, W):
+        p = bsp.bsp_pack(dev(W, dtype), R, torch.from_numpy(keep).cuda(), 32)
+        Xd, bd, Y = dev(X, dtype), dev(bias, dtype), torch.full((T, O), 7.0, dtype=TDT[dtype], device="cuda")
+        at = [ctypes.c_void_p(x.data_ptr()) for x in (p.blk_cnt, p.blk_ptr, p.col_idx, p.vals, bd, Y, ws)]
+        f = bsp.lib().bsp_linear_transposed_ws if form == "transposed" else bsp.lib().bsp_linear_ws
+        ws.fill_(255)
+        assert f(ctypes.c_void_p(Xd.data_ptr()), CODE[dtype], T, M, N, R, 32, *at, ws.numel(),
+                 ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)) == 0
+        return host(Y)
+
+    clean = run(X, W)
+    spoilt = np.arange(T)
+    if what == "weight":
+        b, n = [int(i[-1]) for i in np.nonzero(keep)]
+        W[b * R + R // 2, n] = np.inf
+    else:
+        spoilt = _spoil(X, what, T)
+    Y = run(X, W)
+    assert np.array_equal(np.delete(Y, spoilt, 0), np.delete(clean, spoilt, 0))
+    p_ref = orc.pack(W, R, keep, 32, CODE[dtype])
+    oracle = orc.linear_t_packed if form == "transposed" else orc.linear_packed
+    kw = dict(zdt=CODE[dtype]) if form == "transposed" else dict(ydt=CODE[dtype])
+    for t0, t1 in ((0, min(T, 75)), (max(0, T - 40), T)):
+        with np.errstate(invalid="ignore"):
+            ref = oracle(X, p_ref, bias, t0=t0, t1=t1, n_threads=16, **kw)[0]
+        _assert_like(Y[t0:t1], ref[t0:t1], dtype)
+
+
+def test_expanded_costs_the_same_order_whatever_the_inputs():
+    """A batch of non-finite inputs (an overflow in fp16 training) takes a few times as long as a finite one: 2 to 9 were
+    measured, 30 are allowed (it was several hundred when each such token was computed by itself)."""
+    R, T, M, N = 8, 2048, 768, 3072
+    W = dev(wl.normal(97, (M, N), 0.02, "bf16"), "bf16")
+    p = bsp.bsp_pack(W, R, torch.from_numpy(wl.bernoulli_keep_mask(98, M // R, N, 0.5)).cuda(), 32)
+    assert bsp.lib().bsp_linear_workspace_bytes(bsp.BF16, T, M, N, R, 32, p.total_cols) > 0
+    e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    for f, K in ((bsp.bsp_linear_transposed, M), (bsp.bsp_linear, N)):
+        A = torch.ones((T, K), dtype=torch.bfloat16, device="cuda")
+        ms = []
+        for B in (A, torch.full_like(A, float("inf"))):
+            best = float("inf")
+            for _ in range(5):
+                e0.record()
+                f(B, p)
+                e1.record()
+                torch.cuda.synchronize()
+                best = min(best, e0.elapsed_time(e1))
+            ms.append(best)
+        assert ms[1] < 30 * ms[0], ms
+
+
 @pytest.mark.parametrize("C", [16, 32])
 def test_row_segment_variant_end_to_end_on_transposed_storage(C):
     """The other division of Alg. 1: V [out, in] is cut into column blocks of C columns and a group is one row's
