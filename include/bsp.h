@@ -223,9 +223,11 @@ int bsp_linear(const void *X, int xdt, int64_t T, int64_t M, int64_t N, int32_t 
  * nothing: tokens whose sums are not finite are multiplied again over the kept positions alone, at 2 to 7 times the
  * call's usual time if all are.
  * bsp_linear_workspace_bytes: the bytes this takes for a storage of up to capacity_cols padded kept columns, or 0 where
- * bsp_linear itself is the faster one; then, or with ws == NULL, the call is bsp_linear.  ws: 256-byte aligned, undefined
- * before and after; calls that may overlap need one each.  Errors as bsp_linear, and BSP_ERR_CAPACITY (ws_bytes too
- * small), BSP_ERR_SHAPE (ws alignment). */
+ * bsp_linear itself is the faster one.  ws_bytes is what it returned, also for a larger buffer that serves several layers:
+ * with ws_bytes == 0 or ws == NULL, and for what the query always answers with 0, the call is bsp_linear; any other
+ * ws_bytes asks for the expanded form.  ws: 256-byte aligned, undefined before and after; calls that may overlap need one
+ * each.  Errors as bsp_linear, and for the expanded form BSP_ERR_CAPACITY (ws_bytes too small), BSP_ERR_SHAPE (ws
+ * alignment). */
 size_t bsp_linear_workspace_bytes(int xdt, int64_t T, int64_t M, int64_t N, int32_t R, int32_t k_align,
                                   int64_t capacity_cols);
 int bsp_linear_ws(const void *X, int xdt, int64_t T, int64_t M, int64_t N, int32_t R, int32_t k_align,
@@ -260,7 +262,7 @@ int bsp_linear_transposed(const void *U, int udt, int64_t T, int64_t M, int64_t 
  * call's usual time if all are.  ws: at least
  * bsp_linear_transposed_workspace_bytes(...) bytes, 256-byte aligned, undefined before and after; calls that may
  * overlap need one each.
- * That query returns 0 where no scratch is used; with ws == NULL, or U not 16-byte aligned, the call is
+ * That query returns 0 where no scratch is used; with ws == NULL or ws_bytes == 0, or U not 16-byte aligned, the call is
  * bsp_linear_transposed.  Errors as there, and BSP_ERR_CAPACITY (ws_bytes too small), BSP_ERR_SHAPE (ws alignment). */
 size_t bsp_linear_transposed_workspace_bytes(int udt, int64_t T, int64_t M, int64_t N, int32_t R);
 int bsp_linear_transposed_ws(const void *U, int udt, int64_t T, int64_t M, int64_t N, int32_t R, int32_t k_align,

@@ -257,7 +257,7 @@ extern "C" int bsp_linear_ws(const void *X, int xdt, int64_t T, int64_t M, int64
     hipStream_t s = (hipStream_t)stream;
     dim3 grid((unsigned)tok_tiles, (unsigned)B, 1);
     const bool mfma_ok = xdt != BSP_F32 && k_align % 32 == 0 && col_idx && vals && aligned(col_idx, 16);
-    if (ws && mfma_ok && aligned(Y, 16) && tiled_supported(xdt, N, k_align) && M < ((int64_t)1 << 23)) {
+    if (ws && ws_bytes > 0 && mfma_ok && aligned(Y, 16) && tiled_supported(xdt, N, k_align) && M < ((int64_t)1 << 23)) {
         if (ws_bytes < linear_expand_bytes(M, N, R)) return BSP_ERR_CAPACITY;
         if (!aligned(ws, 256)) return BSP_ERR_SHAPE;
         const int st = linear_expand(X, xdt, T, M, N, R, blk_cnt, blk_ptr, col_idx, vals, bias, Y, ws, s);

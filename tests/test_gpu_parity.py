@@ -848,6 +848,27 @@ def test_linear_transposed_expanded_tiles(dtype, R, T, M, N, p_keep, k_align):
             assert_y_close(np.where(fin, out, 0.0), np.where(fin, ref, 0.0), dtype)
 
 
+@pytest.mark.parametrize("T", [1, 300])
+def test_a_workspace_of_no_bytes_is_the_call_without_one(T):
+    """A scratch buffer that serves several layers, with the query's 0 for this one: the bits of bsp_linear; the same for the
+    transposed product."""
+    M, N, R = 256, 384, 16
+    W, keep = wl.normal(99, (M, N), 0.02, "bf16"), wl.bernoulli_keep_mask(100, M // R, N, 0.2)
+    p = bsp.bsp_pack(dev(W, "bf16"), R, torch.from_numpy(keep).cuda(), 32)
+    L, ws = bsp.lib(), torch.full((1 << 20,), 255, dtype=torch.uint8, device="cuda")
+    assert L.bsp_linear_workspace_bytes(bsp.BF16, T, M, N, R, 32, p.total_cols) == 0
+    s = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    for plain, with_ws, K, O in ((L.bsp_linear, L.bsp_linear_ws, N, M), (L.bsp_linear_transposed, L.bsp_linear_transposed_ws, M, N)):
+        X = dev(wl.normal(101, (T, K), 1.0, "bf16"), "bf16")
+        out = [torch.full((T, O), 7.0, dtype=torch.bfloat16, device="cuda") for _ in range(2)]
+        args = [[ctypes.c_void_p(x.data_ptr()) for x in (p.blk_cnt, p.blk_ptr, p.col_idx, p.vals)] + [None, ctypes.c_void_p(y.data_ptr())]
+                for y in out]
+        head = (ctypes.c_void_p(X.data_ptr()), bsp.BF16, T, M, N, R, 32)
+        assert plain(*head, *args[0], s) == 0
+        assert with_ws(*head, *args[1], ctypes.c_void_p(ws.data_ptr()), 0, s) == 0
+        assert torch.equal(*out) and bool((ws == 255).all())
+
+
 def _spoil(A, what, seed):
     """Non-finite inputs: every row with one or more of them, or a few rows at the edges of 32-row pieces and of the batch."""
     rng = np.random.default_rng(seed)
