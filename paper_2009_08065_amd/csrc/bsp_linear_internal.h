@@ -211,7 +211,7 @@ int launch_linear_f32_tile(const float *X, int64_t T, int64_t M, int64_t N, int3
 
 // The transposed product as a dense one on the expanded matrix (bsp_linear_t_expand.hip), for 16-bit types: whether
 // these arguments can take it, the workspace it needs, and its launch.  No argument checks of its own.
-bool linear_t_expand_supported(int udt, int64_t M, int32_t R);
+bool linear_t_expand_supported(int udt, int64_t M, int64_t N, int32_t R);
 size_t linear_t_expand_bytes(int64_t M, int64_t N, int32_t R);
 int linear_t_expand(const void *U, int udt, int64_t T, int64_t M, int64_t N, int32_t R, const int32_t *blk_cnt,
                     const int32_t *blk_ptr, const int32_t *col_idx, const void *vals, const void *bias, void *Z,

@@ -454,7 +454,7 @@ using namespace bsp;
 
 extern "C" size_t bsp_linear_transposed_workspace_bytes(int udt, int64_t T, int64_t M, int64_t N, int32_t R) {
     if (!valid_dtype(udt) || T <= 0 || M <= 0 || N <= 0 || R < 1 || R > 64 || M % R != 0) return 0;
-    return linear_t_expand_supported(udt, M, R) ? linear_t_expand_bytes(M, N, R) : 0;
+    return linear_t_expand_supported(udt, M, N, R) ? linear_t_expand_bytes(M, N, R) : 0;
 }
 
 extern "C" int bsp_linear_transposed(const void *U, int udt, int64_t T, int64_t M, int64_t N, int32_t R,
@@ -480,7 +480,7 @@ extern "C" int bsp_linear_transposed_ws(const void *U, int udt, int64_t T, int64
     // the matrix-core kernel indexes the storage with 32 bits: at most M (N + k_align) values
     const bool mfma_ok = udt != BSP_F32 && R % 4 == 0 && k_align % 8 == 0 && col_idx && vals && aligned(U, 4) &&
                          aligned(vals, 4) && (double)M * (double)(N + 64) < 4.0e9;
-    if (ws && ws_bytes > 0 && col_idx && vals && aligned(U, 16) && linear_t_expand_supported(udt, M, R)) {
+    if (ws && ws_bytes > 0 && col_idx && vals && aligned(U, 16) && linear_t_expand_supported(udt, M, N, R)) {
         if (ws_bytes < linear_t_expand_bytes(M, N, R)) return BSP_ERR_CAPACITY;
         if (!aligned(ws, 256)) return BSP_ERR_SHAPE;
         const int st = linear_t_expand(U, udt, T, M, N, R, blk_cnt, blk_ptr, col_idx, vals, bias, Z, ws, s);

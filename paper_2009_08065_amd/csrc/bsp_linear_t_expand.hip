@@ -543,9 +543,9 @@ int launch_all(const Args &a) {
 
 }  // namespace
 
-// (a tile's rows of U are addressed with 32-bit byte offsets)
-bool linear_t_expand_supported(int udt, int64_t M, int32_t R) {
-    return udt != BSP_F32 && R % 8 == 0 && M < ((int64_t)1 << 23);
+// (a tile's rows of U are addressed with 32-bit byte offsets; the expansion's grid has a row per 256 columns)
+bool linear_t_expand_supported(int udt, int64_t M, int64_t N, int32_t R) {
+    return udt != BSP_F32 && R % 8 == 0 && M < ((int64_t)1 << 23) && N <= 65535 * (int64_t)kColPad;
 }
 
 size_t linear_t_expand_bytes(int64_t M, int64_t N, int32_t R) { return expanded_bytes(M, N) + kept_bytes(M / R, N); }

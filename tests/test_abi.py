@@ -95,3 +95,12 @@ def test_host_side_argument_checks():
     assert L.bsp_prune_mask_workspace_bytes(4, 100, 1) >= 2 * (2048 + 64) * 4   # two histogram slots at least
     assert L.bsp_prune_mask_workspace_bytes(256, 4096, 1) > L.bsp_prune_mask_workspace_bytes(4, 100, 1)
     assert L.bsp_prune_mask_workspace_bytes(4, 100, 0) == 0
+
+
+def test_expansion_is_not_offered_beyond_its_grid():
+    """More columns than the expansion's grid has rows for: no scratch, so the transposed product stays with the kernel on the storage."""
+    L = bsp.lib()
+    cols = 65535 * 256
+    assert L.bsp_linear_transposed_workspace_bytes(bsp.BF16, 4, 64, cols, 16) >= 2 * 64 * cols
+    assert L.bsp_linear_transposed_workspace_bytes(bsp.BF16, 4, 64, cols + 1, 16) == 0
+    assert L.bsp_linear_transposed_workspace_bytes(bsp.BF16, 4, 64, 1 << 32, 16) == 0
