@@ -119,6 +119,16 @@ def _stream():
     return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
+def _scratch(need: int, device):
+    """Scratch of a call that is only faster with it; None (the call without) where the device has no such room."""
+    if not need:
+        return None
+    try:
+        return torch.empty(need, dtype=torch.uint8, device=device)
+    except torch.OutOfMemoryError:
+        return None
+
+
 def _check(st: int, where: str):
     if st != 0:
         raise BspError(st, where)
@@ -362,7 +372,7 @@ def bsp_linear(X, p: Packed, bias=None, Y=None):
         Y = torch.empty((T, p.M), dtype=X.dtype, device=X.device)
     has = p.total_cols > 0
     need = lib().bsp_linear_workspace_bytes(_DT[X.dtype], T, p.M, N, p.R, p.k_align, p.total_cols)
-    ws = torch.empty(need, dtype=torch.uint8, device=X.device) if need else None
+    ws = _scratch(need, X.device)
     st = lib().bsp_linear_ws(_ptr(X), _DT[X.dtype], T, p.M, N, p.R, p.k_align, _ptr(p.blk_cnt), _ptr(p.blk_ptr),
                              _ptr(p.col_idx) if has else None, _ptr(p.vals) if has else None, _ptr(bias), _ptr(Y),
                              _ptr(ws), need, _stream())
@@ -380,7 +390,7 @@ def bsp_linear_transposed(U, p: Packed, bias=None, Z=None):
         Z = torch.empty((T, p.N), dtype=U.dtype, device=U.device)
     has = p.total_cols > 0
     need = lib().bsp_linear_transposed_workspace_bytes(_DT[U.dtype], T, M, p.N, p.R)
-    ws = torch.empty(need, dtype=torch.uint8, device=U.device) if need else None
+    ws = _scratch(need, U.device)
     st = lib().bsp_linear_transposed_ws(_ptr(U), _DT[U.dtype], T, M, p.N, p.R, p.k_align, _ptr(p.blk_cnt),
                                         _ptr(p.blk_ptr), _ptr(p.col_idx) if has else None,
                                         _ptr(p.vals) if has else None, _ptr(bias), _ptr(Z), _ptr(ws), need, _stream())

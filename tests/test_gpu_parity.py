@@ -869,6 +869,31 @@ def test_a_workspace_of_no_bytes_is_the_call_without_one(T):
         assert torch.equal(*out) and bool((ws == 255).all())
 
 
+def test_no_room_for_scratch_is_the_call_without(monkeypatch):
+    """Where the expanded matrix does not fit any more, the layer and the transposed product run from the storage as they did
+    without a workspace."""
+    T, M, N, R = 2048, 768, 3072, 8
+    W, keep = wl.normal(102, (M, N), 0.02, "bf16"), wl.bernoulli_keep_mask(103, M // R, N, 0.5)
+    p = bsp.bsp_pack(dev(W, "bf16"), R, torch.from_numpy(keep).cuda(), 32)
+    L, s = bsp.lib(), ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    assert L.bsp_linear_workspace_bytes(bsp.BF16, T, M, N, R, 32, p.total_cols) > 0
+    empty = torch.empty
+
+    def no_room(*a, **k):
+        if k.get("dtype") == torch.uint8:
+            raise torch.OutOfMemoryError("no room")
+        return empty(*a, **k)
+
+    for call, plain, K, O in ((bsp.bsp_linear, L.bsp_linear, N, M), (bsp.bsp_linear_transposed, L.bsp_linear_transposed, M, N)):
+        X, ref = dev(wl.normal(104, (T, K), 1.0, "bf16"), "bf16"), torch.zeros((T, O), dtype=torch.bfloat16, device="cuda")
+        at = [ctypes.c_void_p(x.data_ptr()) for x in (p.blk_cnt, p.blk_ptr, p.col_idx, p.vals)] + [None, ctypes.c_void_p(ref.data_ptr())]
+        assert plain(ctypes.c_void_p(X.data_ptr()), bsp.BF16, T, M, N, R, 32, *at, s) == 0
+        with monkeypatch.context() as m:
+            m.setattr(torch, "empty", no_room)
+            out = call(X, p)
+        assert torch.equal(out, ref)
+
+
 def _spoil(A, what, seed):
     """Non-finite inputs: every row with one or more of them, or a few rows at the edges of 32-row pieces and of the batch."""
     rng = np.random.default_rng(seed)
