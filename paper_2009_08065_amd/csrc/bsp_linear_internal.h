@@ -133,30 +133,42 @@ inline double plan_steps(const TiledArgs &a) {
 // (with less than 8 tiles they spread over all XCDs).  When the units of 25 or 33
 // tiles went to all XCDs, X came from memory eight times: 1024 x 4096 at 1.43x, 1537 tokens 49.8 us, now 44.1;
 // 768 x 3072 in 8-row blocks at 3x, 1537 tokens 31.5 and 27.9.
-__host__ __device__ inline int64_t tile_workgroups(int64_t tiles, int64_t units) {
-    return (tiles >= 8 ? (tiles + 7) / 8 * 8 : tiles) * units;
+// With the units of few tiles more than an XCD can hold, the XCD that has one tile more than the others decides (9 tiles: two
+// on one XCD), and all XCDs are given all tiles if that saves rounds and not only the difference in memory traffic: 32768 x 1024 at 5x, 1100
+// tokens 44.6 us by XCD and 38.0 spread, 32768 x 2048 at 20x, 513 tokens 45.1 and 34.0, 30528 x 768 at 20x, 513 tokens 18.6 and 15.7.
+// Rounds of such a launch whose workgroups fill a compute unit each, by XCD and over all of them.
+inline int64_t tile_rounds_xcd(int64_t tiles, int64_t units) { return ((tiles + 7) / 8 * units + 31) / 32; }
+inline int64_t tile_rounds_all(int64_t tiles, int64_t units) { return (tiles * units + 255) / 256; }
+constexpr double kTileSpread = 1.12;  // what a round takes longer when all XCDs read all tiles
+inline bool tile_spread(int64_t tiles, int64_t units) {
+    return tiles < 8 || kTileSpread * (double)tile_rounds_all(tiles, units) < (double)tile_rounds_xcd(tiles, units);
 }
-__device__ inline void tile_place(uint32_t id, int32_t tiles, int32_t units, int32_t &tile, int32_t &unit) {
-    const uint32_t u = (uint32_t)units;
-    if (tiles >= 8) {
+inline double tile_rounds(int64_t tiles, int64_t units) {
+    if (tiles < 8) return (double)tile_rounds_all(tiles, units);
+    return tile_spread(tiles, units) ? kTileSpread * (double)tile_rounds_all(tiles, units) : (double)tile_rounds_xcd(tiles, units);
+}
+inline int64_t tile_workgroups(int64_t tiles, int64_t units) {
+    return (tile_spread(tiles, units) ? tiles : (tiles + 7) / 8 * 8) * units;
+}
+__device__ inline void tile_place(uint32_t id, int32_t tiles, int32_t units, int32_t spread, int32_t &tile, int32_t &unit) {
+    if (tiles < 8) {
+        tile = (int32_t)(id / (uint32_t)units);
+        unit = (int32_t)(id % (uint32_t)units);
+    } else if (spread) {  // (a round's workgroups share the weights of few units)
+        tile = (int32_t)(id % (uint32_t)tiles);
+        unit = (int32_t)(id / (uint32_t)tiles);
+    } else {
         const uint32_t at = id >> 3, rows = ((uint32_t)tiles + 7u) >> 3;
         tile = (int32_t)(at % rows * 8u + (id & 7u));  // (may lie past the last tile)
         unit = (int32_t)(at / rows);
-    } else {
-        tile = (int32_t)(id / u);
-        unit = (int32_t)(id % u);
     }
-}
-// Rounds of such a launch whose workgroups fill a compute unit each.
-inline int64_t tile_rounds(int64_t tiles, int64_t units) {
-    return tiles >= 8 ? ((tiles + 7) / 8 * units + 31) / 32 : (tiles * units + 255) / 256;
 }
 // Groups of the plan that a workgroup of the kernel for narrow layers walks.  A workgroup fills a compute unit, so
 // what counts is the rounds that a launch takes, times a workgroup's copy-in and walk
 // (microseconds fitted to measurements).  Enough strips to reach 256 workgroups was the rule once: 65 token tiles of a
 // 4096 x 1024 layer were 260 workgroups in two rounds, 68 us at 1.43x, and are 195 in one, 46.
 inline double steploop_walk_us(int64_t tiles, int64_t NG, int64_t gps, int64_t N, double steps) {
-    return (double)tile_rounds(tiles, (NG + gps - 1) / gps) * (0.0016 * (double)N + 0.42 * steps * (double)gps);
+    return tile_rounds(tiles, (NG + gps - 1) / gps) * (0.0016 * (double)N + 0.42 * steps * (double)gps);
 }
 inline int64_t steploop_groups(int64_t tiles, int64_t NG, int64_t N, double steps) {
     // (the fp32 bias of a strip's quads fills what LDS the tile leaves: 4 KiB per two groups, and a strip of gps groups
@@ -175,7 +187,7 @@ inline int64_t steploop_groups(int64_t tiles, int64_t NG, int64_t N, double step
 // 15.2 / 12.6 / 23.8.
 inline double stream_load(int64_t tiles, int64_t B, int waves) {
     const int64_t streams = (B + 3) / 4;
-    return (double)tile_rounds(tiles, (streams + waves - 1) / waves) * (waves == 8 ? 1.0 : (waves == 4 ? 0.82 : 0.76));
+    return tile_rounds(tiles, (streams + waves - 1) / waves) * (waves == 8 ? 1.0 : (waves == 4 ? 0.82 : 0.76));
 }
 inline int stream_waves(int64_t tiles, int64_t B) {
     int best = 8;

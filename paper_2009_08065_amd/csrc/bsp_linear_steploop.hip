@@ -336,9 +336,10 @@ template <int DT, int ACT>
 __global__ __launch_bounds__(kSlWaves * 64) void linear_steploop16_kernel(
     const uint16_t *__restrict__ X, int64_t T, int64_t M, int64_t N, int32_t npad, const int32_t *__restrict__ wptr,
     const uint8_t *__restrict__ wfrag, const uint8_t *__restrict__ xoff, const void *__restrict__ bias,
-    void *__restrict__ Y, int32_t ntiles, int32_t groups_per_strip, int32_t NG, int32_t B, int32_t max_step) {
+    void *__restrict__ Y, int32_t ntiles, int32_t groups_per_strip, int32_t NG, int32_t B, int32_t max_step,
+    int32_t spread) {
     int32_t tile, strip;
-    tile_place(blockIdx.x, ntiles, (NG + groups_per_strip - 1) / groups_per_strip, tile, strip);
+    tile_place(blockIdx.x, ntiles, (NG + groups_per_strip - 1) / groups_per_strip, spread, tile, strip);
     if (tile >= ntiles) return;
     const int64_t t0 = (int64_t)tile * 64;
     const int g0 = strip * groups_per_strip;
@@ -419,7 +420,7 @@ int launch_linear_steploop16(const TiledArgs &a, int64_t max_step, hipStream_t s
         if (st != BSP_OK) return st;
         kern<<<dim3((unsigned)wgs), dim3(kSlWaves * 64), lds, s>>>(
             a.X, a.T, a.M, a.N, a.npad, a.wptr, (const uint8_t *)a.wfrag, (const uint8_t *)a.xoff, a.bias, a.Y,
-            (int32_t)ntiles, (int32_t)gps, (int32_t)NG, (int32_t)a.B, (int32_t)max_step);
+            (int32_t)ntiles, (int32_t)gps, (int32_t)NG, (int32_t)a.B, (int32_t)max_step, tile_spread(ntiles, nstrips) ? 1 : 0);
         return check_launch();
     };
     if (a.residual) return BSP_ERR_SHAPE;  // (a residual is added by the kernel that writes its output at its end)

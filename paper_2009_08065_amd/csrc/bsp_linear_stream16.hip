@@ -262,10 +262,10 @@ __global__ __launch_bounds__((CW + kStLoadWaves) * 64) void linear_stream16_kern
     const uint16_t *__restrict__ X, int64_t T, int64_t M, int64_t N, int32_t npad, const int32_t *__restrict__ wptr,
     const uint8_t *__restrict__ wfrag, const uint8_t *__restrict__ xoff, const void *__restrict__ bias,
     void *__restrict__ Y, int32_t ntiles, int32_t NG, int32_t B, int32_t nq, int32_t max_step,
-    const uint16_t *__restrict__ residual) {
+    const uint16_t *__restrict__ residual, int32_t spread) {
     // the workgroup's streams: CW of the group's eight
     int32_t tile, unit;
-    tile_place(blockIdx.x, ntiles, ((B + kStNacc - 1) / kStNacc + CW - 1) / CW, tile, unit);
+    tile_place(blockIdx.x, ntiles, ((B + kStNacc - 1) / kStNacc + CW - 1) / CW, spread, tile, unit);
     if (tile >= ntiles) return;
     const int first_stream = unit * CW, g = first_stream / kStComputeWaves;
     const int64_t t0 = (int64_t)tile * 64;
@@ -436,7 +436,8 @@ int launch_linear_stream16(const TiledArgs &a, int64_t max_step, hipStream_t s) 
         if (st != BSP_OK) return st;
         kern<<<dim3((unsigned)wgs), dim3((decltype(waves)::value + kStLoadWaves) * 64), lds, s>>>(
             a.X, a.T, a.M, a.N, a.npad, a.wptr, (const uint8_t *)a.wfrag, (const uint8_t *)a.xoff, a.bias, a.Y,
-            (int32_t)ntiles, (int32_t)NG, (int32_t)a.B, ch.n, (int32_t)max_step, (const uint16_t *)a.residual);
+            (int32_t)ntiles, (int32_t)NG, (int32_t)a.B, ch.n, (int32_t)max_step, (const uint16_t *)a.residual,
+            tile_spread(ntiles, (streams + cw - 1) / cw) ? 1 : 0);
         return check_launch();
     };
     auto go = [&](auto dt, auto act, auto res) {

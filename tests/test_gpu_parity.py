@@ -593,6 +593,22 @@ def test_linear_planned_few_and_many_tokens(dtype, R, M, N, act, with_res):
             assert_y_close(Y[i], Y_ref, dtype)
 
 
+@pytest.mark.parametrize("R,T,M,N", [(16, 600, 32768, 64), (8, 1090, 30528, 72), (16, 577, 16400, 1544), (32, 1030, 30528, 2056)])
+def test_linear_planned_tall_layers(R, T, M, N):
+    """Tall layers of 9 to 18 ragged token tiles, whose workgroups go to all compute units and not tile by tile to the XCDs: every
+    (tile, unit) once, none past the end."""
+    d = wl.layer(7500 + M + N, T, M, N, "bf16")
+    keep = wl.bernoulli_keep_mask(7501 + M, M // R, N, 0.1)
+    p_ref = orc.pack(d["W"], R, keep, 32, CODE["bf16"])
+    p = bsp.bsp_pack(dev(d["W"], "bf16"), R, torch.from_numpy(keep).cuda(), 32)
+    Y = torch.full((T, M), 7.0, dtype=torch.bfloat16, device="cuda")
+    bsp.bsp_linear_planned(dev(d["X"], "bf16"), p, bsp.bsp_linear_plan(p), dev(d["bias"], "bf16"), Y)
+    Y = host(Y)
+    _check_y(Y, d["X"], p_ref, d["bias"], CODE["bf16"], "bf16", [(0, 40), (T // 2, T // 2 + 40), (T - 40, T)])
+    last = bsp.bsp_linear_planned(dev(d["X"][:64], "bf16"), p, bsp.bsp_linear_plan(p), dev(d["bias"], "bf16"))
+    assert_y_close(Y[:64], host(last), "bf16")
+
+
 @pytest.mark.parametrize("R,k_align,T,M,N", [
     (16, 32, 128, 768, 768), (16, 8, 1, 48, 20), (1, 8, 17, 33, 64), (8, 16, 300, 1024, 256), (24, 8, 47, 120, 388),
     (64, 32, 130, 192, 1024), (5, 64, 31, 35, 100), (16, 32, 1100, 2304, 260),   # 16 units per workgroup
