@@ -28,7 +28,12 @@
 namespace bsp {
 namespace {
 
-constexpr int kThreads = 512;
+// Threads of the workgroups that build a plan.  512 shorten the chain of a workgroup (768 x 3072, R = 8, 1.43x: 31.7 us with 256,
+// 28.1 with 512; 4096 x 1024, R = 16 18.5 and 16.0), 256 leave room for more workgroups where there are many: us with 256 / 512 for
+// 576 of them (2304 x 768, R = 4, 1.43x) 18.9 / 17.0, for 1024 (4096 x 1024, R = 4) 27.1 / 32.7, for 1908 (30528 x 768, R = 16)
+// 54.1 / 65.5.
+constexpr int kMaxThreads = 512;
+constexpr int64_t kWideWorkgroups = 768;
 constexpr int kMaxKp = 4096 + 32;
 constexpr int kMaxChunk = 1024 + 32;  // kept columns of one row-block inside one column chunk, padded
 
@@ -41,6 +46,7 @@ __device__ __forceinline__ int slot_index(int set, int group) {
 // One workgroup per block; the result goes to steps_bq[b * kPlanMaxChunks + q].  virt: the plan's block b is made
 // of the stored row-blocks 2 b and 2 b + 1 (8 rows each) and keeps the union of their columns; split > 1: the
 // plan's block b is a 16-row slab of the stored row-block b / split.
+template <int kThreads>
 __global__ __launch_bounds__(kThreads) void plan_count_kernel(const int32_t *__restrict__ blk_cnt,
                                                               const int32_t *__restrict__ blk_ptr,
                                                               const int32_t *__restrict__ col_idx,
@@ -121,7 +127,7 @@ __device__ inline int plan_entry_steps(const PlanShape &P, int w, int e) {
 // its own stream, added up by the whole workgroup (every thread must call; the plan's streams hold a few hundred
 // entries in all).  The workgroups that fill the plan find their places this way instead of waiting for the table.
 __device__ inline int plan_start(const PlanShape &P, int ew, int ee) {
-    __shared__ int s_part[kThreads / 64];
+    __shared__ int s_part[kMaxThreads / 64];
     const int E = P.entries();
     int acc = 0;
     for (int idx = threadIdx.x; idx < ew * E + ee; idx += blockDim.x) acc += plan_entry_steps(P, idx / E, idx % E);
@@ -187,6 +193,7 @@ __device__ inline void plan_write_table(const PlanShape &P, int64_t cap_steps, i
 // its kept columns are the union of theirs, and a step's fragment holds the first one's weights in rows 0-7 and the
 // second one's in rows 8-15 (zeros where only the other one keeps the column).  split > 1: the block is a 16-row slab
 // of the stored row-block pb / split: that block's columns, the slab's rows of its panel.
+template <int kThreads>
 __global__ __launch_bounds__(kThreads) void plan_fill_kernel(int32_t R, int32_t nfrag, int32_t NG, int32_t nacc,
                                                              int32_t chunk_shift,
                                                              int32_t nchunks, const int32_t *__restrict__ blk_cnt,
@@ -482,9 +489,6 @@ extern "C" int bsp_linear_plan(int vdt, int64_t M, int64_t N, int32_t R, int32_t
     int32_t *steps_bq = (int32_t *)((uint8_t *)plan + L.wptr_bytes + L.wfrag_bytes + L.xoff_bytes);
     // a layer of one chunk needs no count (its steps per row-block follow from blk_cnt) unless its blocks are unions
     const bool counted = ch.n > 1 || virt;
-    if (counted)
-        plan_count_kernel<<<(unsigned)B, kThreads, 0, s>>>(blk_cnt, blk_ptr, col_idx, capacity_cols, ch.shift, ch.n,
-                                                           virt ? 1 : 0, split, steps_bq);
     const int32_t nacc = plan_nacc(nf, ch.n > 1, Re);
     const int waves = plan_waves(N, Re, M);
     // One launch fills the plan: a workgroup per (block of the plan, chunk), each finding its place in its stream by
@@ -492,10 +496,18 @@ extern "C" int bsp_linear_plan(int vdt, int64_t M, int64_t N, int32_t R, int32_t
     // a row-block keeps at most N columns, padded to the alignment (at most 64)
     const int32_t cols_cap = (int32_t)(N + 64 < kMaxKp ? (N + 64 + 7) / 8 * 8 : kMaxKp);
     const int64_t filled = ch.n > 1 && min_one ? L.NG * waves * nacc : B;
-    plan_fill_kernel<<<dim3((unsigned)filled + 1, (unsigned)ch.n), kThreads, (size_t)cols_cap * 2 * (virt ? 2 : 1), s>>>(
-        R, nf, (int32_t)L.NG, nacc, ch.shift, ch.n, blk_cnt, blk_ptr, col_idx, (const uint16_t *)vals, capacity_cols,
-        (int64_t)L.steps, wptr, wfrag, xoff, cols_cap, waves, paired, min_one, virt ? 1 : 0, split, (int32_t)B,
-        counted ? steps_bq : nullptr, plan_slack_steps());
+    auto build = [&](auto threads) {
+        constexpr int n = decltype(threads)::value;
+        if (counted)
+            plan_count_kernel<n><<<(unsigned)B, n, 0, s>>>(blk_cnt, blk_ptr, col_idx, capacity_cols, ch.shift, ch.n, virt ? 1 : 0,
+                                                           split, steps_bq);
+        plan_fill_kernel<n><<<dim3((unsigned)filled + 1, (unsigned)ch.n), n, (size_t)cols_cap * 2 * (virt ? 2 : 1), s>>>(
+            R, nf, (int32_t)L.NG, nacc, ch.shift, ch.n, blk_cnt, blk_ptr, col_idx, (const uint16_t *)vals, capacity_cols,
+            (int64_t)L.steps, wptr, wfrag, xoff, cols_cap, waves, paired, min_one, virt ? 1 : 0, split, (int32_t)B,
+            counted ? steps_bq : nullptr, plan_slack_steps());
+    };
+    if (filled * ch.n <= kWideWorkgroups) build(std::integral_constant<int, kMaxThreads>{});
+    else build(std::integral_constant<int, 256>{});
     return check_launch();
 }
 
