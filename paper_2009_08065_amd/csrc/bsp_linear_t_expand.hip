@@ -476,16 +476,30 @@ struct Tile {
     int ft, fn;
 };
 
-Tile choose_tile(int64_t T, int64_t M, int64_t N, double *us = nullptr) {
+// (count: workgroups per compute unit)
+double tile_us(const Tile &c, double count, double stages) {
+    if (c.fn == 2) return __builtin_ceil(count) * (0.70 * stages + 9.0);
+    if (c.ft == 4) return (count <= 1.0 ? 0.46 : 0.515 * (count < 1.8 ? 1.8 : count)) * stages + 7.0;
+    return (count <= 1.0 ? 0.36 : 0.31 * (count < 2.0 ? 2.0 : count)) * stages + 6.0;
+}
+
+// us: the estimate; us_xcd: what it is with the token tiles on one XCD each, as the launch places them (less than 8
+// leave XCDs without work).
+Tile choose_tile(int64_t T, int64_t M, int64_t N, double *us = nullptr, double *us_xcd = nullptr) {
     const double stages = (double)((M + kStageK - 1) / kStageK);
-    auto count = [&](int tt, int nn) { return (double)((T + tt - 1) / tt) * (double)((N + nn - 1) / nn) / 256.0; };  // per unit
-    const double a = count(128, 256), b = count(128, 128), c = count(64, 128);
-    const double ta = __builtin_ceil(a) * (0.70 * stages + 9.0);
-    const double tb = (b <= 1.0 ? 0.46 : 0.515 * (b < 1.8 ? 1.8 : b)) * stages + 7.0;
-    const double tc = (c <= 1.0 ? 0.36 : 0.31 * (c < 2.0 ? 2.0 : c)) * stages + 6.0;
-    if (us) *us = ta < tb ? (ta < tc ? ta : tc) : (tb < tc ? tb : tc);
-    if (ta <= tb && ta <= tc) return {4, 2};
-    return tb <= tc ? Tile{4, 1} : Tile{2, 1};
+    constexpr Tile shapes[] = {{4, 2}, {4, 1}, {2, 1}};
+    Tile best = shapes[0];
+    double best_us = 0.0;
+    for (const Tile &c : shapes) {
+        const int64_t tiles = (T + 32 * c.ft - 1) / (32 * c.ft), ranges = (N + 128 * c.fn - 1) / (128 * c.fn);
+        const double t = tile_us(c, (double)tiles * (double)ranges / 256.0, stages);
+        if (best_us != 0.0 && t >= best_us) continue;
+        best = c;
+        best_us = t;
+        if (us_xcd) *us_xcd = tile_us(c, (double)((tiles + 7) / 8 * 8) * (double)ranges / 256.0, stages);
+    }
+    if (us) *us = best_us;
+    return best;
 }
 
 // The expanded matrix (N columns, M rows); behind it one bit per row-block and column of the pruned matrix.
@@ -566,13 +580,26 @@ size_t linear_expand_bytes(int64_t M, int64_t N, int32_t R) { return expanded_by
 // 8192 tokens, R = 16 at 1.43x 342 / 81, at 5x 115 / 72, 2048 tokens at 5x 41 / 34 (stays), 512 at 5x 19 / 32;
 // 4096 x 1024, 8192 tokens, R = 16 at 1.43x 125 / 107, at 3x 76 / 103, R = 8 at 2x 167 / 104; 3072 x 768, 4096 tokens at 3x
 // 29 / 46.
+// Those leave out what grows with the layer and not with the tokens: the expansion writes the whole matrix, in workgroups
+// of at most 16 rows each, and few token tiles fill few XCDs; and row-blocks of one row, or more than 32.  So a second pair of
+// estimates has to agree, fitted to 2600 calls of 64 x 64 to 30528 x 768 and 16384 x 4096, R = 1 to 64, 1 to 8192 tokens, 1.1x to
+// 10x (the dense one to 15 %, the gather's to a factor of 2).  Of 709 calls that the first pair alone made dense, 39 were slower
+// so: 30528 x 768, R = 8 at 1.1x, one token 20.4 us by the gather and 96.3 dense; 4096 x 1024, R = 1 at 1.43x, 40 tokens 27.6 / 58.7;
+// 16384 x 4096, R = 16 at 1.1x, 40 tokens 115 / 266.
 bool linear_expand_pays(int64_t T, int64_t M, int64_t N, int32_t R, int64_t capacity_cols) {
     const int64_t npad = (N + 255) / 256 * 256, tok = npad <= 1024 ? 64 : (npad <= 2048 ? 32 : 16);
+    const double steps = (double)capacity_cols / 32.0 * (double)((T + tok - 1) / tok) / 256.0;  // per compute unit
     const double per_step = (tok == 64 ? 0.040 : (tok == 32 ? 0.035 : 0.030)) * (R <= 16 ? 1.0 : (R <= 32 ? 2.1 : 4.0));
-    const double gather = 8.0 + per_step * (double)capacity_cols / 32.0 * (double)((T + tok - 1) / tok) / 256.0;
-    double tiles;
-    choose_tile(T, N, M, &tiles);
-    return 8.0 + tiles + (double)T * (double)M * 0.5e-6 < 0.9 * gather;
+    double tiles, tiles_xcd;
+    choose_tile(T, N, M, &tiles, &tiles_xcd);
+    const double out = (double)T * (double)M * 1e-6;
+    if (8.0 + tiles + 0.5 * out >= 0.9 * (8.0 + per_step * steps)) return false;
+    const double workgroups = (double)((M + 255) / 256 * 256 / R) * (double)(npad / 256) * (double)((R + 15) / 16);
+    const double dense = 4.0 + 0.72 * tiles + 0.6 * (tiles_xcd - tiles) + 0.0018 * workgroups + 1.4e-6 * (double)M * (double)N + 0.7 * out;
+    constexpr double kStep[3][3] = {{0.050, 0.105, 1.1}, {0.042, 0.085, 0.39}, {0.042, 0.090, 0.35}};  // [width][R to 16, 32, 64]
+    const double gather = 11.0 + kStep[tok == 64 ? 0 : (tok == 32 ? 1 : 2)][R <= 16 ? 0 : (R <= 32 ? 1 : 2)] * steps +
+                          0.07 * (double)(M / R) * (double)((T + tok - 1) / tok) / 256.0;
+    return dense < gather;
 }
 
 int linear_expand(const void *X, int xdt, int64_t T, int64_t M, int64_t N, int32_t R, const int32_t *blk_cnt,

@@ -104,3 +104,17 @@ def test_expansion_is_not_offered_beyond_its_grid():
     assert L.bsp_linear_transposed_workspace_bytes(bsp.BF16, 4, 64, cols, 16) >= 2 * 64 * cols
     assert L.bsp_linear_transposed_workspace_bytes(bsp.BF16, 4, 64, cols + 1, 16) == 0
     assert L.bsp_linear_transposed_workspace_bytes(bsp.BF16, 4, 64, 1 << 32, 16) == 0
+
+
+def test_expansion_pays_for_enough_tokens_only():
+    """The layer's scratch query: calls whose expansion alone costs more than the gather get none (all three were measured 2 to 5
+    times slower with it), calls of many tokens of layers that keep much get some."""
+    L = bsp.lib()
+    q = L.bsp_linear_workspace_bytes
+    kept = lambda M, N, R, rate: int(M // R * N / rate) // 32 * 32
+    for M, N, R, rate, T in ((30528, 768, 8, 1.1, 1), (30528, 768, 8, 1.1, 40), (4096, 1024, 1, 1.43, 40), (16384, 4096, 16, 1.1, 40),
+                             (16384, 4096, 4, 1.43, 1), (2048, 2048, 1, 1.43, 40)):
+        assert q(bsp.BF16, T, M, N, R, 32, kept(M, N, R, rate)) == 0, (M, N, R, rate, T)
+    for M, N, R, rate, T in ((1024, 4096, 16, 1.43, 8192), (1024, 4096, 16, 5.0, 8192), (768, 3072, 8, 2.0, 4096), (4096, 1024, 16, 1.43, 8192),
+                             (4096, 1024, 1, 1.43, 1100)):
+        assert q(bsp.BF16, T, M, N, R, 32, kept(M, N, R, rate)) > 0, (M, N, R, rate, T)
