@@ -233,6 +233,12 @@ size_t bsp_linear_workspace_bytes(int xdt, int64_t T, int64_t M, int64_t N, int3
 int bsp_linear_ws(const void *X, int xdt, int64_t T, int64_t M, int64_t N, int32_t R, int32_t k_align,
                   const int32_t *blk_cnt, const int32_t *blk_ptr, const int32_t *col_idx, const void *vals,
                   const void *bias, void *Y, void *ws, size_t ws_bytes, void *stream);
+/* bsp_linear_ws for a caller that knows a bound on the storage's padded kept columns (capacity_cols >= 0, as in the query):
+ * in single precision the kernel then follows from what is kept and not from the layer's size alone.  Errors as
+ * bsp_linear_ws, and BSP_ERR_CAPACITY (capacity_cols < 0). */
+int bsp_linear_sized(const void *X, int xdt, int64_t T, int64_t M, int64_t N, int32_t R, int32_t k_align,
+                     const int32_t *blk_cnt, const int32_t *blk_ptr, const int32_t *col_idx, const void *vals,
+                     int64_t capacity_cols, const void *bias, void *Y, void *ws, size_t ws_bytes, void *stream);
 
 /* ---- the transposed product of the pruned layer (Sec. 3.1: with Wp the matrix after Alg. 1
  * the layer is Y = X Wp^T + bias, so the gradient with respect to its input is dX = dY Wp;

@@ -73,6 +73,7 @@ def lib():
     L.bsp_linear_workspace_bytes.argtypes = [C.c_int, i64, i64, i64, i32, i32, i64]
     L.bsp_linear_workspace_bytes.restype = sz
     L.bsp_linear_ws.argtypes = [vp, C.c_int, i64, i64, i64, i32, i32, vp, vp, vp, vp, vp, vp, vp, sz, vp]
+    L.bsp_linear_sized.argtypes = [vp, C.c_int, i64, i64, i64, i32, i32, vp, vp, vp, vp, i64, vp, vp, vp, sz, vp]
     L.bsp_linear_transposed.argtypes = [vp, C.c_int, i64, i64, i64, i32, i32, vp, vp, vp, vp, vp, vp, vp]
     L.bsp_linear_transposed_workspace_bytes.argtypes = [C.c_int, i64, i64, i64, i32]
     L.bsp_linear_transposed_workspace_bytes.restype = sz
@@ -95,7 +96,7 @@ def lib():
     L.bsp_last_hip_error.restype = C.c_int
     L.bsp_version.restype = C.c_char_p
     for name in ("bsp_group_norms", "bsp_penalty_grad", "bsp_prune_mask", "bsp_pack_count", "bsp_pack",
-                 "bsp_packed_validate", "bsp_linear", "bsp_linear_ws", "bsp_linear_transposed", "bsp_linear_transposed_ws", "bsp_linear_transposed_dense", "bsp_linear_dvals", "bsp_linear_plan", "bsp_linear_planned", "bsp_linear_planned_fused",
+                 "bsp_packed_validate", "bsp_linear", "bsp_linear_ws", "bsp_linear_sized", "bsp_linear_transposed", "bsp_linear_transposed_ws", "bsp_linear_transposed_dense", "bsp_linear_dvals", "bsp_linear_plan", "bsp_linear_planned", "bsp_linear_planned_fused",
                  "bsp_mask_weights",
                  "bsp_group_norms_grad", "bsp_adam_step", "bsp_prune_mask_count"):
         getattr(L, name).restype = C.c_int
@@ -373,9 +374,9 @@ def bsp_linear(X, p: Packed, bias=None, Y=None):
     has = p.total_cols > 0
     need = lib().bsp_linear_workspace_bytes(_DT[X.dtype], T, p.M, N, p.R, p.k_align, p.total_cols)
     ws = _scratch(need, X.device)
-    st = lib().bsp_linear_ws(_ptr(X), _DT[X.dtype], T, p.M, N, p.R, p.k_align, _ptr(p.blk_cnt), _ptr(p.blk_ptr),
-                             _ptr(p.col_idx) if has else None, _ptr(p.vals) if has else None, _ptr(bias), _ptr(Y),
-                             _ptr(ws), need, _stream())
+    st = lib().bsp_linear_sized(_ptr(X), _DT[X.dtype], T, p.M, N, p.R, p.k_align, _ptr(p.blk_cnt), _ptr(p.blk_ptr),
+                                _ptr(p.col_idx) if has else None, _ptr(p.vals) if has else None, p.total_cols, _ptr(bias),
+                                _ptr(Y), _ptr(ws), need, _stream())
     _check(st, "bsp_linear")
     return Y
 

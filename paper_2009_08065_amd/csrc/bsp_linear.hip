@@ -244,10 +244,18 @@ extern "C" size_t bsp_linear_workspace_bytes(int xdt, int64_t T, int64_t M, int6
 extern "C" int bsp_linear_ws(const void *X, int xdt, int64_t T, int64_t M, int64_t N, int32_t R, int32_t k_align,
                              const int32_t *blk_cnt, const int32_t *blk_ptr, const int32_t *col_idx, const void *vals,
                              const void *bias, void *Y, void *ws, size_t ws_bytes, void *stream) {
+    return bsp_linear_sized(X, xdt, T, M, N, R, k_align, blk_cnt, blk_ptr, col_idx, vals, INT64_MAX, bias, Y, ws, ws_bytes, stream);
+}
+
+extern "C" int bsp_linear_sized(const void *X, int xdt, int64_t T, int64_t M, int64_t N, int32_t R, int32_t k_align,
+                                const int32_t *blk_cnt, const int32_t *blk_ptr, const int32_t *col_idx, const void *vals,
+                                int64_t capacity_cols, const void *bias, void *Y, void *ws, size_t ws_bytes,
+                                void *stream) {
     if (!X || !blk_cnt || !blk_ptr || !Y) return BSP_ERR_NULL;
     if (!valid_dtype(xdt)) return BSP_ERR_DTYPE;
     if (T < 0 || M <= 0 || N <= 0 || R < 1 || R > 64 || M % R != 0) return BSP_ERR_SHAPE;
     if (!(k_align == 1 || k_align == 8 || k_align == 16 || k_align == 32 || k_align == 64)) return BSP_ERR_SHAPE;
+    if (capacity_cols < 0) return BSP_ERR_CAPACITY;
     if (T == 0) return BSP_OK;
     const int64_t B = M / R;
     const int64_t tok_tiles = (T + 63) / 64;
@@ -285,7 +293,8 @@ extern "C" int bsp_linear_ws(const void *X, int xdt, int64_t T, int64_t M, int64
     } else if (xdt == BSP_F32) {
         const int64_t tiles16 = (T + 15) / 16;
         if (tiles16 >= ((int64_t)1 << 31)) return BSP_ERR_SHAPE;
-        if (linear_f32_tile_supported(N, k_align, col_idx, (const float *)vals))
+        if (linear_f32_tile_supported(N, k_align, col_idx, (const float *)vals) &&
+            linear_f32_tile_pays(T, M, N, R, capacity_cols))
             return launch_linear_f32_tile((const float *)X, T, M, N, R, blk_ptr, col_idx, (const float *)vals,
                                           (const float *)bias, (float *)Y, s);
         linear_f32_mfma_kernel<<<dim3((unsigned)tiles16, (unsigned)B, 1), kThreads, 0, s>>>(

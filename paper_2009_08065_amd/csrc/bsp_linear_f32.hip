@@ -170,6 +170,18 @@ bool linear_f32_tile_supported(int64_t N, int32_t k_align, const int32_t *col_id
     return N % 4 == 0 && k_align % 4 == 0 && col_idx && vals && aligned(col_idx, 16) && f32_lds(N) <= kF32MaxLds;
 }
 
+// The direct-gather kernel stays the faster one where row-blocks keep so little that copying whole rows of X costs more than
+// naming its elements, and all of it fits the chip at once.  Measured, us, direct gather / tile: 512 x 2048 at 100x, 17 tokens
+// 4.3 / 8.3, at 5x 10.2 / 8.9; 2304 x 768, R = 8, one token at 20x 4.3 / 6.9, at 1.43x 10.5 / 7.5; 64 x 64 at every rate 3.9 / 4.7;
+// 512 x 2048 at 100x, 1024 tokens 10 / 12.  Of 936 calls of 64 to 8192 rows, 64 to 2556 columns, 1 to 1024 tokens, 1.43x to
+// 100x, 177 were slower by more than 8 % in the tile, with this rule 31 (most of them up to 20 %).
+bool linear_f32_tile_pays(int64_t T, int64_t M, int64_t N, int32_t R, int64_t capacity_cols) {
+    const double slabs = (double)((R + 15) / 16), blocks = (double)(M / R);
+    const double cols = (double)capacity_cols < blocks * (double)N ? (double)capacity_cols : blocks * (double)N;
+    return cols / blocks * slabs > 64.0 + 0.03 * (double)N ||
+           cols * slabs * (double)((T + 15) / 16) / 256.0 > 128.0 + 0.2 * (double)N;
+}
+
 int launch_linear_f32_tile(const float *X, int64_t T, int64_t M, int64_t N, int32_t R, const int32_t *blk_ptr,
                            const int32_t *col_idx, const float *vals, const float *bias, float *Y, hipStream_t s) {
     const int32_t slabs = (R + 15) / 16;

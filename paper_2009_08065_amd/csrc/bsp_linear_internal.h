@@ -216,7 +216,8 @@ __host__ __device__ inline uint32_t lds_col_offset4(uint32_t c, uint32_t p) {
 __host__ __device__ inline uint32_t lds_bank_group(uint32_t c) { return (c >> 2) & 7u; }
 
 // The layer in single precision on its compact storage, from a tile of X in LDS (bsp_linear_f32.hip): whether these
-// arguments can take it, and its launch.  No argument checks of its own.
+// arguments can take it, whether it is the faster one for these sizes, and its launch.  No argument checks of its own.
+bool linear_f32_tile_pays(int64_t T, int64_t M, int64_t N, int32_t R, int64_t capacity_cols);
 bool linear_f32_tile_supported(int64_t N, int32_t k_align, const int32_t *col_idx, const float *vals);
 int launch_linear_f32_tile(const float *X, int64_t T, int64_t M, int64_t N, int32_t R, const int32_t *blk_ptr,
                            const int32_t *col_idx, const float *vals, const float *bias, float *Y, hipStream_t s);

@@ -106,6 +106,13 @@ def test_expansion_is_not_offered_beyond_its_grid():
     assert L.bsp_linear_transposed_workspace_bytes(bsp.BF16, 4, 64, 1 << 32, 16) == 0
 
 
+def test_linear_sized_refuses_a_negative_count():
+    one = C.c_void_p(16)
+    assert bsp.lib().bsp_linear_sized(one, 0, 4, 64, 64, 16, 32, one, one, one, one, -1, None, one, None, 0, None) == 4
+    assert bsp.lib().bsp_linear_sized(None, 0, 4, 64, 64, 16, 32, one, one, one, one, 64, None, one, None, 0, None) == 1
+    assert bsp.lib().bsp_linear_sized(one, 0, 0, 64, 64, 16, 32, one, one, one, one, 64, None, one, None, 0, None) == 0   # no tokens
+
+
 def test_expansion_pays_for_enough_tokens_only():
     """The layer's scratch query: calls whose expansion alone costs more than the gather get none (all three were measured 2 to 5
     times slower with it), calls of many tokens of layers that keep much get some."""

@@ -629,6 +629,22 @@ def test_linear_f32_tile_and_direct(R, k_align, T, M, N):
     assert torch.equal(bsp.bsp_linear(dev(X), p, dev(d["bias"])), clean)
 
 
+@pytest.mark.parametrize("R,T,M,N,p_keep", [(16, 17, 512, 2048, 0.01), (8, 1, 2304, 768, 0.05), (64, 33, 192, 1024, 0.02), (1, 130, 96, 260, 0.03),
+                                            (16, 40, 64, 68, 0.9), (24, 300, 1200, 512, 0.05)])
+def test_linear_f32_with_and_without_its_size(R, T, M, N, p_keep):
+    """Layers that keep little: the kernel that the known count selects, and the one that the layer's size alone does."""
+    d = wl.layer(7720 + M + N, T, M, N, "f32")
+    keep = wl.bernoulli_keep_mask(7721 + M, M // R, N, p_keep)
+    p_ref = orc.pack(d["W"], R, keep, 32, orc.F32)
+    p = bsp.bsp_pack(dev(d["W"]), R, torch.from_numpy(keep).cuda(), 32)
+    X, bias, Y = dev(d["X"]), dev(d["bias"]), torch.empty((T, M), device="cuda")
+    _check_y(host(bsp.bsp_linear(X, p, bias)), d["X"], p_ref, d["bias"], orc.F32, "f32", None)
+    at = [ctypes.c_void_p(x.data_ptr()) for x in (p.blk_cnt, p.blk_ptr, p.col_idx, p.vals, bias, Y)]
+    assert bsp.lib().bsp_linear(ctypes.c_void_p(X.data_ptr()), bsp.F32, T, M, N, R, 32, *at,
+                                ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)) == 0
+    _check_y(host(Y), d["X"], p_ref, d["bias"], orc.F32, "f32", None)
+
+
 @pytest.mark.parametrize("dtype,R,T,M,N", [
     ("bf16", 16, 1, 16, 32), ("f16", 8, 130, 200, 520), ("bf16", 24, 67, 264, 1000), ("f16", 64, 200, 640, 2056),
     ("bf16", 1, 70, 37, 264), ("bf16", 16, 2100, 1040, 776), ("f16", 32, 4200, 2080, 128), ("bf16", 16, 2048, 768, 3072)])
