@@ -3,7 +3,7 @@
 // or on the prediction loss followed by W = W * Mask (retraining), in one pass over the state.
 //
 // Per parameter 16 bytes are read (w, g, m, v) and 12 written (w, m, v); the factor and the mask
-// byte of a group once per four.  The path is HBM-bound; a lane takes four rows of a group (a column segment
+// byte of a group once per four.  The path is HBM-bound; a lane takes about four rows of a group (a column segment
 // of a row-block), and nothing crosses lanes.
 // Adam itself is Kingma & Ba's Algorithm 1, evaluated in fp32 with one rounding per operation.
 #include "bsp_common.h"
@@ -111,12 +111,15 @@ extern "C" int bsp_adam_step(float *W, const void *G, int gdt, float *m, float *
     h.eps = eps;
     hipStream_t s = (hipStream_t)stream;
     const int64_t cols = (N + kThreads - 1) / kThreads;
-    // Four rows of a row-block per thread: a thread with all of them walks them four loads at a time, and small
+    // About four rows of a row-block per thread: a thread with all of them walks them four loads at a time, and small
     // matrices then have one wavefront per SIMD.  Measured (fp32 state): 24576 x 1024, R = 16, bf16 gradient 121 -> 110 us, fp32
-    // gradient 137 -> 127; 1024 x 1024 10.6 -> 7.1.  The printed form's factor needs the norm of the whole group: all rows.
-    int32_t rows = alpha && mode == BSP_ALPHA_NORM ? R : 4;
-    if (B * ((R + rows - 1) / rows) > 65535) rows = R;
-    const int32_t parts = (R + rows - 1) / rows;
+    // gradient 137 -> 127; 1024 x 1024 10.6 -> 7.1.  In pieces of one size: a piece of one row is a workgroup for a quarter of
+    // the work (R = 5 in pieces of 4 and 1, 27190 x 258: 65.6 us, 44 in one piece; 319 matrices of R = 5 took 1.06 of the time of
+    // whole row-blocks, up to 1.43).  From R = 8 on pieces of at most 5 rows take 0.92 (R = 8) to 0.79 (R = 15) of it; R = 7 0.94
+    // on average, but one matrix in forty 1.1.  The printed form's factor needs the norm of the whole group: all rows.
+    int32_t parts = alpha && mode == BSP_ALPHA_NORM ? 1 : (R + 1) / 4;
+    if (R < 8 || B * parts > 65535) parts = 1;
+    const int32_t rows = (R + parts - 1) / parts;
     const dim3 grid((unsigned)cols, (unsigned)(B * parts));
     BSP_DISPATCH_DTYPE(gdt, GDT, { launch_adam<GDT>(grid, s, W, G, m, v, N, R, rows, parts, alpha, lambda, mode, keep, h); });
     return check_launch();

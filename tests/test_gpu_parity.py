@@ -174,6 +174,12 @@ def test_adam_step_bit_exact(gdt, R, M, N):
             assert not host(Wd)[~np.repeat(keep, R, axis=0).astype(bool)].any()
 
 
+@pytest.mark.parametrize("R,M,N", [(7, 28, 131), (9, 36, 300), (10, 40, 259), (13, 39, 64), (18, 90, 77)])
+def test_adam_step_pieces_of_row_blocks(R, M, N):
+    """Row-blocks that are not whole pieces of four rows: one piece (R = 7), 5 + 4, 5 + 5, 5 + 5 + 3, 5 + 5 + 5 + 3."""
+    test_adam_step_bit_exact("f32", R, M, N)
+
+
 def test_adam_step_argument_checks():
     W = torch.zeros(32, 64, device="cuda")
     L = bsp.lib()
