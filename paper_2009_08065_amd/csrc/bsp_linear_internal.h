@@ -147,8 +147,8 @@ inline double tile_rounds(int64_t tiles, int64_t units) {
     if (tiles < 8) return (double)tile_rounds_all(tiles, units);
     return tile_spread(tiles, units) ? kTileSpread * (double)tile_rounds_all(tiles, units) : (double)tile_rounds_xcd(tiles, units);
 }
-inline int64_t tile_workgroups(int64_t tiles, int64_t units) {
-    return (tile_spread(tiles, units) ? tiles : (tiles + 7) / 8 * 8) * units;
+inline int64_t tile_workgroups(int64_t tiles, int64_t units, bool spread) {
+    return (spread || tiles < 8 ? tiles : (tiles + 7) / 8 * 8) * units;
 }
 __device__ inline void tile_place(uint32_t id, int32_t tiles, int32_t units, int32_t spread, int32_t &tile, int32_t &unit) {
     if (tiles < 8) {
@@ -167,6 +167,10 @@ __device__ inline void tile_place(uint32_t id, int32_t tiles, int32_t units, int
 // what counts is the rounds that a launch takes, times a workgroup's copy-in and walk
 // (microseconds fitted to measurements).  Enough strips to reach 256 workgroups was the rule once: 65 token tiles of a
 // 4096 x 1024 layer were 260 workgroups in two rounds, 68 us at 1.43x, and are 195 in one, 46.
+// Below 256 columns that rule stays, with the units over all XCDs: a workgroup is little more than its start and its output
+// there, which the estimate does not know.  5632 x 32, 5691 tokens 25.0 us before, 29.4 by the estimate; 9792 x 40, 2363 tokens
+// 15.0 and 19.5; of 3807 calls of up to 248 columns 118 were more than 8 % slower by it, for 2.6 % on average.
+constexpr int64_t kNarrowColumns = 256;
 inline double steploop_walk_us(int64_t tiles, int64_t NG, int64_t gps, int64_t N, double steps) {
     return tile_rounds(tiles, (NG + gps - 1) / gps) * (0.0016 * (double)N + 0.42 * steps * (double)gps);
 }
@@ -174,6 +178,11 @@ inline int64_t steploop_groups(int64_t tiles, int64_t NG, int64_t N, double step
     // (the fp32 bias of a strip's quads fills what LDS the tile leaves: 4 KiB per two groups, and a strip of gps groups
     // touches at most gps / 2 + 1 of them)
     constexpr int64_t max_gps = 14;
+    if (N < kNarrowColumns) {
+        const int64_t strips = (256 + tiles - 1) / tiles;
+        const int64_t gps = strips < NG ? (NG + strips - 1) / strips : 1;
+        return gps < max_gps ? gps : max_gps;
+    }
     int64_t best = NG < max_gps ? NG : max_gps;
     for (int64_t gps = best - 1; gps >= 1; --gps)
         if (steploop_walk_us(tiles, NG, gps, N, steps) < steploop_walk_us(tiles, NG, best, N, steps)) best = gps;

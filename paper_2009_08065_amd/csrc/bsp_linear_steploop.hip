@@ -412,7 +412,8 @@ int launch_linear_steploop16(const TiledArgs &a, int64_t max_step, hipStream_t s
     const int64_t ntiles = (a.T + 63) / 64;
     const int64_t gps = steploop_groups(ntiles, NG, a.N, plan_steps(a));
     const int64_t nstrips = (NG + gps - 1) / gps;
-    const int64_t wgs = tile_workgroups(ntiles, nstrips);
+    const bool spread = a.N < kNarrowColumns || tile_spread(ntiles, nstrips);
+    const int64_t wgs = tile_workgroups(ntiles, nstrips, spread);
     if (wgs >= ((int64_t)1 << 31)) return BSP_ERR_SHAPE;
     const size_t lds = kXTileBytes + (size_t)(gps / 2 + 1) * (4 * kSlWaves * 16 * 4);
     auto go = [&](auto kern, size_t &configured) {
@@ -420,7 +421,7 @@ int launch_linear_steploop16(const TiledArgs &a, int64_t max_step, hipStream_t s
         if (st != BSP_OK) return st;
         kern<<<dim3((unsigned)wgs), dim3(kSlWaves * 64), lds, s>>>(
             a.X, a.T, a.M, a.N, a.npad, a.wptr, (const uint8_t *)a.wfrag, (const uint8_t *)a.xoff, a.bias, a.Y,
-            (int32_t)ntiles, (int32_t)gps, (int32_t)NG, (int32_t)a.B, (int32_t)max_step, tile_spread(ntiles, nstrips) ? 1 : 0);
+            (int32_t)ntiles, (int32_t)gps, (int32_t)NG, (int32_t)a.B, (int32_t)max_step, spread ? 1 : 0);
         return check_launch();
     };
     if (a.residual) return BSP_ERR_SHAPE;  // (a residual is added by the kernel that writes its output at its end)

@@ -424,7 +424,8 @@ int launch_linear_stream16(const TiledArgs &a, int64_t max_step, hipStream_t s) 
     const int64_t ntiles = (a.T + 63) / 64;
     const int64_t streams = (a.B + kStNacc - 1) / kStNacc;
     const int cw = stream_waves(ntiles, a.B);
-    const int64_t wgs = tile_workgroups(ntiles, (streams + cw - 1) / cw);
+    const bool spread = tile_spread(ntiles, (streams + cw - 1) / cw);
+    const int64_t wgs = tile_workgroups(ntiles, (streams + cw - 1) / cw, spread);
     if (wgs >= ((int64_t)1 << 31) || ch.n > kPlanMaxChunks) return BSP_ERR_SHAPE;
     if (a.act != BSP_ACT_NONE && a.act != BSP_ACT_GELU) return BSP_ERR_SHAPE;
     if (a.residual && !aligned(a.residual, 8)) return BSP_ERR_SHAPE;
@@ -437,7 +438,7 @@ int launch_linear_stream16(const TiledArgs &a, int64_t max_step, hipStream_t s) 
         kern<<<dim3((unsigned)wgs), dim3((decltype(waves)::value + kStLoadWaves) * 64), lds, s>>>(
             a.X, a.T, a.M, a.N, a.npad, a.wptr, (const uint8_t *)a.wfrag, (const uint8_t *)a.xoff, a.bias, a.Y,
             (int32_t)ntiles, (int32_t)NG, (int32_t)a.B, ch.n, (int32_t)max_step, (const uint16_t *)a.residual,
-            tile_spread(ntiles, (streams + cw - 1) / cw) ? 1 : 0);
+            spread ? 1 : 0);
         return check_launch();
     };
     auto go = [&](auto dt, auto act, auto res) {
