@@ -695,7 +695,8 @@ def test_linear_expanded(dtype, R, T, M, N):
 def test_gelu_over_its_range(dtype, T):
     """GELU of -9 .. 9 and far outside, in the kernel for few tokens and the one for many: zero weights, so the sums are
     the biases.  Bound: one rounding (half a unit in the last place; of fp16's subnormals below 2^-14), and the
-    approximation's error of 1.5e-7 |v|."""
+    approximation's error of 1.5e-7 |v| (an absolute bound: below -5.2 it is more than the value itself, whose relative error it
+    says nothing about)."""
     M, N = 1024, 64
     v = np.concatenate([np.linspace(-9.0, 9.0, M - 4), [-60.0, 60.0, -1e4, 1e4]]).astype(np.float32)
     v = host(dev(v, dtype)).astype(np.float64)
