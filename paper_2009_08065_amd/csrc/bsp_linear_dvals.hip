@@ -39,6 +39,7 @@ constexpr uint32_t kDvXBytes = kDvRange * 64;     // 64 KiB
 constexpr uint32_t kDvYBytes = kDvStrip * 1024;   // 12 KiB: per item 32 tokens x 16 rows
 constexpr int kDvUnits = 256;            // workgroups of the product: one per compute unit
 constexpr size_t kDvHeaderBytes = 256;
+constexpr int kDvRsrcFlags = 0x00020000;  // word 3 of a raw buffer descriptor: 32-bit data, offsets in bytes
 
 struct DvItem {
     int32_t b;      // row-block
@@ -70,6 +71,10 @@ __device__ __forceinline__ uint32_t dv_x_offset(uint32_t c, uint32_t kg) {
     const uint32_t sw = ((c >> 5) & 3u) ^ (((c >> 4) & 1u) << 1);
     return dv_row(c) * 64u + ((kg ^ sw) << 4);
 }
+
+// byte offset of token t's 16 values of dY: the two halves of every other 8 tokens change places, so that the 32 lanes of half
+// a transposing read meet all 64 banks
+__device__ __forceinline__ uint32_t dv_y_offset(uint32_t t) { return (t * 32u) ^ ((t & 8u) << 4); }
 
 // Bank group of column c: the 16 lanes of one pass of a 16-byte LDS read are conflict-free exactly when their
 // columns differ in this number (row modulo 4, and the rotation of the row's pieces).
@@ -148,8 +153,9 @@ __global__ __launch_bounds__(kDvThreads) void dvals_items_kernel(int64_t B, int3
 
     // Deal every item's columns to (group, lane) slots.  The first m groups take one column of every bank group, in
     // the lane of that number: their LDS reads are conflict-free.  Columns of bank groups that hold more than m fill
-    // the groups behind them in any order.  m is the largest number for which one group more than the item's columns
-    // need (16 at most) is enough.  perm[slot] = place of the column among the item's columns, 0xffff = none.
+    // the groups behind them.  m is the number that takes the fewest passes over the LDS banks of those for which one group
+    // more than the item's columns need (16 at most) is enough.  perm[slot] = place of the column among the item's columns,
+    // 0xffff = none.
     {
         const int lane = tid & (kWave - 1), wave = tid / kWave;
         const uint64_t below = ((uint64_t)1 << lane) - 1;
@@ -183,16 +189,28 @@ __global__ __launch_bounds__(kDvThreads) void dvals_items_kernel(int64_t B, int3
                 if (lane == k) mycnt = running;
             }
             const int budget = min(16, (ncols + 15) / 16 + 1);
-            int m = 16, tail = 0;
-            for (; m >= 0; --m) {
-                int over = lane < 16 ? max(0, mycnt - m) : 0;
+            // (passes of an LDS read: one for a group of all bank groups; the columns of one bank group that fill the groups
+            // behind are dealt round these, so one of them takes as many as its fullest bank group has there)
+            int m = 0, tail = 0, best = 1 << 30;
+            for (int mm = 16; mm >= 0; --mm) {
+                int over = lane < 16 ? max(0, mycnt - mm) : 0, most = over;
 #pragma unroll
-                for (int o = 1; o < 16; o <<= 1) over += __shfl_xor(over, o, kWave);
-                tail = over;  // (the same in lanes 0 .. 15; lane 0 decides)
-                tail = __shfl(tail, 0, kWave);
-                if (m + (tail + 15) / 16 <= budget) break;
+                for (int o = 1; o < 16; o <<= 1) {
+                    over += __shfl_xor(over, o, kWave);
+                    most = max(most, __shfl_xor(most, o, kWave));
+                }
+                over = __shfl(over, 0, kWave);  // (the same in lanes 0 .. 15; lane 0 decides)
+                most = __shfl(most, 0, kWave);
+                const int behind = (over + 15) / 16;
+                if (mm + behind > budget) continue;
+                const int passes = mm + (behind ? behind * ((most + behind - 1) / behind) : 0);
+                if (passes < best) {
+                    best = passes;
+                    m = mm;
+                    tail = over;
+                }
             }
-            if (m < 0) m = 0;  // (m = 0 always fits)
+            const int behind = max(1, (tail + 15) / 16);  // groups behind the first m
             int ovf = lane < 16 ? max(0, mycnt - m) : 0, pre = ovf;  // exclusive prefix of the overflow per bank group
 #pragma unroll
             for (int o = 1; o < 16; o <<= 1) {
@@ -207,7 +225,8 @@ __global__ __launch_bounds__(kDvThreads) void dvals_items_kernel(int64_t B, int3
             for (int e = 0; e < 4; ++e) {
                 const int start = __shfl(pre, cls[e] & 15, kWave);
                 if (cls[e] < 16) {
-                    const int slot = rk[e] < m ? rk[e] * 16 + cls[e] : m * 16 + start + rk[e] - m;
+                    const int i = start + rk[e] - m;
+                    const int slot = rk[e] < m ? rk[e] * 16 + cls[e] : (m + i % behind) * 16 + i / behind;
                     mine[slot] = (uint16_t)(lane + kWave * e);
                 }
             }
@@ -248,7 +267,10 @@ __device__ __forceinline__ void dv_ranges(int strips, int ntiles, int &tpu, int 
 // unit), and a wavefront cannot multiply meanwhile, so the two kinds of work belong to different wavefronts.  Two tile
 // buffers in LDS, one workgroup barrier per tile: while tile i is multiplied out of one buffer, the copying
 // wavefronts write tile i + 1 into the other (every wavefront finished reading it before the barrier that ended
-// tile i - 1) and then issue the loads of tile i + 2, which have a whole tile's time to arrive.
+// tile i - 1), piece by piece as it arrives, and ask for the same piece of tile i + 2 at once.
+// 4096 x 1024, 8192 tokens, R = 16, 5x: 51.6 us, 1.3 us a tile (67 and 2.7 when a tile was written whole before the next
+// was asked for); R = 32 at 1.43x, 4099 tokens 66 us (91).  LDS is busy for three quarters of a tile; 20 us are the
+// launch's chain of dependent loads and the 41 MB of partial sums at its end.
 template <int DT>
 __global__ __launch_bounds__(kDvThreads) void dvals_partial_kernel(const uint16_t *__restrict__ X,
                                                                   const uint16_t *__restrict__ dY, int64_t T, int64_t M,
@@ -286,7 +308,8 @@ __global__ __launch_bounds__(kDvThreads) void dvals_partial_kernel(const uint16_
             // ---------------------------------------------------------------- copying wavefronts
             // X: the thread's 4 columns x 32 tokens, one 8-byte load per token; columns past N are read from the last
             // valid place instead (nothing reads those LDS cells).  dY: kDvYPieces pieces of 8 rows of one token.
-            // Tokens past T must be zeros in both operands (only the last tile can hold some).
+            // Tokens past T must be zeros in both operands: a tile is read through buffer descriptors that end behind
+            // its last token, and what lies past a descriptor's end reads as zero -- all of it for a tile past the last.
             const int cqc = col0 + 4 * ltid + 4 <= N ? 4 * ltid : (int)(N - col0 - 4);
             uint32_t yoff[kDvYPieces];  // byte offset of the piece from the tile's first token row of dY
             uint32_t ydst[kDvYPieces];
@@ -298,58 +321,59 @@ __global__ __launch_bounds__(kDvThreads) void dvals_partial_kernel(const uint16_
                 // (for R = 8 the upper half of the last row-block's slab lies past M: its rows are never written out)
                 const int64_t row = row0 + 8 * half + 8 <= M ? row0 + 8 * half : row0;
                 yoff[e] = 2u * ((uint32_t)tok * (uint32_t)M + (uint32_t)row);
-                ydst[e] = kDvXBytes + (uint32_t)it * 1024u + (uint32_t)tok * 32u + (uint32_t)half * 16u;
+                ydst[e] = kDvXBytes + (uint32_t)it * 1024u + dv_y_offset((uint32_t)tok) + (uint32_t)half * 16u;
             }
             uint2 xa[kDvTok];
             uint4 ya[kDvYPieces];
-            auto issue = [&](int tile) {
+            // A tile moves in four pieces: 8 tokens of X (and a piece of dY with the first three).
+            auto tile_of = [&](const uint16_t *p, int64_t first, int64_t width, int tile) __attribute__((always_inline)) {  // rows of `width` elements
                 const int64_t t0 = (int64_t)tile * kDvTok;
-                const int left = (int)(T - t0 < kDvTok ? T - t0 : kDvTok);
-                const uint8_t *xrow = reinterpret_cast<const uint8_t *>(X + t0 * N + col0) + 2 * cqc;
-#pragma unroll
-                for (int t = 0; t < kDvTok; ++t) {
-                    xa[t] = t < left ? *reinterpret_cast<const uint2 *>(xrow) : make_uint2(0u, 0u);  // (t < left: uniform)
-                    xrow += 2 * N;
-                }
-                const uint8_t *yrow = reinterpret_cast<const uint8_t *>(dY + t0 * M);
-#pragma unroll
-                for (int e = 0; e < kDvYPieces; ++e) {
-                    const int tok = ((ltid + kDvLoadThreads * e) & 63) >> 1;
-                    ya[e] = tok < left ? *reinterpret_cast<const uint4 *>(yrow + yoff[e]) : make_uint4(0u, 0u, 0u, 0u);
-                }
+                const int left = tile < tile1 ? (int)(T - t0 < kDvTok ? T - t0 : kDvTok) : 0;
+                const int64_t bytes = left ? 2 * (left * width - first) : 0;
+                return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(p + (left ? t0 : 0) * width + first), 0, (int)bytes, kDvRsrcFlags);
             };
-            auto commit = [&](uint32_t buf) {
+            auto issue = [&](auto piece, __amdgpu_buffer_rsrc_t xr, __amdgpu_buffer_rsrc_t yr) __attribute__((always_inline)) {
+                constexpr int g = decltype(piece)::value;
+#pragma unroll
+                for (int t = 8 * g; t < 8 * g + 8; ++t)
+                    xa[t] = __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(xr, 2 * (cqc + t * (int)N), 0, 0));
+                if constexpr (g < kDvYPieces) ya[g] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(yr, (int)yoff[g], 0, 0));
+            };
+            auto commit = [&](auto piece, uint32_t buf) __attribute__((always_inline)) {
+                constexpr int g = decltype(piece)::value;
                 uint8_t *base = smem_x + buf * kBuf;
                 // column c + j, tokens 8 g .. 8 g + 7: the j-th 16-bit field of eight consecutive loads
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
+                    uint32_t w[4];
 #pragma unroll
-                    for (int g = 0; g < 4; ++g) {
-                        uint32_t w[4];
-#pragma unroll
-                        for (int h = 0; h < 4; ++h) {
-                            const uint2 lo = xa[8 * g + 2 * h], hi = xa[8 * g + 2 * h + 1];
-                            const uint32_t a = j < 2 ? lo.x : lo.y, bb = j < 2 ? hi.x : hi.y;
-                            w[h] = (j & 1) ? ((a >> 16) | (bb & 0xffff0000u)) : ((a & 0xffffu) | (bb << 16));
-                        }
-                        *reinterpret_cast<uint4 *>(base + dv_x_offset(4u * (uint32_t)ltid + (uint32_t)j, (uint32_t)g)) =
-                            make_uint4(w[0], w[1], w[2], w[3]);
+                    for (int h = 0; h < 4; ++h) {
+                        const uint2 lo = xa[8 * g + 2 * h], hi = xa[8 * g + 2 * h + 1];
+                        w[h] = __builtin_amdgcn_perm(j < 2 ? hi.x : hi.y, j < 2 ? lo.x : lo.y, (j & 1) ? 0x07060302u : 0x05040100u);
                     }
+                    *reinterpret_cast<uint4 *>(base + dv_x_offset(4u * (uint32_t)ltid + (uint32_t)j, (uint32_t)g)) =
+                        make_uint4(w[0], w[1], w[2], w[3]);
                 }
-#pragma unroll
-                for (int e = 0; e < kDvYPieces; ++e) *reinterpret_cast<uint4 *>(base + ydst[e]) = ya[e];
+                if constexpr (g < kDvYPieces) *reinterpret_cast<uint4 *>(base + ydst[g]) = ya[g];
             };
+            {
+                const auto x0 = tile_of(X, col0, N, tile0), y0 = tile_of(dY, 0, M, tile0);
+                static_for<0, 4>([&](auto g) { issue(g, x0, y0); });
+                const auto x1 = tile_of(X, col0, N, tile0 + 1), y1 = tile_of(dY, 0, M, tile0 + 1);
+                static_for<0, 4>([&](auto g) { commit(g, 0u); issue(g, x1, y1); });
+            }
             __syncthreads();
-            issue(tile0);
-            commit(0);
-            if (tile0 + 1 < tile1) issue(tile0 + 1);
             __syncthreads();
+            // Every piece of tile + 1 goes to LDS as it arrives and its registers take the load of tile + 2 at once.
             for (int tile = tile0; tile < tile1; ++tile) {
-                const uint32_t cur = (uint32_t)(tile - tile0) & 1u;
-                if (tile + 1 < tile1) {
-                    commit(cur ^ 1u);
-                    if (tile + 2 < tile1) issue(tile + 2);
-                }
+                const auto xr = tile_of(X, col0, N, tile + 2), yr = tile_of(dY, 0, M, tile + 2);
+                const uint32_t next = (uint32_t)(tile + 1 - tile0) & 1u;
+                static_for<0, 4>([&](auto g) {
+                    commit(g, next);
+                    __builtin_amdgcn_sched_barrier(0);
+                    issue(g, xr, yr);
+                    __builtin_amdgcn_sched_barrier(0);
+                });
                 __syncthreads();
             }
         } else {
@@ -368,7 +392,7 @@ __global__ __launch_bounds__(kDvThreads) void dvals_partial_kernel(const uint16_
             }
             // the lane's address inside the item's dY rows for the transposing read (token 8 kg + qd, rows 4 p4 ..
             // 4 p4 + 3; the second read takes the token 4 further on)
-            const uint32_t a_off = kDvXBytes + (uint32_t)wave * 1024u + (uint32_t)(8 * kg + qd) * 32u + (uint32_t)p4 * 8u;
+            const uint32_t a_off = kDvXBytes + (uint32_t)wave * 1024u + dv_y_offset((uint32_t)(8 * kg + qd)) + (uint32_t)p4 * 8u;
             __syncthreads();
             __syncthreads();
             for (int tile = tile0; tile < tile1; ++tile) {
@@ -377,7 +401,7 @@ __global__ __launch_bounds__(kDvThreads) void dvals_partial_kernel(const uint16_
                 // the current one is multiplied; a group past the item's last one multiplies some column into an
                 // accumulator that is never written out.
                 const uint2 lo = tr_read(xt, a_off);
-                const uint2 hi = tr_read(xt, a_off + 4 * 32);
+                const uint2 hi = tr_read(xt, a_off ^ (4 * 32));  // (token 8 kg + qd + 4)
                 const uint4 a = make_uint4(lo.x, lo.y, hi.x, hi.y);
                 uint4 bq[2][4];
                 auto read_quad = [&](auto Q, uint4(&dst)[4]) {
@@ -565,7 +589,7 @@ extern "C" int bsp_linear_dvals(const void *X, const void *dY, int xdt, int64_t 
     if (B >= ((int64_t)1 << 31) - 65536 || (double)R * (double)capacity_cols >= 9.0e18) return BSP_ERR_SHAPE;
     hipStream_t s = (hipStream_t)stream;
     const int64_t ntiles = (T + kDvTok - 1) / kDvTok;
-    const bool fast = xdt != BSP_F32 && T > 0 && R % 8 == 0 && R <= 64 && N % 4 == 0 && N < ((int64_t)1 << 22) &&
+    const bool fast = xdt != BSP_F32 && T > 0 && R % 8 == 0 && R <= 64 && N % 4 == 0 && N < ((int64_t)1 << 22) && M < ((int64_t)1 << 26) &&
                       ntiles < ((int64_t)1 << 30) && capacity_cols < ((int64_t)1 << 31) && aligned(X, 8) &&
                       aligned(dY, 16) && ws && aligned(ws, 256);
     if (fast) {
