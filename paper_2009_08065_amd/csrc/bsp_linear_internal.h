@@ -196,7 +196,7 @@ inline int64_t steploop_groups(int64_t tiles, int64_t NG, int64_t N, double step
 // 15.2 / 12.6 / 23.8.
 inline double stream_load(int64_t tiles, int64_t B, int waves) {
     const int64_t streams = (B + 3) / 4;
-    return tile_rounds(tiles, (streams + waves - 1) / waves) * (waves == 8 ? 1.0 : (waves == 4 ? 0.82 : 0.76));
+    return tile_rounds(tiles, (streams + waves - 1) / waves) * (waves == 8 ? 1.0 : (waves == 4 ? 0.77 : 0.70));
 }
 inline int stream_waves(int64_t tiles, int64_t B) {
     int best = 8;

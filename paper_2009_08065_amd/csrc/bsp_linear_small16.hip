@@ -306,10 +306,13 @@ namespace {
 
 // Microseconds that a call takes, launch included, by the kernels for many tokens and by this one; from layers of 256 to
 // 4096 columns at 1.4x to 5x and 8 to 4099 tokens, to about 15 %.  steps: of a row-block, over all chunks.
-double estimate_many(const TiledArgs &a, const SmPlan &P, double steps) {
-    const int64_t tiles = (a.T + 63) / 64;
+double estimate_many(const TiledArgs &a, const SmPlan &P, int64_t T, double steps) {
+    const int64_t tiles = (T + 63) / 64;
     if (P.nq > 1) {
-        return 5.0 + stream_load(tiles, a.B, stream_waves(tiles, a.B)) * (0.4 + 1.5 * P.nq + 0.35 * steps);
+        const int waves = stream_waves(tiles, a.B);
+        // (that kernel's GELU: 384 x 1536 at 5x, 3344 tokens 9.9 us without, 13.7 with)
+        const double gelu = a.act == BSP_ACT_GELU ? 5.4 : 0.0;
+        return 5.0 + stream_load(tiles, a.B, waves) * (0.4 + 1.5 * P.nq + (waves == 8 ? 0.43 : 0.38) * steps + gelu);
     }
     const int64_t gps = steploop_groups(tiles, P.NG, a.N, steps);
     return 4.5 + steploop_walk_us(tiles, P.NG, gps, a.N, steps);
@@ -319,8 +322,8 @@ struct SmShape {
     int nw, nsub, nb;
 };
 
-double estimate_few(const TiledArgs &a, double steps, const SmShape &c) {
-    const double wgs = (double)((a.T + 16 * c.nsub - 1) / (16 * c.nsub)) * (double)((a.B + c.nb - 1) / c.nb) / 256.0;
+double estimate_few(const TiledArgs &a, int64_t T, double steps, const SmShape &c) {
+    const double wgs = (double)((T + 16 * c.nsub - 1) / (16 * c.nsub)) * (double)((a.B + c.nb - 1) / c.nb) / 256.0;
     const double mine = steps * (double)c.nb / (double)c.nw;  // steps of a wavefront
     const double one = 4.8 + 0.0003 * (double)a.N + (c.nw == 16 ? 0.20 : (c.nsub == 2 ? 0.18 : 0.11)) * mine;
     if (wgs <= 1.0) return one;
@@ -335,12 +338,38 @@ int launch_shape(const TiledArgs &a, const SmPlan &P, const SmShape &c, hipStrea
     return c.nsub == 2 ? launch_small<DT, 2, 8>(a, P, c.nb, s) : launch_small<DT, 1, 8>(a, P, c.nb, s);
 }
 
+// The shape with the least estimated time for T tokens, if that is below us (which becomes it).
+SmShape choose_shape(const TiledArgs &a, int64_t T, double steps, double &us) {
+    constexpr SmShape shapes[] = {{8, 1, 1}, {8, 1, 2}, {8, 1, 4}, {8, 1, 8}, {8, 2, 4}, {8, 2, 8}, {16, 1, 8}, {16, 1, 16}, {16, 1, 32}};
+    SmShape best = {0, 0, 0};
+    for (const SmShape &c : shapes) {
+        if (c.nsub * a.npad > 4096) continue;  // (128 KiB of LDS)
+        const double t = estimate_few(a, T, steps, c);
+        if (t < us) us = t, best = c;
+    }
+    return best;
+}
+
+// The same call on rows first .. first + count - 1 of the batch.
+TiledArgs token_rows(const TiledArgs &a, int64_t first, int64_t count) {
+    TiledArgs r = a;
+    r.X = a.X + first * a.N;
+    r.Y = (uint16_t *)a.Y + first * a.M;
+    if (a.residual) r.residual = (const uint16_t *)a.residual + first * a.M;
+    r.T = count;
+    return r;
+}
+
 }  // namespace
 
 // True when this layer's call was taken (status in st).  Which kernel and which shape: the one with the least estimated
 // time.  Measured, us (many tokens / this one): 2304 x 768 at 2x, 24 tokens 10.4 / 5.0, 400 tokens 10.9 / 7.6,
 // 1200 tokens 11.7 / 15.3 (stays); 768 x 3072 at 2x, 24 tokens 31 / 6.3, 400 tokens 31 / 12.2, 1537 tokens 34 / 24.3
 // and at 3x 26.7 / 19.2; 1024 x 4096 at 5x, 2048 tokens 26.1 / 23.0, 4099 tokens 29.6 / 60 (stays).
+// A batch a little longer than a whole number of token tiles on every XCD costs the kernels for many tokens a round of
+// mostly idle compute units, or the wide split that avoids it: then the tiles that are too many come here and only the others go
+// there, if that is less by the estimates: whole / in two, us, 1024 x 4096 with a residual at 1.43x, 4099 tokens 57.0 / 52.7, at 2x,
+// 8200 tokens 81.0 / 54.0; 4096 x 1024 with GELU at 1.43x, 4099 tokens 44.3 / 42.4; 2048 x 512 at 1.5x, 8200 tokens 28.1 / 24.3.
 bool launch_linear_small16(const TiledArgs &a, int64_t max_step, hipStream_t s, int &st) {
     const PlanChunks ch = plan_chunks(a.N, a.R, a.M);
     const bool chunked = ch.n > 1;
@@ -356,13 +385,20 @@ bool launch_linear_small16(const TiledArgs &a, int64_t max_step, hipStream_t s, 
     P.max_step = (int32_t)max_step;
     const double steps = plan_steps(a);
 
-    SmShape best = {0, 0, 0};
-    double best_us = 0.85 * estimate_many(a, P, steps);  // (the estimates' spread: near a tie the other kernels stay)
-    constexpr SmShape shapes[] = {{8, 1, 1}, {8, 1, 2}, {8, 1, 4}, {8, 1, 8}, {8, 2, 4}, {8, 2, 8}, {16, 1, 8}, {16, 1, 16}, {16, 1, 32}};
-    for (const SmShape &c : shapes) {
-        if (c.nsub * a.npad > 4096) continue;  // (128 KiB of LDS)
-        const double us = estimate_few(a, steps, c);
-        if (us < best_us) best_us = us, best = c;
+    const double many_us = estimate_many(a, P, a.T, steps);
+    double best_us = 0.85 * many_us;  // (the estimates' spread: near a tie the other kernels stay)
+    const SmShape best = choose_shape(a, a.T, steps, best_us);
+    const int64_t tiles = (a.T + 63) / 64, over = tiles % 8;
+    if (best.nw == 0 && tiles > 24 && over >= 1 && over <= 4 && aligned(a.Y, 16)) {
+        const int64_t head = (tiles - over) * 64;
+        double tail_us = 0.95 * many_us - estimate_many(a, P, head, steps);
+        const SmShape c = choose_shape(a, a.T - head, steps, tail_us);
+        if (c.nw != 0) {
+            const TiledArgs first = token_rows(a, 0, head), rest = token_rows(a, head, a.T - head);
+            st = chunked ? launch_linear_stream16(first, max_step, s) : launch_linear_steploop16(first, max_step, s);
+            if (st == BSP_OK) st = a.xdt == BSP_BF16 ? launch_shape<BSP_BF16>(rest, P, c, s) : launch_shape<BSP_F16>(rest, P, c, s);
+            return true;
+        }
     }
     if (best.nw == 0) return false;
     st = a.xdt == BSP_BF16 ? launch_shape<BSP_BF16>(a, P, best, s) : launch_shape<BSP_F16>(a, P, best, s);

@@ -136,6 +136,95 @@ constexpr int kStChunk = 512;  // columns
           [c67] "s"(cnt[3])                                                                                       \
         : ST_CLOBBERS)
 
+// The same walk for workgroups of four or two multiplying wavefronts, which have 168 registers each: operands of six steps
+// and X fragments of three on their way.  With one wavefront on a SIMD nothing covers another's waits: a ring of four
+// steps takes a fourth of an L2 trip per step and X fragments requested one step ahead an LDS trip.  1024 x 4096 at 1.43x
+// with a residual, 4096 tokens 47.2 -> 42.8 us; 768 x 3072 in 8-row blocks at 3x, 1537 tokens 27.3 -> 24.1.
+// Registers: v64-87 fragments of six steps, v88-93 offset words, v94-109 / v110-125 / v126-141 X fragments of steps 0, 1, 2
+// modulo 3, v142-148 as v116-122 above (the fragment pointer is 2 KiB further on: offsets reach from -4 to 4 KiB).
+#define SD_W(J) "v[64+4*" #J ":67+4*" #J "]"
+#define SD_O(J) "v[88+" #J "]"
+#define SD_XP(P, U, H) "v[94+16*" #P "+4*" #U "+2*" #H ":95+16*" #P "+4*" #U "+2*" #H "]"
+#define SD_XQ(P, U) "v[94+16*" #P "+4*" #U ":97+16*" #P "+4*" #U "]"
+#define SD_LOAD(J)                                                            \
+    "global_load_dword " SD_O(J) ", v146, s[42:43] offset:64*" #J "\n"          \
+    "global_load_dwordx4 " SD_W(J) ", v145, s[40:41] offset:1024*" #J "-2048\n"
+#define SD_ADVANCE                                         \
+    "s_add_u32 s40, s40, 6144\n s_addc_u32 s41, s41, 0\n"  \
+    "s_add_u32 s42, s42, 384\n s_addc_u32 s43, s43, 0\n"
+#define SD_ADDR(JN)                                                                                            \
+    "v_xor_b32 v144, " SD_O(JN) ", v147\n"                                                                     \
+    "v_lshlrev_b32_sdwa v142, v148, v144 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_0\n" \
+    "v_lshlrev_b32_sdwa v143, v148, v144 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1\n"
+#define SD_RD(PN, U, OFF)                                              \
+    "ds_read_b64_tr_b16 " SD_XP(PN, U, 0) ", v142 offset:" #OFF "\n"     \
+    "ds_read_b64_tr_b16 " SD_XP(PN, U, 1) ", v143 offset:" #OFF "\n"
+#define SD_READS(JN, PN) SD_ADDR(JN) SD_RD(PN, 0, 0) SD_RD(PN, 1, 16384) SD_RD(PN, 2, 32768) SD_RD(PN, 3, 49152)
+#define SD_MF(MFMA, A, J, P, U) MFMA " %[a" #A #U "], " SD_W(J) ", " SD_XQ(P, U) ", %[a" #A #U "]\n"
+// One step at ring slot J, X set P; JN, PN are those of the step after the next.  vmcnt(7): the weights of this step and the
+// offsets of that one are there; lgkmcnt(8): the X fragments of this step are.
+#define SD_STEP(MFMA, A, J, JN, P, PN)                      \
+    "s_waitcnt vmcnt(7)\n"                                  \
+    SD_ADDR(JN)                                             \
+    "s_waitcnt lgkmcnt(8)\n"                                \
+    SD_MF(MFMA, A, J, P, 0) SD_RD(PN, 0, 0)                 \
+    SD_MF(MFMA, A, J, P, 1) SD_RD(PN, 1, 16384)             \
+    SD_MF(MFMA, A, J, P, 2) SD_RD(PN, 2, 32768)             \
+    SD_MF(MFMA, A, J, P, 3) SD_RD(PN, 3, 49152)             \
+    SD_LOAD(J)                                              \
+    "s_sub_u32 s44, s44, 1\n"                               \
+    "s_cbranch_scc1 Lend" #A "_" #J "_%=\n"                 \
+    "Lres" #A "_" #J "_%=:\n"
+#define SD_SET(MFMA, A)                                                                                   \
+    "Ltop" #A "_%=:\n"                                                                                    \
+    SD_STEP(MFMA, A, 0, 2, 0, 2) SD_STEP(MFMA, A, 1, 3, 1, 0) SD_STEP(MFMA, A, 2, 4, 2, 1)                \
+    SD_STEP(MFMA, A, 3, 5, 0, 2) SD_STEP(MFMA, A, 4, 0, 1, 0) SD_STEP(MFMA, A, 5, 1, 2, 1)                \
+    SD_ADVANCE                                                                                            \
+    "s_branch Ltop" #A "_%=\n"
+#define SD_NEXT_RUNS(A, AN) ST_NEXT_RUN(A, AN, 0) ST_NEXT_RUN(A, AN, 1) ST_NEXT_RUN(A, AN, 2) \
+                            ST_NEXT_RUN(A, AN, 3) ST_NEXT_RUN(A, AN, 4) ST_NEXT_RUN(A, AN, 5)
+// The chunk has ended behind ring slot J: the X fragments of the next two steps (every chunk has at least four) are
+// requested again behind the barrier.
+#define SD_NEXT_CHUNK(J, JN, PN, JM, PM)                                                       \
+    "Lend3_" #J "_%=:\n"                                                                       \
+    "s_sub_u32 s45, s45, 1\n"                                                                  \
+    "s_cbranch_scc1 Ldone%=\n"                                                                 \
+    "s_mov_b32 s46, s47\n s_mov_b32 s47, s48\n s_mov_b32 s48, s49\n s_mov_b32 s49, s50\n"      \
+    "s_mov_b32 s50, s51\n s_mov_b32 s51, s52\n s_mov_b32 s52, s53\n"                           \
+    "s_and_b32 s44, s46, 0xff\n s_sub_u32 s44, s44, 1\n"                                       \
+    "s_waitcnt lgkmcnt(0)\n"                                                                   \
+    "s_barrier\n"                                                                              \
+    SD_READS(JN, PN) SD_READS(JM, PM)                                                          \
+    "s_branch Lres0_" #J "_%=\n"
+#define SD_CLOBBERS                                                                                                    \
+    "v123", "v124", "v125", "v126", "v127", "v128", "v129", "v130", "v131", "v132", "v133", "v134", "v135", "v136",    \
+        "v137", "v138", "v139", "v140", "v141", "v142", "v143", "v144", "v145", "v146", "v147", "v148", ST_CLOBBERS
+#define SD_WALK(MFMA)                                                                                             \
+    asm volatile(                                                                                                 \
+        "s_mov_b64 s[40:41], %[wb]\n s_mov_b64 s[42:43], %[ob]\n s_sub_u32 s45, %[nq], 1\n"                       \
+        "s_add_u32 s40, s40, 2048\n s_addc_u32 s41, s41, 0\n"                                                     \
+        "s_mov_b64 s[46:47], %[c01]\n s_mov_b64 s[48:49], %[c23]\n s_mov_b64 s[50:51], %[c45]\n"                  \
+        "s_mov_b64 s[52:53], %[c67]\n"                                                                            \
+        "v_mbcnt_lo_u32_b32 v144, -1, 0\n v_mbcnt_hi_u32_b32 v144, -1, v144\n"                                    \
+        "v_lshlrev_b32 v145, 4, v144\n v_and_b32 v146, 0xfc, v144\n"                                              \
+        "v_and_b32 v147, 3, v144\n v_lshl_or_b32 v147, v147, 16, v147\n v_mov_b32 v148, 3\n"                      \
+        SD_LOAD(0) SD_LOAD(1) SD_LOAD(2) SD_LOAD(3) SD_LOAD(4) SD_LOAD(5) SD_ADVANCE                              \
+        "s_and_b32 s44, s46, 0xff\n s_sub_u32 s44, s44, 1\n"                                                      \
+        "s_barrier\n" /* the first chunk is there */                                                              \
+        "s_waitcnt vmcnt(9)\n"                                                                                    \
+        SD_READS(0, 0) SD_READS(1, 1)                                                                             \
+        SD_SET(MFMA, 0) SD_SET(MFMA, 1) SD_SET(MFMA, 2) SD_SET(MFMA, 3)                                           \
+        SD_NEXT_RUNS(0, 1) SD_NEXT_RUNS(1, 2) SD_NEXT_RUNS(2, 3)                                                  \
+        SD_NEXT_CHUNK(0, 1, 1, 2, 2) SD_NEXT_CHUNK(1, 2, 2, 3, 0) SD_NEXT_CHUNK(2, 3, 0, 4, 1)                    \
+        SD_NEXT_CHUNK(3, 4, 1, 5, 2) SD_NEXT_CHUNK(4, 5, 2, 0, 0) SD_NEXT_CHUNK(5, 0, 0, 1, 1)                    \
+        "Ldone%=:\n"                                                                                              \
+        "s_waitcnt vmcnt(0) lgkmcnt(0)\n"                                                                         \
+        "s_nop 15\n s_nop 7\n" /* the last matrix instruction has written its result */                           \
+        : ST_ACC_OPERANDS                                                                                         \
+        : [wb] "s"(wb), [ob] "s"(ob), [nq] "s"(nq), [c01] "s"(cnt[0]), [c23] "s"(cnt[1]), [c45] "s"(cnt[2]),      \
+          [c67] "s"(cnt[3])                                                                                       \
+        : SD_CLOBBERS)
+
 // Loads of one chunk of X by the copying wavefronts: thread j of 256 takes units j, j + 256, ... (a unit = 4 columns
 // x 4 tokens); the values wait in registers until the half of the tile they go to is free.
 constexpr int kStUnits = 4;  // per thread: 64 tokens x 512 columns / 16 / 512
@@ -315,8 +404,13 @@ __global__ __launch_bounds__((CW + kStLoadWaves) * 64) void linear_stream16_kern
     for (int i = 0; i < 4; ++i)
         cnt[i] = (uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)cnt[i]) |
                  ((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(cnt[i] >> 32)) << 32);
-    if constexpr (DT == BSP_BF16) ST_WALK("v_mfma_f32_16x16x32_bf16");
-    else ST_WALK("v_mfma_f32_16x16x32_f16");
+    if constexpr (CW == 8) {
+        if constexpr (DT == BSP_BF16) ST_WALK("v_mfma_f32_16x16x32_bf16");
+        else ST_WALK("v_mfma_f32_16x16x32_f16");
+    } else {
+        if constexpr (DT == BSP_BF16) SD_WALK("v_mfma_f32_16x16x32_bf16");
+        else SD_WALK("v_mfma_f32_16x16x32_f16");
+    }
 
     // ---- output: bias, activation, residual, rounding, lane re-deal, whole lines ----
     if (b0 >= B) return;

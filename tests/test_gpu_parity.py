@@ -599,6 +599,28 @@ def test_linear_planned_few_and_many_tokens(dtype, R, M, N, act, with_res):
             assert_y_close(Y[i], Y_ref, dtype)
 
 
+@pytest.mark.parametrize("dtype,R,T,M,N,rate,act,with_res", [
+    ("bf16", 32, 4099, 1024, 2048, 1.3, bsp.ACT_NONE, True), ("f16", 16, 8200, 1024, 4096, 2.0, bsp.ACT_GELU, True),
+    ("bf16", 16, 4100, 4096, 1024, 1.4, bsp.ACT_GELU, False), ("f16", 16, 8195, 2048, 512, 1.5, bsp.ACT_NONE, False)])
+def test_linear_planned_batch_in_two(dtype, R, T, M, N, rate, act, with_res):
+    """Batches a few tokens longer than 8 n tiles, whose end goes through the kernel for few tokens: rows on both sides of the
+    seam and the last, with and without epilogue."""
+    d = wl.layer(7600 + M + N, T, M, N, dtype)
+    keep = wl.bernoulli_keep_mask(7601 + M, M // R, N, 1.0 / rate)
+    p_ref = orc.pack(d["W"], R, keep, 32, CODE[dtype])
+    p = bsp.bsp_pack(dev(d["W"], dtype), R, torch.from_numpy(keep).cuda(), 32)
+    res = wl.layer(7602 + M, T, 16, M, dtype)["X"] if with_res else None
+    Y = torch.full((T, M), 7.0, dtype=dev(d["X"][:1], dtype).dtype, device="cuda")
+    bsp.bsp_linear_planned_fused(dev(d["X"], dtype), p, bsp.bsp_linear_plan(p), dev(d["bias"], dtype), act=act,
+                                 residual=dev(res, dtype) if with_res else None, Y=Y)
+    Y, seam = host(Y), T // 512 * 512
+    code = orc.ACT_GELU if act else orc.ACT_NONE
+    for lo, hi in ((0, 16), (seam - 16, T)):
+        ref, _ = orc.linear_packed_fused(d["X"][lo:hi], p_ref, d["bias"], act=code, residual=res[lo:hi] if with_res else None,
+                                         ydt=CODE[dtype], n_threads=16)
+        assert_y_close(Y[lo:hi], ref, dtype)
+
+
 @pytest.mark.parametrize("R,T,M,N", [(16, 600, 32768, 64), (8, 1090, 30528, 72), (16, 577, 16400, 1544), (32, 1030, 30528, 2056)])
 def test_linear_planned_tall_layers(R, T, M, N):
     """Tall layers of 9 to 18 ragged token tiles, whose workgroups go to all compute units and not tile by tile to the XCDs: every
