@@ -15,7 +15,11 @@
 // columns of X go into LDS transposed (64 bytes per column: a lane's operand, 8 consecutive tokens of its own kept
 // column, is one 16-byte read) and the items' 16 columns of dY untransposed (the transposing LDS read delivers the
 // other operand).
+//
+// That form pays where a layer keeps little and the batch is large; elsewhere the call is a dense product of which the kept
+// positions are written (bsp_linear_dvals_dense.hip; dvals_dense_pays decides).
 #include "bsp_common.h"
+#include "bsp_linear_internal.h"
 #include "bsp_mfma_device.h"
 
 namespace bsp {
@@ -107,7 +111,13 @@ __global__ __launch_bounds__(kDvThreads) void dvals_items_kernel(int64_t B, int3
                                                                 DvItem *__restrict__ items,
                                                                 uint16_t *__restrict__ perm,
                                                                 uint16_t *__restrict__ slotcol,
-                                                                int32_t *__restrict__ groups) {
+                                                                int32_t *__restrict__ groups, int32_t tables,
+                                                                int32_t *__restrict__ colstart) {
+    // for the dense form: entry j of row-block b's table counts its kept columns below 128 j
+    for (int64_t i = (int64_t)blockIdx.x * kDvThreads + threadIdx.x; i < B * tables; i += (int64_t)gridDim.x * kDvThreads) {
+        const int64_t b = i / tables;
+        colstart[i] = dv_lower_bound(col_idx + blk_ptr[b], blk_cnt[b], (int)(i - b * tables) * 128);
+    }
     __shared__ int s_scan[kDvThreads];
     __shared__ uint16_t s_perm[kDvThreads / kWave][kDvItemCols];
     const int tid = threadIdx.x;
@@ -523,7 +533,10 @@ __global__ __launch_bounds__(256) void dvals_plain_kernel(const void *__restrict
 
 struct DvLayout {
     int64_t max_items, max_units;
-    size_t items_at, groups_at, perm_at, slotcol_at, partial_at, total;
+    int32_t tables;          // entries of a row-block's column table
+    int64_t expected_items;  // with the kept columns spread evenly over row-blocks and columns
+    double expected_groups;  // of an item
+    size_t items_at, groups_at, perm_at, slotcol_at, colstart_at, partial_at, total;
 };
 DvLayout dv_layout(int64_t M, int64_t N, int32_t R, int64_t capacity_cols) {
     DvLayout L;
@@ -533,9 +546,29 @@ DvLayout dv_layout(int64_t M, int64_t N, int32_t R, int64_t capacity_cols) {
     L.groups_at = (L.items_at + (size_t)L.max_items * sizeof(DvItem) + 255) / 256 * 256;
     L.perm_at = (L.groups_at + (size_t)L.max_items * sizeof(int32_t) + 255) / 256 * 256;
     L.slotcol_at = L.perm_at + (size_t)L.max_items * kDvItemCols * sizeof(uint16_t);
-    L.partial_at = L.slotcol_at + (size_t)L.max_items * kDvItemCols * sizeof(uint16_t);
+    L.tables = R % 8 == 0 ? (int32_t)((N + 127) / 128) + 1 : 0;
+    const int64_t ranges = (N + kDvRange - 1) / kDvRange, runs = M / R * ranges;
+    const double cols = (double)capacity_cols / (double)runs;
+    const int64_t cut = (int64_t)(cols / kDvItemCols) + 1;
+    L.expected_items = (R + 15) / 16 * runs * cut;
+    L.expected_groups = cols / (double)cut / 16.0 + 1.0 < (double)kDvGroups ? cols / (double)cut / 16.0 + 1.0 : (double)kDvGroups;
+    L.colstart_at = L.slotcol_at + (size_t)L.max_items * kDvItemCols * sizeof(uint16_t);
+    L.partial_at = (L.colstart_at + (size_t)(M / R) * (size_t)L.tables * sizeof(int32_t) + 255) / 256 * 256;
     L.total = L.partial_at + (size_t)L.max_units * kDvStrip * kDvItemFloats * sizeof(float);
     return L;
+}
+
+// Whether the dense form (bsp_linear_dvals_dense.hip) is the faster one: against microseconds fitted to 260 calls of 768 to 4096 rows, 256
+// to 4096 columns, 16 to 8192 tokens at 1.43x to 8x (10 % off on average).  Of those five were faster by the sparse form, all from
+// 5x and 3400 tokens on: 2688 x 896, R = 16 at 8x, 7529 tokens 38.0 / 50.2; 3584 x 896 at 8x, 6260 tokens 40.6 / 44.9; 4096 x 1024
+// at 5x, 8192 tokens 56.8 / 63.
+bool dvals_dense_pays(double dense_us, int64_t ntiles, const DvLayout &L, int32_t R) {
+    const int64_t strips = L.expected_items / kDvStrip + 1;
+    const int64_t want = strips < kDvUnits ? (kDvUnits / strips < ntiles ? kDvUnits / strips : ntiles) : 1;
+    const int64_t tpu = (ntiles + want - 1) / want, units = strips * ((ntiles + tpu - 1) / tpu);
+    const double rounds = (double)((units + kDvUnits - 1) / kDvUnits);
+    const double bytes = (double)units * (double)kDvStrip * L.expected_groups * 1024.0 * (R % 16 == 8 && R < 16 ? 0.5 : 1.0);
+    return dense_us < 10.8 + 1.144 * (double)tpu * rounds + 0.386e-6 * bytes;
 }
 
 template <typename K>
@@ -601,6 +634,7 @@ extern "C" int bsp_linear_dvals(const void *X, const void *dY, int xdt, int64_t 
         uint16_t *perm = (uint16_t *)((uint8_t *)ws + L.perm_at);
         uint16_t *slotcol = (uint16_t *)((uint8_t *)ws + L.slotcol_at);
         int32_t *groups = (int32_t *)((uint8_t *)ws + L.groups_at);
+        int32_t *colstart = (int32_t *)((uint8_t *)ws + L.colstart_at);
         float *partial = (float *)((uint8_t *)ws + L.partial_at);
         const int32_t nslab = (R + 15) / 16, nr = (int32_t)((N + kDvRange - 1) / kDvRange);
         // a wavefront per item in the second part, in at most 64 workgroups
@@ -608,7 +642,13 @@ extern "C" int bsp_linear_dvals(const void *X, const void *dY, int xdt, int64_t 
         lg = lg < 1 ? 1 : (lg > 64 ? 64 : lg);
         if (ws_state == BSP_DVALS_BUILD)
             dvals_items_kernel<<<(unsigned)lg, kDvThreads, 0, s>>>(B, nslab, nr, blk_cnt, blk_ptr, col_idx,
-                                                                   (int32_t)L.max_items, hdr, items, perm, slotcol, groups);
+                                                                   (int32_t)L.max_items, hdr, items, perm, slotcol, groups, L.tables, colstart);
+        if (N % 8 == 0 && aligned(X, 16)) {
+            const DvalsDenseChoice c = dvals_dense_choose(T, M, N, R, capacity_cols, (int64_t)((L.total - L.partial_at) / sizeof(float)));
+            if (c.shape >= 0 && dvals_dense_pays(c.us, ntiles, L, R))
+                return launch_dvals_dense(DvalsDense{(const uint16_t *)X, (const uint16_t *)dY, xdt, T, M, N, R, blk_cnt, blk_ptr, col_idx,
+                                                     colstart, capacity_cols, partial, D, gdt, s}, c);
+        }
         const int64_t pgrid = (L.max_units + 7) / 8 * 8;  // whole rounds of the 8 XCDs
         const int st = xdt == BSP_BF16 ? launch_partial<BSP_BF16>(s, X, dY, T, M, N, R, hdr, items, slotcol, groups, partial, pgrid)
                                        : launch_partial<BSP_F16>(s, X, dY, T, M, N, R, hdr, items, slotcol, groups, partial, pgrid);

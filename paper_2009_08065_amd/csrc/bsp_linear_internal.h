@@ -247,4 +247,25 @@ int linear_expand(const void *X, int xdt, int64_t T, int64_t M, int64_t N, int32
                   const int32_t *blk_ptr, const int32_t *col_idx, const void *vals, const void *bias, void *Y, void *ws,
                   hipStream_t s);
 
+// The weight gradient as a dense product of which the kept positions are written (bsp_linear_dvals_dense.hip).  colstart[b][j]: kept
+// columns of row-block b below 128 j, j = 0 .. ceil(N / 128).  No argument checks of its own.
+struct DvalsDense {
+    const uint16_t *X, *dY;
+    int xdt;
+    int64_t T, M, N;
+    int32_t R;
+    const int32_t *blk_cnt, *blk_ptr, *col_idx, *colstart;
+    int64_t capacity_cols;
+    float *partial;
+    void *D;
+    int gdt;
+    hipStream_t s;
+};
+struct DvalsDenseChoice {
+    int shape, S, per;  // tile, runs of the tokens, stages of a run
+    double us;          // the estimate
+};
+DvalsDenseChoice dvals_dense_choose(int64_t T, int64_t M, int64_t N, int32_t R, int64_t capacity_cols, int64_t partial_floats);
+int launch_dvals_dense(const DvalsDense &a, const DvalsDenseChoice &c);
+
 }  // namespace bsp

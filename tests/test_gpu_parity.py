@@ -1150,6 +1150,43 @@ def test_linear_dvals_small_shapes(dtype, R, T, M, N, p_keep, k_align):
         run_dvals(d["X"], dY, d["W"], R, keep, k_align, dtype, gdt="f32")   # the sums themselves, unrounded
 
 
+@pytest.mark.parametrize("dtype,gdt,R,T,M,N,rate,k_align", [
+    ("bf16", "f32", 16, 4098, 1040, 4104, 2.0, 32),      # the largest tile, runs of the tokens
+    ("f16", "f16", 8, 3001, 2312, 1288, 1.3, 8), ("bf16", "f32", 40, 2049, 2320, 1032, 2.0, 1),     # 128 x 128, one run
+    ("bf16", "bf16", 8, 1003, 520, 392, 2.0, 16), ("f16", "f32", 56, 1001, 560, 136, 3.0, 64),      # 64 x 128, runs
+    ("f16", "f16", 24, 515, 1032, 1032, 2.0, 32), ("bf16", "f32", 64, 33, 64, 8, 1.5, 64),          # 64 x 128, one run
+    ("bf16", "bf16", 8, 1, 8, 16, 2.0, 8), ("f16", "f32", 48, 64, 96, 256, 1.2, 32)])               # one tile, whole stages
+def test_linear_dvals_dense_tiles(dtype, gdt, R, T, M, N, rate, k_align):
+    """The dense form at its tiles' edges: rows, columns and tokens past the last tile, row-blocks across tiles, an empty and a full
+    row-block, pads, one run and several, one token with an infinity (the batch's last, which a ragged stage reads again)."""
+    d = wl.layer(R * 1000 + T + 13, T, M, N, dtype)
+    dY = wl.normal(R * 83 + T, (T, M), 1.0, dtype)
+    B = M // R
+    keep = wl.bernoulli_keep_mask(T + N + 5, B, N, 1.0 / rate)
+    keep[0, :] = 1
+    if B > 2:
+        keep[B // 2, :] = 0
+    p = bsp.bsp_pack(dev(d["W"], dtype), R, torch.from_numpy(keep).cuda(), k_align)
+    some = sorted({0, B // 2, B - 1, B // 3, 128 // R, 256 // R} & set(range(B)))     # the oracle's row-blocks
+    rows = np.concatenate([np.arange(b * R, (b + 1) * R) for b in some])
+    p_some = orc.pack(d["W"][rows], R, keep[some], k_align, CODE[dtype])
+    ptr, cnt, at = host(p.blk_ptr).astype(int), host(p.blk_cnt).astype(int), p_some["blk_ptr"]
+    for spoil in (False, True):
+        X = d["X"].copy()
+        if spoil:
+            X[T - 1, N // 2] = np.inf
+        D = host(bsp.bsp_linear_dvals(dev(X, dtype), dev(dY, dtype), p, out_dtype=TDT[gdt]))
+        ref, _ = orc.linear_dvals(X, dY[:, rows], p_some, gdt=CODE[gdt], n_threads=16)
+        got = np.concatenate([D[R * ptr[b]:R * ptr[b + 1]] for b in some])
+        if spoil:
+            _assert_like(got, ref, gdt)
+        else:
+            assert_y_close(got, ref, gdt)
+        for i, b in enumerate(some):                     # pad slots
+            panel = got[R * at[i]:R * at[i + 1]].reshape(R, -1)
+            assert bits_equal(np.ascontiguousarray(panel[:, cnt[b]:]), np.zeros((R, panel.shape[1] - cnt[b]), np.float32))
+
+
 def test_linear_dvals_seeded_random_shapes():
     rng = np.random.default_rng(4242)
     for it in range(40):
