@@ -20,6 +20,8 @@ _TORCH = {F32: torch.float32, BF16: torch.bfloat16, F16: torch.float16}
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB = None
+_NATIVE = None
+_U8, _I32 = 3, 4  # types of a native allocation that are none of the library's
 
 
 class BspError(RuntimeError):
@@ -42,7 +44,7 @@ def lib():
         return _LIB
     path = library_path()
     from . import build as _build
-    if not os.path.exists(path):
+    if not os.path.exists(path) or not os.path.exists(_build.HOST_LIB):
         _build.build(force=True)
     elif _build.stale():
         # a built library is loaded as it is (GPU runs must not compile); say so when a source is newer
@@ -104,6 +106,16 @@ def lib():
     return L
 
 
+def _native():
+    """The hot entry points as native functions of tensors (None for NULL), with the checks of _ptr; and empty()."""
+    global _NATIVE
+    if _NATIVE is None:
+        lib()  # (the same library, loaded once)
+        from . import _bsp_host
+        _NATIVE = _bsp_host
+    return _NATIVE
+
+
 def _ptr(t: Optional[torch.Tensor], dtype=None):
     if t is None:
         return None
@@ -137,17 +149,17 @@ def _check(st: int, where: str):
 
 def bsp_group_norms(W, R, eps=1e-6, mode=ALPHA_SQNORM, sumsq=None, norm=None, alpha=None, want=("sumsq", "norm", "alpha")):
     """Returns (sumsq, norm, alpha) [B, N] fp32; entries not in `want` (and not passed) are None."""
+    native = _native()
     M, N = W.shape
     B = M // max(R, 1)
-    mk = lambda: torch.empty((B, N), dtype=torch.float32, device=W.device)
+    mk = lambda: native.empty(W, F32, B, N)
     if sumsq is None and "sumsq" in want:
         sumsq = mk()
     if norm is None and "norm" in want:
         norm = mk()
     if alpha is None and "alpha" in want:
         alpha = mk()
-    st = lib().bsp_group_norms(_ptr(W), _DT[W.dtype], M, N, R, eps, mode, _ptr(sumsq, torch.float32),
-                               _ptr(norm, torch.float32), _ptr(alpha, torch.float32), _stream())
+    st = native.bsp_group_norms(W, _DT[W.dtype], M, N, R, eps, mode, sumsq, norm, alpha, _stream())
     _check(st, "bsp_group_norms")
     return sumsq, norm, alpha
 
@@ -155,9 +167,10 @@ def bsp_group_norms(W, R, eps=1e-6, mode=ALPHA_SQNORM, sumsq=None, norm=None, al
 def bsp_group_norms_grad(W, R, lam, eps=1e-6, mode=ALPHA_SQNORM, sumsq=None, norm=None, alpha=None, grad=None,
                          accumulate=False, want=("sumsq", "alpha")):
     """bsp_group_norms and bsp_penalty_grad in one pass over W.  Returns (sumsq, norm, alpha, grad)."""
+    native = _native()
     M, N = W.shape
     B = M // max(R, 1)
-    mk = lambda: torch.empty((B, N), dtype=torch.float32, device=W.device)
+    mk = lambda: native.empty(W, F32, B, N)
     if sumsq is None and "sumsq" in want:
         sumsq = mk()
     if norm is None and "norm" in want:
@@ -169,9 +182,8 @@ def bsp_group_norms_grad(W, R, lam, eps=1e-6, mode=ALPHA_SQNORM, sumsq=None, nor
         accumulate = False
     if grad.dtype != W.dtype or grad.shape != W.shape:
         raise ValueError("grad must have the shape and dtype of W")
-    st = lib().bsp_group_norms_grad(_ptr(W), _DT[W.dtype], M, N, R, eps, mode, lam, int(bool(accumulate)),
-                                    _ptr(sumsq, torch.float32), _ptr(norm, torch.float32), _ptr(alpha, torch.float32),
-                                    _ptr(grad), _stream())
+    st = native.bsp_group_norms_grad(W, _DT[W.dtype], M, N, R, eps, mode, lam, int(bool(accumulate)), sumsq, norm,
+                                     alpha, grad, _stream())
     _check(st, "bsp_group_norms_grad")
     return sumsq, norm, alpha, grad
 
@@ -180,14 +192,15 @@ def bsp_adam_step(W, G, m, v, R, lr, beta1=0.9, beta2=0.999, eps=1e-8, t=1, alph
                   keep=None):
     """One Adam update of Alg. 2 in place on fp32 W, m, v: optional regulariser gradient (alpha, lam, mode) added
     to G, optional W = W * Mask (keep)."""
+    native = _native()
     M, N = W.shape
     for x in (W, m, v):
         if x.dtype != torch.float32 or x.shape != W.shape or not x.is_contiguous():
             raise ValueError("W, m, v must be contiguous fp32 tensors of one shape")
     if G.shape != W.shape or not G.is_contiguous():
         raise ValueError("G must be contiguous and have the shape of W")
-    st = lib().bsp_adam_step(_ptr(W), _ptr(G), _DT[G.dtype], _ptr(m), _ptr(v), M, N, R, _ptr(alpha, torch.float32), lam,
-                             mode, _ptr(keep, torch.uint8), lr, beta1, beta2, eps, t, _stream())
+    st = native.bsp_adam_step(W, G, _DT[G.dtype], m, v, M, N, R, alpha, lam, mode, keep, lr, beta1,
+                              beta2, eps, t, _stream())
     _check(st, "bsp_adam_step")
     return W, m, v
 
@@ -216,19 +229,19 @@ def bsp_penalty_grad(W, R, alpha, lam, mode=ALPHA_SQNORM, grad=None, accumulate=
 
 def bsp_prune_mask(sumsq, t=0.0, n_keep=-1, scope=SCOPE_BLOCK, keep=None, t_used=None, ws=None, want_t_used=False):
     """Returns (keep uint8 [B, N], t_used or None)."""
+    native = _native()
     B, N = sumsq.shape
     if keep is None:
-        keep = torch.empty((B, N), dtype=torch.uint8, device=sumsq.device)
+        keep = native.empty(sumsq, _U8, B, N)
     if t_used is None and want_t_used and n_keep >= 0:
         t_used = torch.empty(B if scope == SCOPE_BLOCK else 1, dtype=torch.float32, device=sumsq.device)
     ws_bytes = 0
     if n_keep >= 0:
-        need = lib().bsp_prune_mask_workspace_bytes(B, N, scope)
+        need = native.bsp_prune_mask_workspace_bytes(B, N, scope)
         if ws is None and need:
-            ws = torch.empty(need, dtype=torch.uint8, device=sumsq.device)
+            ws = native.empty(sumsq, _U8, need)
         ws_bytes = 0 if ws is None else ws.numel() * ws.element_size()
-    st = lib().bsp_prune_mask(_ptr(sumsq, torch.float32), B, N, t, n_keep, scope, _ptr(keep, torch.uint8),
-                              _ptr(t_used, torch.float32), _ptr(ws), ws_bytes, _stream())
+    st = native.bsp_prune_mask(sumsq, B, N, t, n_keep, scope, keep, t_used, ws, ws_bytes, _stream())
     _check(st, "bsp_prune_mask")
     return keep, t_used
 
@@ -245,8 +258,9 @@ def bsp_prune_mask_static(sumsq, keep, t=0.0, n_keep=-1, scope=SCOPE_BLOCK, t_us
 
 def bsp_mask_weights(W, R, keep):
     """In place: zero every pruned group of W (Alg. 1; the W = W * Mask step of Alg. 2).  Returns W."""
+    native = _native()
     M, N = W.shape
-    st = lib().bsp_mask_weights(_ptr(W), _DT[W.dtype], M, N, R, _ptr(keep, torch.uint8), _stream())
+    st = native.bsp_mask_weights(W, _DT[W.dtype], M, N, R, keep, _stream())
     _check(st, "bsp_mask_weights")
     return W
 
@@ -287,13 +301,13 @@ def bsp_mask_weights_rowseg(W, Cs, keep_seg):
 
 
 def bsp_pack_count(keep, k_align=32, blk_cnt=None, blk_ptr=None):
+    native = _native()
     B, N = keep.shape
     if blk_cnt is None:
-        blk_cnt = torch.empty(B, dtype=torch.int32, device=keep.device)
+        blk_cnt = native.empty(keep, _I32, B)
     if blk_ptr is None:
-        blk_ptr = torch.empty(B + 1, dtype=torch.int32, device=keep.device)
-    st = lib().bsp_pack_count(_ptr(keep, torch.uint8), B, N, k_align, _ptr(blk_cnt, torch.int32),
-                              _ptr(blk_ptr, torch.int32), _stream())
+        blk_ptr = native.empty(keep, _I32, B + 1)
+    st = native.bsp_pack_count(keep, B, N, k_align, blk_cnt, blk_ptr, _stream())
     _check(st, "bsp_pack_count")
     return blk_cnt, blk_ptr
 
@@ -301,23 +315,22 @@ def bsp_pack_count(keep, k_align=32, blk_cnt=None, blk_ptr=None):
 def bsp_prune_mask_count(sumsq, t=0.0, n_keep=-1, scope=SCOPE_BLOCK, k_align=32, keep=None, t_used=None, ws=None,
                          blk_cnt=None, blk_ptr=None):
     """bsp_prune_mask and bsp_pack_count in one call.  Returns (keep, t_used, blk_cnt, blk_ptr)."""
+    native = _native()
     B, N = sumsq.shape
-    dev = sumsq.device
     if keep is None:
-        keep = torch.empty((B, N), dtype=torch.uint8, device=dev)
+        keep = native.empty(sumsq, _U8, B, N)
     if blk_cnt is None:
-        blk_cnt = torch.empty(B, dtype=torch.int32, device=dev)
+        blk_cnt = native.empty(sumsq, _I32, B)
     if blk_ptr is None:
-        blk_ptr = torch.empty(B + 1, dtype=torch.int32, device=dev)
+        blk_ptr = native.empty(sumsq, _I32, B + 1)
     ws_bytes = 0
     if n_keep >= 0:
-        need = lib().bsp_prune_mask_workspace_bytes(B, N, scope)
+        need = native.bsp_prune_mask_workspace_bytes(B, N, scope)
         if ws is None and need:
-            ws = torch.empty(need, dtype=torch.uint8, device=dev)
+            ws = native.empty(sumsq, _U8, need)
         ws_bytes = 0 if ws is None else ws.numel() * ws.element_size()
-    st = lib().bsp_prune_mask_count(_ptr(sumsq, torch.float32), B, N, t, n_keep, scope, _ptr(keep, torch.uint8),
-                                    _ptr(t_used, torch.float32), k_align, _ptr(blk_cnt, torch.int32),
-                                    _ptr(blk_ptr, torch.int32), _ptr(ws), ws_bytes, _stream())
+    st = native.bsp_prune_mask_count(sumsq, B, N, t, n_keep, scope, keep, t_used, k_align, blk_cnt, blk_ptr, ws,
+                                     ws_bytes, _stream())
     _check(st, "bsp_prune_mask_count")
     return keep, t_used, blk_cnt, blk_ptr
 
@@ -339,18 +352,21 @@ class Packed:
 def bsp_pack(W, R, keep, k_align=32, vdt=None, blk_cnt=None, blk_ptr=None, total_cols=None):
     """Two-phase pack.  Reads blk_ptr[B] back to the host once to size the buffers (unless
     total_cols is given)."""
+    native = _native()
     M, N = W.shape
     if blk_cnt is None or blk_ptr is None:
         blk_cnt, blk_ptr = bsp_pack_count(keep, k_align)
     if total_cols is None:
-        total_cols = int(blk_ptr[-1].item())
+        total_cols = native.last(blk_ptr)
     vdtype = W.dtype if vdt is None else _TORCH[vdt]
-    col_idx = torch.empty(max(total_cols, 1), dtype=torch.int32, device=W.device)
-    vals = torch.empty(max(R * total_cols, 1), dtype=vdtype, device=W.device)
-    st = lib().bsp_pack(_ptr(W), _DT[W.dtype], M, N, R, _ptr(keep, torch.uint8), k_align, _ptr(blk_cnt, torch.int32),
-                        _ptr(blk_ptr, torch.int32), total_cols, _ptr(col_idx), _ptr(vals), _DT[vdtype], _stream())
+    col_idx = native.empty(W, _I32, max(total_cols, 1))
+    vals = native.empty(W, _DT[vdtype], max(R * total_cols, 1))
+    st = native.bsp_pack(W, _DT[W.dtype], M, N, R, keep, k_align, blk_cnt, blk_ptr, total_cols, col_idx, vals,
+                         _DT[vdtype], _stream())
     _check(st, "bsp_pack")
-    return Packed(M, N, R, k_align, blk_cnt, blk_ptr, col_idx[:total_cols], vals[:R * total_cols], total_cols)
+    if total_cols <= 0:
+        col_idx, vals = col_idx[:total_cols], vals[:R * total_cols]
+    return Packed(M, N, R, k_align, blk_cnt, blk_ptr, col_idx, vals, total_cols)
 
 
 def bsp_packed_validate(p: Packed) -> bool:
@@ -364,37 +380,39 @@ def bsp_packed_validate(p: Packed) -> bool:
 
 
 def bsp_linear(X, p: Packed, bias=None, Y=None):
+    native = _native()
     T, N = X.shape
     if N != p.N:
         raise ValueError("X has the wrong number of columns")
     if p.vals.dtype != X.dtype or (bias is not None and bias.dtype != X.dtype):
         raise ValueError("X, vals and bias must share one dtype")
     if Y is None:
-        Y = torch.empty((T, p.M), dtype=X.dtype, device=X.device)
+        Y = native.empty(X, _DT[X.dtype], T, p.M)
     has = p.total_cols > 0
-    need = lib().bsp_linear_workspace_bytes(_DT[X.dtype], T, p.M, N, p.R, p.k_align, p.total_cols)
+    need = native.bsp_linear_workspace_bytes(_DT[X.dtype], T, p.M, N, p.R, p.k_align, p.total_cols)
     ws = _scratch(need, X.device)
-    st = lib().bsp_linear_sized(_ptr(X), _DT[X.dtype], T, p.M, N, p.R, p.k_align, _ptr(p.blk_cnt), _ptr(p.blk_ptr),
-                                _ptr(p.col_idx) if has else None, _ptr(p.vals) if has else None, p.total_cols, _ptr(bias),
-                                _ptr(Y), _ptr(ws), need, _stream())
+    st = native.bsp_linear_sized(X, _DT[X.dtype], T, p.M, N, p.R, p.k_align, p.blk_cnt, p.blk_ptr,
+                                 p.col_idx if has else None, p.vals if has else None, p.total_cols, bias,
+                                 Y, ws, need, _stream())
     _check(st, "bsp_linear")
     return Y
 
 
 def bsp_linear_transposed(U, p: Packed, bias=None, Z=None):
+    native = _native()
     T, M = U.shape
     if M != p.M:
         raise ValueError("U has the wrong number of columns")
     if p.vals.dtype != U.dtype or (bias is not None and bias.dtype != U.dtype):
         raise ValueError("U, vals and bias must share one dtype")
     if Z is None:
-        Z = torch.empty((T, p.N), dtype=U.dtype, device=U.device)
+        Z = native.empty(U, _DT[U.dtype], T, p.N)
     has = p.total_cols > 0
-    need = lib().bsp_linear_transposed_workspace_bytes(_DT[U.dtype], T, M, p.N, p.R)
+    need = native.bsp_linear_transposed_workspace_bytes(_DT[U.dtype], T, M, p.N, p.R)
     ws = _scratch(need, U.device)
-    st = lib().bsp_linear_transposed_ws(_ptr(U), _DT[U.dtype], T, M, p.N, p.R, p.k_align, _ptr(p.blk_cnt),
-                                        _ptr(p.blk_ptr), _ptr(p.col_idx) if has else None,
-                                        _ptr(p.vals) if has else None, _ptr(bias), _ptr(Z), _ptr(ws), need, _stream())
+    st = native.bsp_linear_transposed_ws(U, _DT[U.dtype], T, M, p.N, p.R, p.k_align, p.blk_cnt,
+                                         p.blk_ptr, p.col_idx if has else None,
+                                         p.vals if has else None, bias, Z, ws, need, _stream())
     _check(st, "bsp_linear_transposed")
     return Z
 
@@ -418,6 +436,7 @@ DVALS_BUILD, DVALS_REUSE = 0, 1
 def bsp_linear_dvals(X, dY, p: Packed, out_dtype=None, D=None, ws=None, ws_state=DVALS_BUILD):
     """Gradient with respect to the kept weights, in the layout of p.vals: a tensor of R * p.total_cols elements.
     ws_state=DVALS_REUSE: ws is the workspace of an earlier call on the same storage (its work list is reused)."""
+    native = _native()
     T, N = X.shape
     if N != p.N or dY.shape != (T, p.M):
         raise ValueError("X must be [T, N] and dY [T, M]")
@@ -426,13 +445,13 @@ def bsp_linear_dvals(X, dY, p: Packed, out_dtype=None, D=None, ws=None, ws_state
     out_dtype = out_dtype or X.dtype
     if D is None:
         D = torch.empty(p.R * p.total_cols, dtype=out_dtype, device=X.device)
-    need = lib().bsp_linear_dvals_workspace_bytes(p.M, p.N, p.R, p.total_cols)
+    need = native.bsp_linear_dvals_workspace_bytes(p.M, p.N, p.R, p.total_cols)
     if ws is None:
         ws = torch.empty(max(need, 256), dtype=torch.uint8, device=X.device)
     has = p.total_cols > 0
-    st = lib().bsp_linear_dvals(_ptr(X), _ptr(dY), _DT[X.dtype], T, p.M, p.N, p.R, p.k_align, _ptr(p.blk_cnt),
-                                _ptr(p.blk_ptr), _ptr(p.col_idx) if has else None, p.total_cols,
-                                _ptr(D) if has else None, _DT[D.dtype], _ptr(ws), ws.numel(), ws_state, _stream())
+    st = native.bsp_linear_dvals(X, dY, _DT[X.dtype], T, p.M, p.N, p.R, p.k_align, p.blk_cnt,
+                                 p.blk_ptr, p.col_idx if has else None, p.total_cols,
+                                 D if has else None, _DT[D.dtype], ws, ws.numel(), ws_state, _stream())
     _check(st, "bsp_linear_dvals")
     return D
 
@@ -443,27 +462,29 @@ def bsp_linear_plan_supported(dtype, N, k_align) -> bool:
 
 def bsp_linear_plan(p: Packed, plan=None):
     """Build the derived operand buffer of a compact storage.  Returns a uint8 GPU tensor."""
-    need = lib().bsp_linear_plan_bytes(p.M, p.R, p.total_cols)
+    native = _native()
+    need = native.bsp_linear_plan_bytes(p.M, p.R, p.total_cols)
     if plan is None:
-        plan = torch.empty(max(need, 16), dtype=torch.uint8, device=p.blk_ptr.device)
+        plan = native.empty(p.blk_ptr, _U8, max(need, 16))
     has = p.total_cols > 0
-    st = lib().bsp_linear_plan(_DT[p.vals.dtype], p.M, p.N, p.R, p.k_align, _ptr(p.blk_cnt), _ptr(p.blk_ptr),
-                               _ptr(p.col_idx) if has else None, _ptr(p.vals) if has else None, p.total_cols,
-                               _ptr(plan), plan.numel(), _stream())
+    st = native.bsp_linear_plan(_DT[p.vals.dtype], p.M, p.N, p.R, p.k_align, p.blk_cnt, p.blk_ptr,
+                                p.col_idx if has else None, p.vals if has else None, p.total_cols,
+                                plan, plan.numel(), _stream())
     _check(st, "bsp_linear_plan")
     return plan
 
 
 def bsp_linear_planned(X, p: Packed, plan, bias=None, Y=None):
+    native = _native()
     T, N = X.shape
     if N != p.N:
         raise ValueError("X has the wrong number of columns")
     if bias is not None and bias.dtype != X.dtype:
         raise ValueError("X and bias must share one dtype")
     if Y is None:
-        Y = torch.empty((T, p.M), dtype=X.dtype, device=X.device)
-    st = lib().bsp_linear_planned(_ptr(X), _DT[X.dtype], T, p.M, N, p.R, p.k_align, _ptr(plan),
-                                  p.total_cols, _ptr(bias), _ptr(Y), _stream())
+        Y = native.empty(X, _DT[X.dtype], T, p.M)
+    st = native.bsp_linear_planned(X, _DT[X.dtype], T, p.M, N, p.R, p.k_align, plan,
+                                   p.total_cols, bias, Y, _stream())
     _check(st, "bsp_linear_planned")
     return Y
 
@@ -473,6 +494,7 @@ ACT_NONE, ACT_GELU = 0, 1
 
 def bsp_linear_planned_fused(X, p: Packed, plan, bias=None, act=ACT_NONE, residual=None, Y=None):
     """Y = round(act(X Wp^T + bias) + residual) in the layer kernel (raises BspError where that layer is not fused)."""
+    native = _native()
     T, N = X.shape
     if N != p.N:
         raise ValueError("X has the wrong number of columns")
@@ -482,9 +504,9 @@ def bsp_linear_planned_fused(X, p: Packed, plan, bias=None, act=ACT_NONE, residu
                                  or not residual.is_contiguous()):
         raise ValueError("residual must be a contiguous [T, M] tensor of the dtype of X")
     if Y is None:
-        Y = torch.empty((T, p.M), dtype=X.dtype, device=X.device)
-    st = lib().bsp_linear_planned_fused(_ptr(X), _DT[X.dtype], T, p.M, N, p.R, p.k_align, _ptr(plan),
-                                        p.total_cols, _ptr(bias), act, _ptr(residual), _ptr(Y), _stream())
+        Y = native.empty(X, _DT[X.dtype], T, p.M)
+    st = native.bsp_linear_planned_fused(X, _DT[X.dtype], T, p.M, N, p.R, p.k_align, plan,
+                                         p.total_cols, bias, act, residual, Y, _stream())
     _check(st, "bsp_linear_planned_fused")
     return Y
 

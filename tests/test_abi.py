@@ -4,6 +4,9 @@ import ctypes as C
 import os
 import re
 
+import pytest
+import torch
+
 import paper_2009_08065_amd as bsp
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -125,3 +128,45 @@ def test_expansion_pays_for_enough_tokens_only():
     for M, N, R, rate, T in ((1024, 4096, 16, 1.43, 8192), (1024, 4096, 16, 5.0, 8192), (768, 3072, 8, 2.0, 4096), (4096, 1024, 16, 1.43, 8192),
                              (4096, 1024, 1, 1.43, 1100)):
         assert q(bsp.BF16, T, M, N, R, 32, kept(M, N, R, rate)) > 0, (M, N, R, rate, T)
+
+
+class _Elsewhere:
+    """What the binding asks of an object that is no plain tensor."""
+    is_cuda = True
+
+    def __init__(self, dtype=torch.float32, dense=True, at=4096):
+        self.dtype, self.dense, self.at = dtype, dense, at
+
+    def is_contiguous(self):
+        return self.dense
+
+    def data_ptr(self):
+        return self.at
+
+
+def test_native_functions_check_what_they_are_given():
+    """The native functions refuse what the binding refused: tensors that are not on the GPU or not contiguous, of another
+    type than the function's where that is checked, numbers in the place of tensors and the other way round."""
+    n = bsp.bsp._native()
+    host = torch.zeros(4, 4)
+    with pytest.raises(ValueError, match="contiguous GPU tensor"):
+        n.bsp_mask_weights(host, 0, 4, 4, 2, None, 0)
+    with pytest.raises(ValueError, match="contiguous GPU tensor"):
+        n.bsp_mask_weights(_Elsewhere(dense=False), 0, 4, 4, 2, None, 0)
+    with pytest.raises(ValueError, match="expected dtype torch.uint8, got torch.float32"):
+        n.bsp_mask_weights(_Elsewhere(), 0, 4, 4, 2, _Elsewhere(), 0)
+    for args in ((4096, 0, 4, 4, 2, None, 0), (None, host, 4, 4, 2, None, 0), (None, 0, 4.0, 4, 2, None, 0),
+                 (None, 0, 4, 4, 2, None), (None, 0, 4, 4, 2, None, None)):
+        with pytest.raises((TypeError, AttributeError)):
+            n.bsp_mask_weights(*args)
+    assert n.bsp_mask_weights(None, 0, 4, 4, 2, None, 0) == 1   # NULL: refused by the library
+    # no tokens: accepted without looking at memory
+    a, i = _Elsewhere(), _Elsewhere(torch.int32)
+    assert n.bsp_linear_sized(a, 0, 0, 64, 64, 16, 32, i, i, i, a, 64, None, a, None, 0, 0) == 0
+    assert n.bsp_linear_sized(a, 0, 0, 64, 64, 16, 32, i, i, i, a, -1, None, a, None, 0, 0) == 4
+    assert n.bsp_linear_workspace_bytes(1, 4096, 1024, 4096, 16, 32, 1 << 17) == bsp.lib().bsp_linear_workspace_bytes(
+        1, 4096, 1024, 4096, 16, 32, 1 << 17)
+    assert n.empty(host, 3, 5).shape == (5,) and n.empty(host, 1, 2, 3).dtype == torch.bfloat16
+    assert n.last(torch.tensor([3, 9, 7], dtype=torch.int32)) == 7
+    with pytest.raises(RuntimeError):
+        n.empty(host, 0, -1)
