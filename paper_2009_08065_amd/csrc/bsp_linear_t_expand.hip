@@ -2,7 +2,7 @@
 // written here; bf16 / fp16, R % 8 == 0, with a workspace for the expanded matrix.
 //
 // Measured (MI355X, 8192 tokens, R = 16, 5x, both kernels): 4096 x 1024 64 us, 3072 x 1024 51, 1024 x 1024 27,
-// 1024 x 4096 76, against 217 / 171 / 67 / 227 of the scattering kernel; 2304 x 768, R = 8, 2x, 509 tokens: 20 against 337.
+// 1024 x 4096 76, against 217 / 171 / 67 / 227 of the scattering kernel; 2304 x 768, R = 8, 2x, 509 tokens: 15.7 against 337.
 //
 // Why dense: the result of a row-block's small product has to be scattered to the kept columns' positions, and an
 // addition to a scattered position costs an LDS read and write of 4 bytes for R multiply-adds.  That bounds the
@@ -30,7 +30,7 @@ namespace {
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
-constexpr int kThreadsX = 256;
+constexpr int kThreadsX = 256;  // of the expansions
 constexpr int kRing = 4;       // stages of U in LDS
 constexpr int kStageK = 64;    // rows of the matrix per stage
 constexpr int kRowBytes = 2 * kStageK;
@@ -261,7 +261,7 @@ __device__ __forceinline__ void kept_sums(const uint8_t *u, int32_t M, int32_t N
 }
 
 // ---------------------------------------------------------------------------------------
-// The product.  A workgroup of 4 wavefronts owns 32 FT tokens x 128 FN columns and walks the rows in stages of 64.  U
+// The product.  A workgroup of NW wavefronts owns 32 FT tokens x 32 NW FN columns and walks the rows in stages of 64.  U
 // goes through LDS ([token][64], 128 bytes per row, 16-byte pieces rotated so that the operand reads meet all
 // banks); the expanded weights are stored as operands and every wavefront has its own columns, so it loads them
 // straight into registers: through LDS as well, a stage of the 128 x 256 tile would move 144 KiB through it in the
@@ -273,16 +273,16 @@ __device__ __forceinline__ void kept_sums(const uint8_t *u, int32_t M, int32_t N
 // ---------------------------------------------------------------------------------------
 // ROWS: the operands are Wp's rows (the layer), U is X and M, N are the layer's columns and rows.
 // (the launch bounds: workgroups of a compute unit as the products' registers allow, whatever kept_sums would like)
-template <int DT, int FT, int FN, bool ROWS>
-__global__ __launch_bounds__(kThreadsX, FN == 2 ? 1 : (FT == 4 ? 2 : 3)) void tile_kernel(
+template <int DT, int FT, int FN, bool ROWS, int NW>
+__global__ __launch_bounds__(64 * NW, FN == 2 ? 1 : (FT == 4 ? 2 : 3)) void tile_kernel(
     const uint16_t *__restrict__ U, int64_t T, int32_t M, int32_t N, int32_t R, int32_t frags_m,
     const uint8_t *__restrict__ W, const uint32_t *__restrict__ kept, const int32_t *__restrict__ blk_cnt,
     const int32_t *__restrict__ blk_ptr, const int32_t *__restrict__ col_idx, const void *__restrict__ bias,
     void *__restrict__ Z) {
-    constexpr int TT = 32 * FT, NN = 128 * FN;
+    constexpr int TT = 32 * FT, NN = 32 * NW * FN, kThreads = 64 * NW;
     constexpr int kUBytes = TT * kRowBytes;
     constexpr int kPitch = NN * 2 + 16;  // bytes of a token's row in the output tile
-    constexpr int kPieces = FT;          // 16-byte pieces of U per thread and stage
+    constexpr int kPieces = 4 * FT / NW; // 16-byte pieces of U per thread and stage
     extern __shared__ __align__(16) uint8_t smem[];
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -307,12 +307,12 @@ __global__ __launch_bounds__(kThreadsX, FN == 2 ? 1 : (FT == 4 ? 2 : 3)) void ti
 #pragma unroll
             for (int i = 0; i < 16; ++i) acc[n][t][i] = 0.0f;
 
-    // as a loader of U: pieces tid % 8 of token rows tid / 8 + 32 i; a token past T reads the last one
+    // as a loader of U: pieces tid % 8 of token rows tid / 8 + 8 NW i; a token past T reads the last one
     const uint8_t *utile = reinterpret_cast<const uint8_t *>(U + t0 * M);
     uint32_t urow[kPieces];
 #pragma unroll
     for (int i = 0; i < kPieces; ++i) {
-        const int row = (tid >> 3) + 32 * i;
+        const int row = (tid >> 3) + 8 * NW * i;
         urow[i] = (uint32_t)(t0 + row < T ? row : (int)(T - 1 - t0)) * 2u * (uint32_t)M;
     }
     const uint32_t st_u = (tid >> 3) * kRowBytes + (((tid & 7) ^ ((tid >> 4) & 7)) << 4);
@@ -334,7 +334,7 @@ __global__ __launch_bounds__(kThreadsX, FN == 2 ? 1 : (FT == 4 ? 2 : 3)) void ti
     };
     auto put_u = [&](auto slot, auto piece) {
         constexpr int s = decltype(slot)::value, I = decltype(piece)::value;
-        if constexpr (I < kPieces) *reinterpret_cast<u32x4 *>(smem + st_u + s * kUBytes + I * 32 * kRowBytes) = ru[s & 1][I];
+        if constexpr (I < kPieces) *reinterpret_cast<u32x4 *>(smem + st_u + s * kUBytes + I * 8 * NW * kRowBytes) = ru[s & 1][I];
     };
     auto ask_w = [&](auto slot, auto n, auto quarter, int stage) {
         constexpr int s = decltype(slot)::value, NI = decltype(n)::value, KK = decltype(quarter)::value;
@@ -448,13 +448,13 @@ __global__ __launch_bounds__(kThreadsX, FN == 2 ? 1 : (FT == 4 ? 2 : 3)) void ti
     if (any) __syncthreads();
     uint16_t *z = (uint16_t *)Z + t0 * N + cr0;
     if ((N & 7) == 0 && (reinterpret_cast<uintptr_t>(Z) & 15) == 0) {
-        for (int i = tid; i < TT * (NN / 8); i += kThreadsX) {
+        for (int i = tid; i < TT * (NN / 8); i += kThreads) {
             const int tok = i / (NN / 8), c = (i % (NN / 8)) * 8;
             if (tok < left && c < ncol)
                 *reinterpret_cast<uint4 *>(z + (int64_t)tok * N + c) = *reinterpret_cast<const uint4 *>(tile + tok * kPitch + c * 2);
         }
     } else {
-        for (int i = tid; i < TT * NN; i += kThreadsX) {
+        for (int i = tid; i < TT * NN; i += kThreads) {
             const int tok = i / NN, c = i % NN;
             if (tok < left && c < ncol)
                 z[(int64_t)tok * N + c] = *reinterpret_cast<const uint16_t *>(tile + tok * kPitch + c * 2);
@@ -462,14 +462,14 @@ __global__ __launch_bounds__(kThreadsX, FN == 2 ? 1 : (FT == 4 ? 2 : 3)) void ti
     }
 }
 
-template <int FT, int FN>
+template <int FT, int FN, int NW>
 constexpr size_t tile_lds() {
     constexpr size_t stages = (size_t)kRing * 32 * FT * kRowBytes;
-    constexpr size_t out = (size_t)32 * FT * (128 * FN * 2 + 16) + 4 * FT;
+    constexpr size_t out = (size_t)32 * FT * (32 * NW * FN * 2 + 16) + 4 * FT;
     return stages > out ? stages : out;
 }
 
-// Which tile: 128 x 256 (ft 4, fn 2), 128 x 128 (4, 1) or 64 x 128 (2, 1).  The larger a tile, the more products a
+// Which tile (where few_columns names no smaller one): 128 x 256 (ft 4, fn 2), 128 x 128 (4, 1) or 64 x 128 (2, 1).  The larger a tile, the more products a
 // loaded operand serves, but one workgroup of the largest fills a compute unit, so what it cannot overlap shows: its
 // start and end (9 us) and the idle units of the last round.  The estimates are microseconds fitted to what was
 // measured at 512 to 8192 tokens of 768 to 4096 rows and columns: per stage 0.70, 0.46 (two on a unit together 1.03)
@@ -505,6 +505,21 @@ Tile choose_tile(int64_t T, int64_t M, int64_t N, double *us = nullptr, double *
     return best;
 }
 
+// Columns of a workgroup of 32 tokens, where such a small tile is the faster one, else 0.  What bounds a stage of the tiles
+// above in a launch of few workgroups is neither a load's nor an LDS read's latency (with twice the stages on their way, or the
+// reads a whole stage ahead, it takes as long) but what a compute unit loads, 33 to 40 bytes per clock whatever the tile: 24 KB
+// of 64 x 128 0.28 us, and 240 workgroups take as long as 6.  32 tokens x 64 columns are 12 KB and 0.2 us, 32 x 128 20 KB, on up
+// to four times the compute units.  They stop paying where an XCD (token tiles go round the 8 of them) has more than its 32
+// compute units' worth of workgroups, and for wide layers, whose matrix then crosses to more XCDs than the larger tiles
+// need.  Measured with the expansion, us, 64 x 128 or the larger / 32 x 128 / 32 x 64: 2304 x 768, 509 tokens 19.3 / 17.7 / 15.7, 800 tokens
+// 19.4 / 17.9 / 18.7, 1537 tokens 19.3 / 21.8 / 22.0; 4096 x 1024, 64 tokens 24.4 / 22.9 / 19.8, 1024 tokens 27.0 / 25.8 / 27.1; 1024 x 2048, 254
+// tokens 15.4 / 16.6 / 16.1 (stays).  Over 150 drawn calls of 8 to 4096 tokens (about two thirds of them taken) the mean is 0.925 of the time.
+int few_columns(int64_t T, int64_t N) {
+    const int64_t per_xcd = (T + 255) / 256;  // token tiles
+    if (N <= 1536 && per_xcd * ((N + 63) / 64) <= 32) return 64;
+    return N <= 1280 && per_xcd * ((N + 127) / 128) <= 32 ? 128 : 0;
+}
+
 // The expanded matrix (N columns, M rows); behind it one bit per row-block and column of the pruned matrix.
 size_t expanded_bytes(int64_t M, int64_t N) {
     return (size_t)((N + kColPad - 1) / kColPad * kColPad) * (size_t)((M + kStageK - 1) / kStageK * kStageK) * 2;
@@ -524,10 +539,10 @@ struct Args {
 
 uint32_t *kept_bits(const Args &a) { return (uint32_t *)((uint8_t *)a.ws + expanded_bytes(a.M, a.N)); }
 
-template <int DT, int FT, int FN, bool ROWS>
+template <int DT, int FT, int FN, bool ROWS, int NW = 4>
 int launch_tiles(const Args &a, int frags_m) {
-    constexpr size_t lds = tile_lds<FT, FN>();
-    auto k = tile_kernel<DT, FT, FN, ROWS>;
+    constexpr size_t lds = tile_lds<FT, FN, NW>();
+    auto k = tile_kernel<DT, FT, FN, ROWS, NW>;
     if (lds > 65536) {  // (asking again is harmless)
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) {
@@ -535,10 +550,10 @@ int launch_tiles(const Args &a, int frags_m) {
             return BSP_ERR_HIP;
         }
     }
-    const int64_t tiles = (a.T + 32 * FT - 1) / (32 * FT), ranges = (a.N + 128 * FN - 1) / (128 * FN);
+    const int64_t tiles = (a.T + 32 * FT - 1) / (32 * FT), ranges = (a.N + 32 * NW * FN - 1) / (32 * NW * FN);
     const int64_t wgs = (tiles + 7) / 8 * 8 * ranges;  // whole rounds of the 8 XCDs
     if (wgs >= ((int64_t)1 << 31)) return BSP_ERR_SHAPE;
-    k<<<dim3((unsigned)wgs), kThreadsX, lds, a.s>>>(a.U, a.T, a.M, a.N, a.R, frags_m, (const uint8_t *)a.ws, kept_bits(a), a.blk_cnt,
+    k<<<dim3((unsigned)wgs), 64 * NW, lds, a.s>>>(a.U, a.T, a.M, a.N, a.R, frags_m, (const uint8_t *)a.ws, kept_bits(a), a.blk_cnt,
                                                     a.blk_ptr, a.col_idx, a.bias, a.Z);
     return BSP_OK;
 }
@@ -554,6 +569,9 @@ int launch_all(const Args &a) {
     else
         expand_kernel<<<dim3((unsigned)a.B, (unsigned)(npad / kColPad), (unsigned)((a.R + 15) / 16)), kThreadsX, 0, a.s>>>(
             a.R, a.B, frags_m, a.blk_cnt, a.blk_ptr, a.col_idx, a.vals, (uint8_t *)a.ws, kept);
+    const int few = few_columns(a.T, a.N);
+    if (few == 64) return launch_tiles<DT, 1, 1, ROWS, 2>(a, frags_m);
+    if (few == 128) return launch_tiles<DT, 1, 1, ROWS, 4>(a, frags_m);
     if (c.ft == 2) return launch_tiles<DT, 2, 1, ROWS>(a, frags_m);
     return c.fn == 2 ? launch_tiles<DT, 4, 2, ROWS>(a, frags_m) : launch_tiles<DT, 4, 1, ROWS>(a, frags_m);
 }

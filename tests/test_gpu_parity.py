@@ -1020,6 +1020,17 @@ def test_expanded_of_what_is_not_finite(form, dtype, R, T, M, N, what):
         _assert_like(Y[t0:t1], ref[t0:t1], dtype)
 
 
+# the edges of the rule for tiles of 32 tokens x 64 and x 128 columns: 32 workgroups on an XCD and one more token, 1536 and 1280
+# columns and more, one token, ragged columns and steps
+@pytest.mark.parametrize("form,dtype,R,T,M,N", [
+    ("transposed", "bf16", 16, 1, 64, 64), ("transposed", "f16", 8, 33, 200, 65), ("transposed", "bf16", 16, 256, 320, 1536),
+    ("transposed", "f16", 8, 256, 72, 1537), ("transposed", "bf16", 32, 512, 128, 1024), ("transposed", "f16", 16, 513, 272, 1024),
+    ("transposed", "bf16", 8, 1024, 72, 1000), ("transposed", "bf16", 16, 1025, 128, 1000), ("transposed", "bf16", 16, 700, 128, 1280),
+    ("layer", "bf16", 16, 1, 64, 64), ("layer", "f16", 24, 40, 1512, 264), ("layer", "bf16", 5, 513, 1020, 72), ("layer", "f16", 16, 1024, 1024, 136)])
+def test_expanded_tiles_of_few_tokens(form, dtype, R, T, M, N):
+    test_expanded_of_what_is_not_finite(form, dtype, R, T, M, N, "some")
+
+
 def test_expanded_costs_the_same_order_whatever_the_inputs():
     """A batch of non-finite inputs (an overflow in fp16 training) takes a few times as long as a finite one: 2 to 9 were
     measured, 30 are allowed (it was several hundred when each such token was computed by itself)."""
