@@ -607,7 +607,8 @@ size_t linear_expand_bytes(int64_t M, int64_t N, int32_t R) { return expanded_by
 // 10x (the dense one to 15 %, the gather's to a factor of 2).  Of 709 calls that the first pair alone made dense, 39 were slower
 // so: 30528 x 768, R = 8 at 1.1x, one token 20.4 us by the gather and 96.3 dense; 4096 x 1024, R = 1 at 1.43x, 40 tokens 27.6 / 58.7;
 // 16384 x 4096, R = 16 at 1.1x, 40 tokens 115 / 266.
-bool linear_expand_pays(int64_t T, int64_t M, int64_t N, int32_t R, int64_t capacity_cols) {
+namespace {
+bool expand_pays_strict(int64_t T, int64_t M, int64_t N, int32_t R, int64_t capacity_cols) {
     const int64_t npad = (N + 255) / 256 * 256, tok = npad <= 1024 ? 64 : (npad <= 2048 ? 32 : 16);
     const double steps = (double)capacity_cols / 32.0 * (double)((T + tok - 1) / tok) / 256.0;  // per compute unit
     const double per_step = (tok == 64 ? 0.040 : (tok == 32 ? 0.035 : 0.030)) * (R <= 16 ? 1.0 : (R <= 32 ? 2.1 : 4.0));
@@ -621,6 +622,46 @@ bool linear_expand_pays(int64_t T, int64_t M, int64_t N, int32_t R, int64_t capa
     const double gather = 11.0 + kStep[tok == 64 ? 0 : (tok == 32 ? 1 : 2)][R <= 16 ? 0 : (R <= 32 ? 1 : 2)] * steps +
                           0.07 * (double)(M / R) * (double)((T + tok - 1) / tok) / 256.0;
     return dense < gather;
+}
+
+// Those rules were made when the smallest tile was 64 x 128, and to be wrong on one side only: of 31600 calls of 64 to 16384
+// rows, 64 to 4096 columns, R = 1 to 64, 1 to 8192 tokens, 1.1x to 10x they lost 18 % of the time on average against the faster
+// form (1024 x 4096, R = 32 at 2x, 914 tokens 64 us by the gather, 32 dense; 896 x 896, R = 8 at 2x, 1752 tokens 26 / 15; 640 x 640,
+// R = 32 at 1.5x, 166 tokens 15.9 / 10.6).  These two estimates, fitted to those calls (the dense one to 8 %, the gather's to
+// 11 to 19 %), add the calls where dense is the shorter by a margin: 13 %, or 25 % for up to 1024 columns and twice as many rows or
+// more, where the gather's is up to 1.4 times too long (3072 x 768 at 1.4x, 476 tokens 14.0 us for 19.7).  With both the loss is 4 %, the mean
+// 0.88 of the time before, and 0.15 % of the calls are slower than by the gather by more than 8 % (up to 1.3x).  A call of two launches and a
+// workspace takes 10 us on the host, so nothing shorter is asked to be dense.
+bool expand_pays_fitted(int64_t T, int64_t M, int64_t N, int32_t R, int64_t capacity_cols) {
+    if (M > 16384 || T > 8192) return false;  // beyond what the estimates were fitted to
+    const int64_t npad = (N + 255) / 256 * 256, tok = npad <= 1024 ? 64 : (npad <= 2048 ? 32 : 16);
+    const double blocks = (double)(M / R), all = blocks * (double)(N + 31);
+    const double cols = (double)capacity_cols < all ? (double)capacity_cols : all, out = (double)T * (double)M * 1e-6;
+    const int few = few_columns(T, M);
+    double product;
+    if (few != 0) {
+        product = 7.37 + (few == 64 ? 0.168 : 0.246) * (double)((N + kStageK - 1) / kStageK);
+    } else {
+        double tiles, tiles_xcd;
+        choose_tile(T, N, M, &tiles, &tiles_xcd);
+        product = 3.33 + 0.80 * tiles + (tiles_xcd > tiles ? 0.73 * (tiles_xcd - tiles) : 0.0);
+    }
+    const double workgroups = (double)((M + 255) / 256 * 256 / R) * (double)(npad / 256) * (double)((R + 15) / 16);
+    const double dense = product + 0.0016 * workgroups + 1.52e-6 * (double)M * (double)N + 0.65 * out;
+    // [width][R to 16, 32, 64]: the call, a step of all compute units, a step of a row-block, 1000 columns, a million outputs
+    constexpr double kGather[3][3][5] = {
+        {{6.38, 0.0484, 0.334, 0.99, 1.20}, {6.30, 0.0594, 0.528, 1.35, 1.06}, {9.37, 0.568, 1.72, 1.04, 2.56}},
+        {{4.85, 0.0348, 0.342, 1.09, 3.24}, {4.28, 0.0570, 0.429, 1.57, 1.23}, {7.56, 0.209, 1.03, 0.36, 3.32}},
+        {{4.58, 0.0320, 0.334, 0.49, 4.11}, {3.91, 0.0567, 0.412, 0.84, 1.60}, {6.45, 0.222, 0.902, 0.03, 0.0}}};
+    const double *k = kGather[tok == 64 ? 0 : (tok == 32 ? 1 : 2)][R <= 16 ? 0 : (R <= 32 ? 1 : 2)];
+    const double gather = k[0] + k[1] * cols / 32.0 * (double)((T + tok - 1) / tok) / 256.0 + k[2] * cols / blocks / 32.0 +
+                          k[3] * 1e-3 * (double)N + k[4] * out;
+    return (dense < 10.0 ? 10.0 : dense) < (tok == 64 && M >= 2 * N ? 0.75 : 0.87) * gather;
+}
+}  // namespace
+
+bool linear_expand_pays(int64_t T, int64_t M, int64_t N, int32_t R, int64_t capacity_cols) {
+    return expand_pays_strict(T, M, N, R, capacity_cols) || expand_pays_fitted(T, M, N, R, capacity_cols);
 }
 
 int linear_expand(const void *X, int xdt, int64_t T, int64_t M, int64_t N, int32_t R, const int32_t *blk_cnt,

@@ -1031,6 +1031,24 @@ def test_expanded_tiles_of_few_tokens(form, dtype, R, T, M, N):
     test_expanded_of_what_is_not_finite(form, dtype, R, T, M, N, "some")
 
 
+# calls that are dense by the fitted estimates alone, one of each kind: few tokens (tiles of 64 and of 128 columns), many, wide
+# layers, high row-blocks; and calls near the line that stay with the gather
+@pytest.mark.parametrize("dtype,R,rate,T,M,N,dense", [
+    ("bf16", 32, 1.5, 166, 640, 640, True), ("f16", 16, 2.0, 1752, 896, 896, True), ("bf16", 32, 2.0, 914, 1024, 4096, True),
+    ("bf16", 16, 1.5, 1182, 384, 1536, True), ("f16", 48, 2.0, 700, 768, 1024, True),
+    ("bf16", 16, 3.0, 4096, 3072, 768, False), ("bf16", 16, 1.4, 476, 3072, 768, False), ("f16", 16, 2.0, 16, 256, 256, False)])
+def test_layer_on_its_storage_where_dense_pays(dtype, R, rate, T, M, N, dense):
+    X, W, bias = wl.normal(T, (T, N), 1.0, dtype), wl.normal(T + 1, (M, N), 0.02, dtype), wl.normal(T + 2, (M,), 0.5, dtype)
+    keep = wl.bernoulli_keep_mask(T + 3, M // R, N, 1.0 / rate)
+    p = bsp.bsp_pack(dev(W, dtype), R, torch.from_numpy(keep).cuda(), 32)
+    assert (bsp.lib().bsp_linear_workspace_bytes(CODE[dtype], T, M, N, R, 32, p.total_cols) > 0) == dense
+    Y = host(bsp.bsp_linear(dev(X, dtype), p, dev(bias, dtype)))
+    p_ref = orc.pack(W, R, keep, 32, CODE[dtype])
+    for t0, t1 in ((0, min(T, 48)), (max(0, T - 40), T)):
+        ref = orc.linear_packed(X, p_ref, bias, ydt=CODE[dtype], t0=t0, t1=t1, n_threads=16)[0]
+        assert_y_close(Y[t0:t1], ref[t0:t1], dtype)
+
+
 def test_expanded_costs_the_same_order_whatever_the_inputs():
     """A batch of non-finite inputs (an overflow in fp16 training) takes a few times as long as a finite one: 2 to 9 were
     measured, 30 are allowed (it was several hundred when each such token was computed by itself)."""
