@@ -111,12 +111,18 @@ __global__ __launch_bounds__(kDvThreads) void dvals_items_kernel(int64_t B, int3
                                                                 DvItem *__restrict__ items,
                                                                 uint16_t *__restrict__ perm,
                                                                 uint16_t *__restrict__ slotcol,
-                                                                int32_t *__restrict__ groups, int32_t tables,
+                                                                int32_t *__restrict__ groups, int32_t list_wgs, int32_t tables,
                                                                 int32_t *__restrict__ colstart) {
-    // for the dense form: entry j of row-block b's table counts its kept columns below 128 j
-    for (int64_t i = (int64_t)blockIdx.x * kDvThreads + threadIdx.x; i < B * tables; i += (int64_t)gridDim.x * kDvThreads) {
-        const int64_t b = i / tables;
-        colstart[i] = dv_lower_bound(col_idx + blk_ptr[b], blk_cnt[b], (int)(i - b * tables) * 128);
+    // The workgroups from list_wgs on make the dense form's table: entry j of row-block b's counts its kept columns below 128 j.
+    // (Beside the list and not in front of it: a search is a chain of ten loads.  With that and the choice of m below for all of
+    // its values at once the launch takes 14.4 us, 22.3 before; 3072 x 1024, R = 16, 5x.)
+    if ((int)blockIdx.x >= list_wgs) {
+        const int64_t step = (int64_t)((int)gridDim.x - list_wgs) * kDvThreads;
+        for (int64_t i = (int64_t)((int)blockIdx.x - list_wgs) * kDvThreads + threadIdx.x; i < B * tables; i += step) {
+            const int64_t b = i / tables;
+            colstart[i] = dv_lower_bound(col_idx + blk_ptr[b], blk_cnt[b], (int)(i - b * tables) * 128);
+        }
+        return;
     }
     __shared__ int s_scan[kDvThreads];
     __shared__ uint16_t s_perm[kDvThreads / kWave][kDvItemCols];
@@ -169,7 +175,7 @@ __global__ __launch_bounds__(kDvThreads) void dvals_items_kernel(int64_t B, int3
     {
         const int lane = tid & (kWave - 1), wave = tid / kWave;
         const uint64_t below = ((uint64_t)1 << lane) - 1;
-        for (int it = blockIdx.x * (kDvThreads / kWave) + wave; it < run; it += gridDim.x * (kDvThreads / kWave)) {
+        for (int it = blockIdx.x * (kDvThreads / kWave) + wave; it < run; it += list_wgs * (kDvThreads / kWave)) {
             const DvItem item = items[it];
             if (item.ncols == 0) {  // a filler
 #pragma unroll
@@ -201,25 +207,21 @@ __global__ __launch_bounds__(kDvThreads) void dvals_items_kernel(int64_t B, int3
             const int budget = min(16, (ncols + 15) / 16 + 1);
             // (passes of an LDS read: one for a group of all bank groups; the columns of one bank group that fill the groups
             // behind are dealt round these, so one of them takes as many as its fullest bank group has there)
-            int m = 0, tail = 0, best = 1 << 30;
-            for (int mm = 16; mm >= 0; --mm) {
-                int over = lane < 16 ? max(0, mycnt - mm) : 0, most = over;
+            // Lane mm looks at m = mm.
+            int over = 0, most = 0;
 #pragma unroll
-                for (int o = 1; o < 16; o <<= 1) {
-                    over += __shfl_xor(over, o, kWave);
-                    most = max(most, __shfl_xor(most, o, kWave));
-                }
-                over = __shfl(over, 0, kWave);  // (the same in lanes 0 .. 15; lane 0 decides)
-                most = __shfl(most, 0, kWave);
-                const int behind = (over + 15) / 16;
-                if (mm + behind > budget) continue;
-                const int passes = mm + (behind ? behind * ((most + behind - 1) / behind) : 0);
-                if (passes < best) {
-                    best = passes;
-                    m = mm;
-                    tail = over;
-                }
+            for (int k = 0; k < 16; ++k) {
+                const int o = max(0, __builtin_amdgcn_readlane(mycnt, k) - lane);
+                over += o;
+                most = max(most, o);
             }
+            const int groups_behind = (over + 15) / 16;
+            const int passes = lane + (groups_behind ? groups_behind * ((most + groups_behind - 1) / groups_behind) : 0);
+            // the fewest passes, and of those the largest m  (m = 0 always fits)
+            int best = lane <= 16 && lane + groups_behind <= budget ? passes * 32 + (16 - lane) : 1 << 30;
+#pragma unroll
+            for (int o = 1; o < 32; o <<= 1) best = min(best, __shfl_xor(best, o, kWave));
+            const int m = 16 - (__builtin_amdgcn_readfirstlane(best) & 31), tail = __shfl(over, m, kWave);
             const int behind = max(1, (tail + 15) / 16);  // groups behind the first m
             int ovf = lane < 16 ? max(0, mycnt - m) : 0, pre = ovf;  // exclusive prefix of the overflow per bank group
 #pragma unroll
@@ -640,9 +642,12 @@ extern "C" int bsp_linear_dvals(const void *X, const void *dY, int xdt, int64_t 
         // a wavefront per item in the second part, in at most 64 workgroups
         int64_t lg = (L.max_items + kDvThreads / kWave - 1) / (kDvThreads / kWave);
         lg = lg < 1 ? 1 : (lg > 64 ? 64 : lg);
+        int64_t tg = (B * L.tables + kDvThreads - 1) / kDvThreads;
+        tg = tg < 4096 ? tg : 4096;
         if (ws_state == BSP_DVALS_BUILD)
-            dvals_items_kernel<<<(unsigned)lg, kDvThreads, 0, s>>>(B, nslab, nr, blk_cnt, blk_ptr, col_idx,
-                                                                   (int32_t)L.max_items, hdr, items, perm, slotcol, groups, L.tables, colstart);
+            dvals_items_kernel<<<(unsigned)(lg + tg), kDvThreads, 0, s>>>(B, nslab, nr, blk_cnt, blk_ptr, col_idx,
+                                                                          (int32_t)L.max_items, hdr, items, perm, slotcol, groups,
+                                                                          (int32_t)lg, L.tables, colstart);
         if (N % 8 == 0 && aligned(X, 16)) {
             const DvalsDenseChoice c = dvals_dense_choose(T, M, N, R, capacity_cols, (int64_t)((L.total - L.partial_at) / sizeof(float)));
             if (c.shape >= 0 && dvals_dense_pays(c.us, ntiles, L, R))
