@@ -550,7 +550,7 @@ def weight_gradient(mats, reps=10, with_cpu=True):
         tot_us += us
         tot_flops += m.useful_flops()
         del dY, D, ws
-    res = {"kernels": ["dvals_items_kernel", "dvals_partial_kernel", "dvals_reduce_kernel"], "per_matrix": out,
+    res = {"kernels": ["dvals_items_kernel", "dvals_dense_kernel", "dvals_sum_kernel"], "per_matrix": out,
            "us": round(tot_us, 1), "useful_tflops": round(tot_flops / tot_us / 1e6, 2),
            "frac_mfma_peak": round(tot_flops / tot_us / 1e6 / MFMA_BF16_PEAK_TFLOPS, 4),
            "roofline": {"bound": "hbm", "achieved": round(hbm_bytes / tot_us / 1e3, 1), "peak": HBM_PEAK_GBS,

@@ -1,5 +1,5 @@
-"""ctypes binding of include/bsp.h.  Same names as the C entry points; argument marshalling
-only.  Tensors must live on the GPU, be contiguous and have the dtype the C call expects; the
+"""Binding of include/bsp.h: native functions (csrc/bsp_host.cpp) for the hot path, ctypes for the rest.  Same names as the C
+entry points; argument marshalling only.  Tensors must live on the GPU, be contiguous and have the dtype the C call expects; the
 kernels are enqueued on torch's current stream.  There is no CPU fallback: if libbsp.so cannot
 be loaded the import of `lib()` raises."""
 from __future__ import annotations
