@@ -302,7 +302,8 @@ int bsp_linear_transposed_dense(const void *U, int udt, int64_t T, int64_t M, in
  * gdt (RNE); two calls with the same arguments give the same bits.  That path needs ws: device
  * scratch of at least bsp_linear_dvals_workspace_bytes(M, N, R, capacity_cols) bytes, 256-byte
  * aligned.  Its head holds a work list derived from the storage alone (not from X, dY or T):
- * ws_state = BSP_DVALS_BUILD builds it (one more launch, 10 to 30 us), BSP_DVALS_REUSE states
+ * ws_state = BSP_DVALS_BUILD builds it (one more launch, 10 to 30 us; whatever T, the type and
+ * the addresses of X and dY, so also with T == 0), BSP_DVALS_REUSE states
  * that the last call with this ws had the same storage and M, N, R, capacity_cols and reuses it
  * -- the case of Alg. 2's retraining, where the mask is fixed while W is updated step after step.
  * The rest of ws is undefined before and after.  Other arguments (fp32 inputs, other R, ws ==

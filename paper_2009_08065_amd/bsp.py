@@ -446,12 +446,12 @@ def bsp_linear_dvals(X, dY, p: Packed, out_dtype=None, D=None, ws=None, ws_state
     if D is None:
         D = torch.empty(p.R * p.total_cols, dtype=out_dtype, device=X.device)
     need = native.bsp_linear_dvals_workspace_bytes(p.M, p.N, p.R, p.total_cols)
-    if ws is None:
+    if ws is None and T > 0 and X.dtype != torch.float32:  # (the others need none, and a list that nobody reuses is not built)
         ws = torch.empty(max(need, 256), dtype=torch.uint8, device=X.device)
     has = p.total_cols > 0
     st = native.bsp_linear_dvals(X, dY, _DT[X.dtype], T, p.M, p.N, p.R, p.k_align, p.blk_cnt,
                                  p.blk_ptr, p.col_idx if has else None, p.total_cols,
-                                 D if has else None, _DT[D.dtype], ws, ws.numel(), ws_state, _stream())
+                                 D if has else None, _DT[D.dtype], ws, 0 if ws is None else ws.numel(), ws_state, _stream())
     _check(st, "bsp_linear_dvals")
     return D
 

@@ -624,13 +624,15 @@ extern "C" int bsp_linear_dvals(const void *X, const void *dY, int xdt, int64_t 
     if (B >= ((int64_t)1 << 31) - 65536 || (double)R * (double)capacity_cols >= 9.0e18) return BSP_ERR_SHAPE;
     hipStream_t s = (hipStream_t)stream;
     const int64_t ntiles = (T + kDvTok - 1) / kDvTok;
-    const bool fast = xdt != BSP_F32 && T > 0 && R % 8 == 0 && R <= 64 && N % 4 == 0 && N < ((int64_t)1 << 22) && M < ((int64_t)1 << 26) &&
-                      ntiles < ((int64_t)1 << 30) && capacity_cols < ((int64_t)1 << 31) && aligned(X, 8) &&
-                      aligned(dY, 16) && ws && aligned(ws, 256);
-    if (fast) {
+    // what the work list asks of the storage and the workspace; what the matrix cores ask of the operands besides
+    const bool listable = R % 8 == 0 && R <= 64 && N % 4 == 0 && N < ((int64_t)1 << 22) && M < ((int64_t)1 << 26) &&
+                          capacity_cols < ((int64_t)1 << 31) && ws && aligned(ws, 256);
+    const bool fast = listable && xdt != BSP_F32 && T > 0 && ntiles < ((int64_t)1 << 30) && aligned(X, 8) && aligned(dY, 16);
+    if (listable) {
         const DvLayout L = dv_layout(M, N, R, capacity_cols);
-        if (L.max_items + B >= ((int64_t)1 << 31)) return BSP_ERR_SHAPE;
-        if (ws_bytes < L.total) return BSP_ERR_CAPACITY;
+        const bool indexable = L.max_items + B < ((int64_t)1 << 31);
+        if (fast && !indexable) return BSP_ERR_SHAPE;
+        if (fast && ws_bytes < L.total) return BSP_ERR_CAPACITY;
         int32_t *hdr = (int32_t *)ws;
         DvItem *items = (DvItem *)((uint8_t *)ws + L.items_at);
         uint16_t *perm = (uint16_t *)((uint8_t *)ws + L.perm_at);
@@ -644,24 +646,28 @@ extern "C" int bsp_linear_dvals(const void *X, const void *dY, int xdt, int64_t 
         lg = lg < 1 ? 1 : (lg > 64 ? 64 : lg);
         int64_t tg = (B * L.tables + kDvThreads - 1) / kDvThreads;
         tg = tg < 4096 ? tg : 4096;
-        if (ws_state == BSP_DVALS_BUILD)
+        // (by every call that says so, also one whose operands take the plain kernel: no tokens, fp32, other addresses.  A later one
+        // that reuses the list may have others)
+        if (ws_state == BSP_DVALS_BUILD && indexable && ws_bytes >= L.total)
             dvals_items_kernel<<<(unsigned)(lg + tg), kDvThreads, 0, s>>>(B, nslab, nr, blk_cnt, blk_ptr, col_idx,
                                                                           (int32_t)L.max_items, hdr, items, perm, slotcol, groups,
                                                                           (int32_t)lg, L.tables, colstart);
-        if (N % 8 == 0 && aligned(X, 16)) {
-            const DvalsDenseChoice c = dvals_dense_choose(T, M, N, R, capacity_cols, (int64_t)((L.total - L.partial_at) / sizeof(float)));
-            if (c.shape >= 0 && dvals_dense_pays(c.us, ntiles, L, R))
-                return launch_dvals_dense(DvalsDense{(const uint16_t *)X, (const uint16_t *)dY, xdt, T, M, N, R, blk_cnt, blk_ptr, col_idx,
-                                                     colstart, capacity_cols, partial, D, gdt, s}, c);
+        if (fast) {
+            if (N % 8 == 0 && aligned(X, 16)) {
+                const DvalsDenseChoice c = dvals_dense_choose(T, M, N, R, capacity_cols, (int64_t)((L.total - L.partial_at) / sizeof(float)));
+                if (c.shape >= 0 && dvals_dense_pays(c.us, ntiles, L, R))
+                    return launch_dvals_dense(DvalsDense{(const uint16_t *)X, (const uint16_t *)dY, xdt, T, M, N, R, blk_cnt, blk_ptr, col_idx,
+                                                         colstart, capacity_cols, partial, D, gdt, s}, c);
+            }
+            const int64_t pgrid = (L.max_units + 7) / 8 * 8;  // whole rounds of the 8 XCDs
+            const int st = xdt == BSP_BF16 ? launch_partial<BSP_BF16>(s, X, dY, T, M, N, R, hdr, items, slotcol, groups, partial, pgrid)
+                                           : launch_partial<BSP_F16>(s, X, dY, T, M, N, R, hdr, items, slotcol, groups, partial, pgrid);
+            if (st != BSP_OK) return st;
+            const unsigned grid = (unsigned)(L.max_items + B);
+            BSP_DISPATCH_DTYPE(gdt, GDT, (dvals_reduce_kernel<GDT><<<grid, kDvReduceThreads, 0, s>>>(
+                                             B, R, blk_cnt, blk_ptr, hdr, items, perm, groups, partial, (int32_t)L.max_items, (int32_t)ntiles, D)));
+            return check_launch();
         }
-        const int64_t pgrid = (L.max_units + 7) / 8 * 8;  // whole rounds of the 8 XCDs
-        const int st = xdt == BSP_BF16 ? launch_partial<BSP_BF16>(s, X, dY, T, M, N, R, hdr, items, slotcol, groups, partial, pgrid)
-                                       : launch_partial<BSP_F16>(s, X, dY, T, M, N, R, hdr, items, slotcol, groups, partial, pgrid);
-        if (st != BSP_OK) return st;
-        const unsigned grid = (unsigned)(L.max_items + B);
-        BSP_DISPATCH_DTYPE(gdt, GDT, (dvals_reduce_kernel<GDT><<<grid, kDvReduceThreads, 0, s>>>(
-                                         B, R, blk_cnt, blk_ptr, hdr, items, perm, groups, partial, (int32_t)L.max_items, (int32_t)ntiles, D)));
-        return check_launch();
     }
     if (B > 0x7fffffff) return BSP_ERR_SHAPE;
     const dim3 grid((unsigned)B, 8);

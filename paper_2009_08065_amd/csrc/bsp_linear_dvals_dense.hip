@@ -167,6 +167,9 @@ __global__ __launch_bounds__(WR *WC * 64) void dvals_dense_kernel(
         constexpr int f = decltype(i)::value / kGroups, g = decltype(i)::value % kGroups;
         gkp[f][g] -= gbase[f][g];
         if (n0 + G::BN >= N) gend[f][g] = gkp[f][g];  // (the last columns' tile writes the pads, too)
+        // (kept inside the row-block's panel whatever the workspace holds)
+        glo[f][g] = min(max(glo[f][g], 0), gkp[f][g]);
+        gend[f][g] = min(max(gend[f][g], glo[f][g]), gkp[f][g]);
 #pragma unroll
         for (int e = 0; e < kCols; ++e) {
             const int c = gbase[f][g] + min(glo[f][g] + lane + 64 * e, gend[f][g] - 1);

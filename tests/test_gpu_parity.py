@@ -1269,6 +1269,30 @@ def test_linear_dvals_same_bits_twice_and_is_the_gradient_of_the_layer():
     assert abs(lhs - rhs) <= 2e-3 * float(np.abs(Y * dY).sum())      # Y carries one bf16 rounding per output
 
 
+@pytest.mark.parametrize("built_by", ["no tokens", "fp32 inputs", "dY at 8 bytes", "X at 4 bytes"])
+@pytest.mark.parametrize("N", [520, 1100])               # the dense form and the sparse one
+def test_linear_dvals_list_built_by_any_call(N, built_by):
+    """BSP_DVALS_BUILD builds the work list from the storage, whatever T, type and addresses the operands of that call have; a call
+    that reuses the list finds it there."""
+    T, M, R = 200, 96, 16
+    d = wl.layer(9100 + N, T, M, N, "bf16")
+    dY = wl.normal(9101 + N, (T, M), 1.0, "bf16")
+    keep = wl.bernoulli_keep_mask(9102 + N, M // R, N, 0.4)
+    p = bsp.bsp_pack(dev(d["W"], "bf16"), R, torch.from_numpy(keep).cuda(), 32)
+    ws = torch.zeros(bsp.lib().bsp_linear_dvals_workspace_bytes(M, N, R, p.total_cols), dtype=torch.uint8, device="cuda")
+    Xd, dYd = dev(d["X"], "bf16"), dev(dY, "bf16")
+    at = lambda t, elements: torch.cat([t.new_zeros(elements), t.flatten()])[elements:].view_as(t)
+    X0, dY0 = {"no tokens": (Xd[:0], dYd[:0]), "fp32 inputs": (Xd[:1].float(), dYd[:1].float()),
+               "dY at 8 bytes": (Xd[:1], at(dYd[:1], 4)), "X at 4 bytes": (at(Xd[:1], 2), dYd[:1])}[built_by]
+    first = host(bsp.bsp_linear_dvals(X0, dY0, p, out_dtype=torch.float32, ws=ws))
+    p_ref = orc.pack(d["W"], R, keep, 32, orc.BF16)
+    T0 = X0.shape[0]
+    assert_y_close(first, orc.linear_dvals(d["X"][:T0], dY[:T0], p_ref, gdt=orc.F32)[0], "f32")
+    assert int(ws[:4].view(torch.int32)[0]) > 0           # (without a list nothing may be reused)
+    D = host(bsp.bsp_linear_dvals(Xd, dYd, p, out_dtype=torch.float32, ws=ws, ws_state=bsp.DVALS_REUSE))
+    assert_y_close(D, orc.linear_dvals(d["X"], dY, p_ref, gdt=orc.F32)[0], "f32")
+
+
 def test_config4_bert_large_layer_set_dvals():
     """The weight gradient of every BERT-large matrix at the benchmark's size (8192 tokens, 5x), every kept position."""
     for i, d in enumerate(wl.config4(R=16)):
