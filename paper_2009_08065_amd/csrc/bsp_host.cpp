@@ -86,6 +86,57 @@ bool read_tensor(PyObject *o, const char *want, at::ScalarType type, void *&out)
     return true;
 }
 
+// What else stands for a number, as for ctypes: its own scalar of the argument's type, and an object that names another as its
+// _as_parameter_.  A new reference, or null with the error that was set.
+PyObject *other_number(PyObject *o, const char *scalar) {
+    if (!PyErr_ExceptionMatches(PyExc_TypeError)) return nullptr;
+    PyObject *type, *value, *trace;
+    PyErr_Fetch(&type, &value, &trace);
+    PyObject *n = strcmp(Py_TYPE(o)->tp_name, scalar) == 0 ? PyObject_GetAttrString(o, "value") : nullptr;
+    if (!n) {
+        PyErr_Clear();
+        n = PyObject_GetAttrString(o, "_as_parameter_");
+    }
+    if (n) {
+        Py_XDECREF(type);
+        Py_XDECREF(value);
+        Py_XDECREF(trace);
+    } else {
+        PyErr_Clear();
+        PyErr_Restore(type, value, trace);
+    }
+    return n;
+}
+
+// Whole numbers: everything with __index__ (numpy's, a tensor of one).  Of one larger than the type the low bits.
+template <typename T>
+bool read_whole(PyObject *o, T &out) {
+    PyObject *n = PyNumber_Index(o);
+    if (!n) {
+        n = other_number(o, std::is_unsigned_v<T> ? "c_ulong" : (sizeof(T) == 8 ? "c_long" : "c_int"));
+        if (!n) return false;
+        const bool ok = read_whole(n, out);
+        Py_DECREF(n);
+        return ok;
+    }
+    out = static_cast<T>(PyLong_AsUnsignedLongLongMask(n));
+    Py_DECREF(n);
+    return true;
+}
+
+bool read_real(PyObject *o, float &out) {
+    const double v = PyFloat_AsDouble(o);
+    if (v == -1.0 && PyErr_Occurred()) {
+        PyObject *n = other_number(o, "c_float");
+        if (!n) return false;
+        const bool ok = read_real(n, out);
+        Py_DECREF(n);
+        return ok;
+    }
+    out = static_cast<float>(v);
+    return true;
+}
+
 // STREAM: the argument is the stream, an address.
 template <unsigned C, bool STREAM, typename T>
 bool read(PyObject *o, T &out) {
@@ -103,19 +154,9 @@ bool read(PyObject *o, T &out) {
         out = static_cast<T>(p);
         return ok;
     } else if constexpr (std::is_floating_point_v<T>) {
-        const double v = PyFloat_AsDouble(o);
-        if (v == -1.0 && PyErr_Occurred()) return false;
-        out = static_cast<T>(v);
-        return true;
+        return read_real(o, out);
     } else {
-        if (!PyLong_Check(o)) {
-            PyErr_Format(PyExc_TypeError, "int expected instead of %s instance", Py_TYPE(o)->tp_name);
-            return false;
-        }
-        const unsigned long long v = PyLong_AsUnsignedLongLongMask(o);
-        if (v == ~0ull && PyErr_Occurred()) return false;
-        out = static_cast<T>(v);
-        return true;
+        return read_whole(o, out);
     }
 }
 

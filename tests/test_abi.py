@@ -4,6 +4,7 @@ import ctypes as C
 import os
 import re
 
+import numpy as np
 import pytest
 import torch
 
@@ -170,3 +171,42 @@ def test_native_functions_check_what_they_are_given():
     assert n.last(torch.tensor([3, 9, 7], dtype=torch.int32)) == 7
     with pytest.raises(RuntimeError):
         n.empty(host, 0, -1)
+
+
+class _Index:
+    def __index__(self):
+        return 16
+
+
+class _Named:
+    def __init__(self, v):
+        self._as_parameter_ = v
+
+
+def test_native_functions_take_the_numbers_that_ctypes_takes():
+    """A number in any form that the ctypes call of the same function accepts reaches the library (0: the call has no tokens; 3: 24
+    rows are not whole row-blocks), and every other form is refused by both."""
+    native, plain = bsp.bsp._native(), bsp.lib()
+    a, i = _Elsewhere(), _Elsewhere(torch.int32)
+
+    def both(M, R):
+        return (native.bsp_linear_sized(a, 0, 0, M, 64, R, 32, i, i, i, a, 64, None, a, None, 0, 0),
+                plain.bsp_linear_sized(4096, 0, 0, M, 64, R, 32, 4096, 4096, 4096, 4096, 64, None, 4096, None, 0, 0))
+    for R in (16, np.int64(16), np.int32(16), np.uint8(16), torch.tensor(16), torch.tensor([16]), _Index(), _Named(16), _Named(_Index()),
+              C.c_int32(16)):
+        assert both(64, R) == (0, 0) and both(40, R) == (2, 2), R
+    assert both(np.prod((4, 16)), 16) == (0, 0) and both(C.c_int64(64), 16) == (0, 0)
+    for R in (16.0, np.float64(16), np.float32(16), torch.tensor(16.0), "16", None, C.c_float(16), _Named(16.0)):
+        with pytest.raises(TypeError):
+            native.bsp_linear_sized(a, 0, 0, 64, 64, R, 32, i, i, i, a, 64, None, a, None, 0, 0)
+        with pytest.raises(C.ArgumentError):
+            plain.bsp_linear_sized(4096, 0, 0, 64, 64, R, 32, 4096, 4096, 4096, 4096, 64, None, 4096, None, 0, 0)
+    # the threshold, without a decision to make (NULL: refused by the library)
+    for t in (0.5, 1, np.float32(0.5), np.int64(1), torch.tensor(0.5), _Index(), _Named(0.5), C.c_float(0.5)):
+        assert native.bsp_prune_mask(None, 4, 4, t, -1, 0, None, None, None, 0, 0) == 1, t
+        assert plain.bsp_prune_mask(None, 4, 4, t, -1, 0, None, None, None, 0, 0) == 1, t
+    for t in ("0.5", None, C.c_double(0.5)):
+        with pytest.raises(TypeError):
+            native.bsp_prune_mask(None, 4, 4, t, -1, 0, None, None, None, 0, 0)
+        with pytest.raises(C.ArgumentError):
+            plain.bsp_prune_mask(None, 4, 4, t, -1, 0, None, None, None, 0, 0)
