@@ -9,7 +9,7 @@
 //
 // The checks are the binding's own: a tensor is contiguous and on the GPU, and of its pointer's type where that function
 // asks for it.  Only plain tensors are read directly; anything else is asked through its Python attributes, as before.
-// The interpreter lock is released during the call, as ctypes does.
+// The interpreter lock is released during the call, as ctypes does, and while results are allocated, as torch does.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 #include <ATen/core/Tensor.h>
@@ -210,7 +210,12 @@ PyObject *empty(PyObject *, PyObject *const *args, Py_ssize_t n) {
         return nullptr;
     }
     const auto options = at::TensorOptions().dtype(types[type]).device(THPVariable_Unpack(args[0]).device());
-    return THPVariable_Wrap(at::empty(at::IntArrayRef(size, (size_t)(n - 2)), options));
+    at::Tensor t;
+    {
+        const Unlocked unlocked;  // (an allocation may wait for the device)
+        t = at::empty(at::IntArrayRef(size, (size_t)(n - 2)), options);
+    }
+    return THPVariable_Wrap(std::move(t));
     END_HANDLE_TH_ERRORS
 }
 

@@ -3,6 +3,8 @@ arguments on the host before anything is launched (so these run without a GPU)."
 import ctypes as C
 import os
 import re
+import threading
+import time
 
 import numpy as np
 import pytest
@@ -210,3 +212,33 @@ def test_native_functions_take_the_numbers_that_ctypes_takes():
             native.bsp_prune_mask(None, 4, 4, t, -1, 0, None, None, None, 0, 0)
         with pytest.raises(C.ArgumentError):
             plain.bsp_prune_mask(None, 4, 4, t, -1, 0, None, None, None, 0, 0)
+
+
+def test_results_are_allocated_without_the_interpreter_lock():
+    """While a result is allocated other Python threads run: an allocation that takes long (here for its filling, on a GPU for hipMalloc
+    or the cache's flush) does not hold them."""
+    native, host = bsp.bsp._native(), torch.zeros(1)
+    ticks, stop = [], threading.Event()
+
+    def tick():
+        while not stop.wait(0.001):
+            ticks.append(time.perf_counter())
+    deterministic = torch.are_deterministic_algorithms_enabled(), torch.is_deterministic_algorithms_warn_only_enabled()
+    threads = torch.get_num_threads()
+    thread = threading.Thread(target=tick)
+    thread.start()
+    try:
+        torch.use_deterministic_algorithms(True)         # new memory is filled
+        torch.set_num_threads(1)
+        start = time.perf_counter()
+        native.empty(host, 3, 1 << 30)
+        end = time.perf_counter()
+    finally:
+        torch.use_deterministic_algorithms(deterministic[0], warn_only=deterministic[1])
+        torch.set_num_threads(threads)
+        stop.set()
+        thread.join()
+    if end - start < 0.05:
+        pytest.skip("the allocation is too short to see another thread beside it")
+    third = (end - start) / 3
+    assert any(start + third < t < end - third for t in ticks)
