@@ -193,14 +193,35 @@ struct Entry<Fn, C> {
     }
 };
 
+// empty() beside an object that is no plain tensor: torch.empty with the object's own device.
+PyObject *empty_beside_other(PyObject *like, const char *type, const int64_t *size, int dims) {
+    PyObject *torch = PyImport_ImportModule("torch");
+    if (!torch) return nullptr;
+    PyObject *make = PyObject_GetAttrString(torch, "empty"), *dtype = PyObject_GetAttrString(torch, type);
+    PyObject *device = PyObject_GetAttrString(like, "device"), *result = nullptr;
+    PyObject *args = dims == 1 ? Py_BuildValue("((L))", (long long)size[0]) : Py_BuildValue("((LL))", (long long)size[0], (long long)size[1]);
+    if (make && dtype && device && args) {
+        PyObject *named = Py_BuildValue("{s:O,s:O}", "dtype", dtype, "device", device);
+        if (named) result = PyObject_Call(make, args, named);
+        Py_XDECREF(named);
+    }
+    Py_DECREF(torch);
+    Py_XDECREF(make);
+    Py_XDECREF(dtype);
+    Py_XDECREF(device);
+    Py_XDECREF(args);
+    return result;
+}
+
 // empty(like, type, n) or empty(like, type, n, m): a tensor on the device of `like`; type: a bsp_dtype, 3 uint8, 4 int32.
 PyObject *empty(PyObject *, PyObject *const *args, Py_ssize_t n) {
     HANDLE_TH_ERRORS
-    if ((n != 3 && n != 4) || !THPVariable_Check(args[0])) {
+    if (n != 3 && n != 4) {
         PyErr_SetString(PyExc_TypeError, "empty(tensor, type, n[, m])");
         return nullptr;
     }
     constexpr at::ScalarType types[] = {at::kFloat, at::kBFloat16, at::kHalf, at::kByte, at::kInt};
+    constexpr const char *names[] = {"float32", "bfloat16", "float16", "uint8", "int32"};
     const long long type = PyLong_AsLongLong(args[1]);
     int64_t size[2] = {0, 0};
     for (Py_ssize_t i = 2; i < n; ++i) size[i - 2] = PyLong_AsLongLong(args[i]);
@@ -209,6 +230,7 @@ PyObject *empty(PyObject *, PyObject *const *args, Py_ssize_t n) {
         PyErr_SetString(PyExc_ValueError, "unknown type");
         return nullptr;
     }
+    if (!THPVariable_CheckExact(args[0])) return empty_beside_other(args[0], names[type], size, (int)n - 2);
     const auto options = at::TensorOptions().dtype(types[type]).device(THPVariable_Unpack(args[0]).device());
     at::Tensor t;
     {
@@ -219,12 +241,17 @@ PyObject *empty(PyObject *, PyObject *const *args, Py_ssize_t n) {
     END_HANDLE_TH_ERRORS
 }
 
-// last(tensor): the last element of a vector of whole numbers, read back.
+// last(tensor): the last element of a vector of whole numbers, read back; of an object that is no plain tensor int(o[-1].item()).
 PyObject *last(PyObject *, PyObject *o) {
     HANDLE_TH_ERRORS
-    if (!THPVariable_Check(o)) {
-        PyErr_SetString(PyExc_TypeError, "last(tensor)");
-        return nullptr;
+    if (!THPVariable_CheckExact(o)) {
+        PyObject *at = PyLong_FromLong(-1), *element = at ? PyObject_GetItem(o, at) : nullptr;
+        PyObject *value = element ? PyObject_CallMethod(element, "item", nullptr) : nullptr;
+        PyObject *whole = value ? PyNumber_Long(value) : nullptr;
+        Py_XDECREF(at);
+        Py_XDECREF(element);
+        Py_XDECREF(value);
+        return whole;
     }
     const at::Tensor &t = THPVariable_Unpack(o);
     int64_t v;

@@ -242,3 +242,26 @@ def test_results_are_allocated_without_the_interpreter_lock():
         pytest.skip("the allocation is too short to see another thread beside it")
     third = (end - start) / 3
     assert any(start + third < t < end - third for t in ticks)
+
+
+def test_native_allocations_beside_an_object_that_is_no_plain_tensor():
+    """Results lie on the device that such an object names, and its last element is read through its own methods."""
+    class Vector:
+        device = torch.device("cpu")
+
+        def __getitem__(self, i):
+            return torch.tensor([4, 6, 9])[i]
+
+    class Sub(torch.Tensor):
+        pass
+    native = bsp.bsp._native()
+    for like in (Vector(), torch.zeros(2).as_subclass(Sub), torch.nn.Parameter(torch.zeros(2)), torch.zeros(2)):
+        a, b = native.empty(like, 4, 5), native.empty(like, 1, np.int64(2), 3)
+        assert type(a) is torch.Tensor and a.shape == (5,) and a.dtype == torch.int32 and a.device.type == "cpu"
+        assert type(b) is torch.Tensor and b.shape == (2, 3) and b.dtype == torch.bfloat16
+    assert native.last(Vector()) == 9 and native.last(torch.tensor([3, 8], dtype=torch.int32).as_subclass(Sub)) == 8
+    assert type(native.last(Vector())) is int
+    with pytest.raises(AttributeError):
+        native.empty(3.0, 4, 5)
+    with pytest.raises(IndexError):
+        native.last(torch.zeros(0, dtype=torch.int32))
