@@ -1,7 +1,7 @@
 """Binding of include/bsp.h: native functions (csrc/bsp_host.cpp) for the hot path, ctypes for the rest.  Same names as the C
 entry points; argument marshalling only.  Tensors must live on the GPU, be contiguous and have the dtype the C call expects; the
 kernels are enqueued on torch's current stream.  There is no CPU fallback: if libbsp.so cannot
-be loaded the import of `lib()` raises."""
+be loaded `lib()` raises."""
 from __future__ import annotations
 
 import ctypes as C
@@ -44,12 +44,12 @@ def lib():
         return _LIB
     path = library_path()
     from . import build as _build
-    if not os.path.exists(path) or not os.path.exists(_build.HOST_LIB):
+    if not os.path.exists(path):
         _build.build(force=True)
     elif _build.stale():
         # a built library is loaded as it is (GPU runs must not compile); say so when a source is newer
         import warnings
-        warnings.warn("libbsp.so is older than its sources: run `python -m paper_2009_08065_amd.build`")
+        warnings.warn("libbsp.so or _bsp_host.so is missing or older than the sources: run `python -m paper_2009_08065_amd.build`")
     L = C.CDLL(path)
     i64, i32, f32, vp, sz = C.c_int64, C.c_int32, C.c_float, C.c_void_p, C.c_size_t
     L.bsp_group_norms.argtypes = [vp, C.c_int, i64, i64, i32, f32, C.c_int, vp, vp, vp, vp]
@@ -111,6 +111,9 @@ def _native():
     global _NATIVE
     if _NATIVE is None:
         lib()  # (the same library, loaded once)
+        from . import build as _build
+        if not os.path.exists(_build.HOST_LIB):
+            _build.build_host()
         from . import _bsp_host
         _NATIVE = _bsp_host
     return _NATIVE

@@ -31,7 +31,7 @@ def _compile(src):
     return obj
 
 
-def _build_host():
+def build_host():
     """The Python functions of the C entry points (tensors in, native code only: no device code in this file)."""
     torch_dir = os.path.dirname(importlib.util.find_spec("torch").origin)
     subprocess.run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-fvisibility=hidden", "-I", INCLUDE,
@@ -60,7 +60,7 @@ def build(force: bool = True) -> str:
     with ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:
         objs = list(ex.map(_compile, SOURCES))
     subprocess.run([_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs, "-ldl"], check=True)
-    _build_host()
+    build_host()
     return LIB
 
 

@@ -265,3 +265,23 @@ def test_native_allocations_beside_an_object_that_is_no_plain_tensor():
         native.empty(3.0, 4, 5)
     with pytest.raises(IndexError):
         native.last(torch.zeros(0, dtype=torch.int32))
+
+
+def test_a_missing_native_module_is_built_alone(monkeypatch, tmp_path):
+    """The library with the kernels does not need the module with the Python functions: without the module it is loaded as it is,
+    and only the module is built, when it is needed."""
+    from paper_2009_08065_amd import build
+    built = []
+
+    def refuse(*args, **kwargs):
+        raise AssertionError("the kernels are compiled")
+    monkeypatch.setattr(build, "HOST_LIB", str(tmp_path / "_bsp_host.so"))
+    monkeypatch.setattr(build, "build", refuse)
+    monkeypatch.setattr(build, "_compile", refuse)
+    monkeypatch.setattr(build, "build_host", lambda: built.append("host"), raising=False)
+    monkeypatch.setattr(bsp.bsp, "_LIB", None)
+    monkeypatch.setattr(bsp.bsp, "_NATIVE", None)
+    with pytest.warns(UserWarning, match="missing or older"):
+        assert bsp.bsp.lib().bsp_version()
+    assert built == []
+    assert bsp.bsp._native().bsp_mask_weights(None, 0, 4, 4, 2, None, 0) == 1 and built == ["host"]
