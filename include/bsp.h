@@ -326,6 +326,9 @@ int bsp_linear_dvals(const void *X, const void *dY, int xdt, int64_t T, int64_t 
  * every lane's matrix-core operands lie ready to load.  bsp_linear_planned computes exactly
  * what bsp_linear computes (same sums, different order of the additions) from that buffer
  * alone; it needs neither blk_ptr, col_idx nor vals.
+ * Rows of one call may be summed in two orders (the end of a long batch may go through another
+ * kernel than the rest), so equal rows of X give rows of Y that are equal up to one rounding;
+ * two calls with the same arguments give the same bits.
  * bsp_linear_plan_supported: 1 when (xdt, N, k_align) can be planned (bf16 / fp16,
  * 32 <= N <= 4096, N % 8 == 0, k_align % 32 == 0), else 0; the other calls return
  * BSP_ERR_SHAPE for an unsupported layer and the caller stays with bsp_linear.

@@ -451,7 +451,7 @@ __global__ __launch_bounds__((CW + kStLoadWaves) * 64) void linear_stream16_kern
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 y[v] = acc[a][u][v] + bv[a][v];
-                if constexpr (ACT == BSP_ACT_GELU) y[v] = 0.5f * y[v] * (1.0f + erff(y[v] * 0.70710678118654752f));
+                if constexpr (ACT == BSP_ACT_GELU) y[v] = gelu_fit(y[v]);
             }
             if constexpr (RESIDUAL) {
                 const uint2 rw = res[u & 1][a];

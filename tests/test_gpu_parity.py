@@ -621,6 +621,28 @@ def test_linear_planned_batch_in_two(dtype, R, T, M, N, rate, act, with_res):
         assert_y_close(Y[lo:hi], ref, dtype)
 
 
+@pytest.mark.parametrize("T,M,N,rate", [(8200, 1024, 4096, 2.0), (4100, 1024, 2048, 1.3)])
+def test_linear_planned_rows_on_both_sides_of_the_seam(T, M, N, rate):
+    """Batches whose end goes through the kernel for few tokens, all rows alike: one GELU on both sides (zero weights, so the sums are
+    the bias itself: the same bits), and sums that differ by the order of their additions alone (at most one rounding apart)."""
+    R, seam = 16, T // 512 * 512
+    keep = torch.from_numpy(wl.bernoulli_keep_mask(7701 + N, M // R, N, 1.0 / rate)).cuda()
+    x = wl.normal(7702, (1, N), 1.0, "bf16")
+    X = dev(np.repeat(x, T, axis=0), "bf16")
+    v = torch.linspace(-9.0, 9.0, M).bfloat16().cuda()
+    p = bsp.bsp_pack(torch.zeros(M, N, dtype=torch.bfloat16, device="cuda"), R, keep, 32)
+    Y = host(bsp.bsp_linear_planned_fused(X, p, bsp.bsp_linear_plan(p), v, act=bsp.ACT_GELU))
+    assert bits_equal(Y, np.repeat(Y[:1], T, axis=0))
+    ref = orc.epilogue(host(v), orc.ACT_GELU)[1]
+    assert np.all(np.abs(Y[T - 1] - ref) <= ULP["bf16"] / 2 * np.abs(ref) + 1.5e-7 * np.abs(host(v)))   # (as in test_gelu_over_its_range)
+    p = bsp.bsp_pack(dev(wl.normal(7703, (M, N), 0.02, "bf16"), "bf16"), R, keep, 32)
+    Y = host(bsp.bsp_linear_planned_fused(X, p, bsp.bsp_linear_plan(p), v))
+    assert bits_equal(Y[:seam], np.repeat(Y[:1], seam, axis=0)) and bits_equal(Y[seam:], np.repeat(Y[seam:seam + 1], T - seam, axis=0))
+    rms = np.sqrt(np.mean(Y[0].astype(np.float64) ** 2))
+    # (fp32 sums of up to 4096 terms: 1e-5 of the rms leaves an order of room)
+    assert np.all(np.abs(Y[0] - Y[seam]) <= ULP["bf16"] * np.abs(Y[0]) + 1e-5 * rms)
+
+
 @pytest.mark.parametrize("R,T,M,N", [(16, 600, 32768, 64), (8, 1090, 30528, 72), (16, 577, 16400, 1544), (32, 1030, 30528, 2056)])
 def test_linear_planned_tall_layers(R, T, M, N):
     """Tall layers of 9 to 18 ragged token tiles, whose workgroups go to all compute units and not tile by tile to the XCDs: every
