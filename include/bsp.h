@@ -297,8 +297,8 @@ int bsp_linear_transposed_dense(const void *U, int udt, int64_t T, int64_t M, in
  * row-major contiguous, dtype xdt; D: R * blk_ptr[B] elements of dtype gdt (at most
  * R * capacity_cols; the caller owns it, every element is written).  bf16 / fp16 inputs with
  * R % 8 == 0, R <= 64, N % 4 == 0, X 8-byte and dY 16-byte aligned go through the matrix cores:
- * products exact, sums in fp32 (per tile of 32 tokens inside the matrix instruction, tiles in
- * ascending order inside a range of tokens, then the ranges in ascending order), rounded once to
+ * products exact, sums in fp32 (chains of matrix instructions over ranges of tokens, whose sums
+ * are added up in ascending order), rounded once to
  * gdt (RNE); two calls with the same arguments give the same bits.  That path needs ws: device
  * scratch of at least bsp_linear_dvals_workspace_bytes(M, N, R, capacity_cols) bytes, 256-byte
  * aligned.  Its head holds a work list derived from the storage alone (not from X, dY or T):

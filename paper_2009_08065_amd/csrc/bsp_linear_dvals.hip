@@ -16,8 +16,8 @@
 // column, is one 16-byte read) and the items' 16 columns of dY untransposed (the transposing LDS read delivers the
 // other operand).
 //
-// That form pays where a layer keeps little and the batch is large; elsewhere the call is a dense product of which the kept
-// positions are written (bsp_linear_dvals_dense.hip; dvals_dense_pays decides).
+// That form pays where a large layer keeps little and the batch is large (4096 x 1024 at 5x from about 5000 tokens); elsewhere the call is a dense
+// product of which the kept positions are written (bsp_linear_dvals_dense.hip; dvals_dense_pays decides).
 #include "bsp_common.h"
 #include "bsp_linear_internal.h"
 #include "bsp_mfma_device.h"
@@ -263,12 +263,11 @@ __global__ __launch_bounds__(kDvThreads) void dvals_items_kernel(int64_t B, int3
 }
 
 // Token ranges of a call: as many as give about kDvUnits workgroups, whole tiles each.  tiles_per_range, ranges.
-__device__ __forceinline__ void dv_ranges(int strips, int ntiles, int &tpu, int &S) {
+__host__ __device__ __forceinline__ void dv_ranges(int64_t strips, int ntiles, int &tpu, int &S) {
     tpu = 1;
     S = 0;
     if (strips <= 0) return;
-    int want = kDvUnits / strips;
-    if (want < 1) want = 1;
+    int want = strips < kDvUnits ? kDvUnits / (int)strips : 1;
     if (want > ntiles) want = ntiles;
     tpu = (ntiles + want - 1) / want;
     S = (ntiles + tpu - 1) / tpu;
@@ -536,8 +535,9 @@ __global__ __launch_bounds__(256) void dvals_plain_kernel(const void *__restrict
 struct DvLayout {
     int64_t max_items, max_units;
     int32_t tables;          // entries of a row-block's column table
-    int64_t expected_items;  // with the kept columns spread evenly over row-blocks and columns
-    double expected_groups;  // of an item
+    int64_t expected_strips;  // with the kept columns spread evenly over row-blocks and columns
+    int64_t least_strips;     // with as many columns in an item as it holds
+    double expected_groups;   // of an item
     size_t items_at, groups_at, perm_at, slotcol_at, colstart_at, partial_at, total;
 };
 DvLayout dv_layout(int64_t M, int64_t N, int32_t R, int64_t capacity_cols) {
@@ -552,7 +552,9 @@ DvLayout dv_layout(int64_t M, int64_t N, int32_t R, int64_t capacity_cols) {
     const int64_t ranges = (N + kDvRange - 1) / kDvRange, runs = M / R * ranges;
     const double cols = (double)capacity_cols / (double)runs;
     const int64_t cut = (int64_t)(cols / kDvItemCols) + 1;
-    L.expected_items = (R + 15) / 16 * runs * cut;
+    L.expected_strips = ((R + 15) / 16 * runs * cut + kDvStrip - 1) / kDvStrip;
+    L.least_strips = ((R + 15) / 16 * (capacity_cols / kDvItemCols) + kDvStrip - 1) / kDvStrip;
+    if (L.least_strips < 1) L.least_strips = 1;
     L.expected_groups = cols / (double)cut / 16.0 + 1.0 < (double)kDvGroups ? cols / (double)cut / 16.0 + 1.0 : (double)kDvGroups;
     L.colstart_at = L.slotcol_at + (size_t)L.max_items * kDvItemCols * sizeof(uint16_t);
     L.partial_at = (L.colstart_at + (size_t)(M / R) * (size_t)L.tables * sizeof(int32_t) + 255) / 256 * 256;
@@ -560,17 +562,15 @@ DvLayout dv_layout(int64_t M, int64_t N, int32_t R, int64_t capacity_cols) {
     return L;
 }
 
-// Whether the dense form (bsp_linear_dvals_dense.hip) is the faster one: against microseconds fitted to 260 calls of 768 to 4096 rows, 256
-// to 4096 columns, 16 to 8192 tokens at 1.43x to 8x (10 % off on average).  Of those five were faster by the sparse form, all from
-// 5x and 3400 tokens on: 2688 x 896, R = 16 at 8x, 7529 tokens 38.0 / 50.2; 3584 x 896 at 8x, 6260 tokens 40.6 / 44.9; 4096 x 1024
-// at 5x, 8192 tokens 56.8 / 63.
-bool dvals_dense_pays(double dense_us, int64_t ntiles, const DvLayout &L, int32_t R) {
-    const int64_t strips = L.expected_items / kDvStrip + 1;
-    const int64_t want = strips < kDvUnits ? (kDvUnits / strips < ntiles ? kDvUnits / strips : ntiles) : 1;
-    const int64_t tpu = (ntiles + want - 1) / want, units = strips * ((ntiles + tpu - 1) / tpu);
+// Whether the dense form (bsp_linear_dvals_dense.hip) is the faster one: against microseconds fitted to 605 calls of 256 to 4096 rows and
+// columns, 16 to 16384 tokens at 1.43x to 8x (7 % off on average).  Sparse / dense, whole calls in us: 4096 x 1024, R = 16 at 5x, 8192 tokens
+// 58.2 / 64.8, 4096 tokens 39.0 / 38.6; at 8x, 6000 tokens 41.6 / 49.6; 1024 x 1024 at 5x, 8192 tokens 31.7 / 25.8.  Near the line the wrong
+// one is taken now and then: at 5x, 6000 tokens 47.3 / 52.0 (dense).
+bool dvals_dense_pays(double dense_us, int64_t tpu, int64_t S, const DvLayout &L, int32_t R) {
+    const int64_t units = L.expected_strips * S;
     const double rounds = (double)((units + kDvUnits - 1) / kDvUnits);
     const double bytes = (double)units * (double)kDvStrip * L.expected_groups * 1024.0 * (R % 16 == 8 && R < 16 ? 0.5 : 1.0);
-    return dense_us < 10.8 + 1.144 * (double)tpu * rounds + 0.386e-6 * bytes;
+    return dense_us < 10.9 + 1.207 * (double)tpu * rounds + 0.451e-6 * bytes;
 }
 
 template <typename K>
@@ -654,8 +654,14 @@ extern "C" int bsp_linear_dvals(const void *X, const void *dY, int xdt, int64_t 
                                                                           (int32_t)lg, L.tables, colstart);
         if (fast) {
             if (N % 8 == 0 && aligned(X, 16)) {
-                const DvalsDenseChoice c = dvals_dense_choose(T, M, N, R, capacity_cols, (int64_t)((L.total - L.partial_at) / sizeof(float)));
-                if (c.shape >= 0 && dvals_dense_pays(c.us, ntiles, L, R))
+                int tpu, S, tpu_least, S_least;
+                dv_ranges(L.expected_strips, (int)ntiles, tpu, S);
+                dv_ranges(L.least_strips, (int)ntiles, tpu_least, S_least);
+                // A result in 16 bits does not show where its fp32 sum was rounded on the way (3e-7 beside 1.7e-4 or more).
+                const int64_t e = dvals_sums_error(tpu, S), e_least = dvals_sums_error(tpu_least, S_least);
+                const int64_t error = gdt != BSP_F32 ? INT64_MAX : (e < e_least ? e : e_least);
+                const DvalsDenseChoice c = dvals_dense_choose(T, M, N, R, capacity_cols, (int64_t)((L.total - L.partial_at) / sizeof(float)), error);
+                if (c.shape >= 0 && dvals_dense_pays(c.us, tpu, S, L, R))
                     return launch_dvals_dense(DvalsDense{(const uint16_t *)X, (const uint16_t *)dY, xdt, T, M, N, R, blk_cnt, blk_ptr, col_idx,
                                                          colstart, capacity_cols, partial, D, gdt, s}, c);
             }

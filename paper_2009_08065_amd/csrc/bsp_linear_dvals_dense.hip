@@ -4,9 +4,9 @@
 // Why dense: the sparse form reads one kibibyte of LDS per 16 x 16 x 32 product and its partial sums fill the registers of
 // the chip, so its start and its end take 20 us whatever the batch; a dense tile reads a sixth of that per product and its sums
 // leave it by their kept positions alone, with few runs of the tokens (often one: no second pass).  At 1 / density times the
-// products it is the faster one for nearly all rates that layers are pruned at (dvals_dense_pays).  Measured (MI355X, us, the
-// sparse form / this one): 2304 x 768, R = 8 at 2x, 509 tokens 25.6 / 7.2; 4096 x 1024, R = 32 at 1.43x, 4099 tokens 73.9 / 40.5; R = 16 at 5x,
-// 8192 tokens 56.8 / 63 (stays sparse): there the matrix cores are busy for two thirds of the time at 1.8 GHz.
+// products it is the faster one except where a large layer keeps little of many tokens (dvals_dense_pays).  Measured (MI355X, us, the whole
+// call with its list, fp32 result, the sparse form / this one): 2304 x 768, R = 8 at 2x, 509 tokens 25.5 / 8.0; 4096 x 1024, R = 32 at 1.43x, 4099 tokens 78.9 / 43.8;
+// R = 16 at 5x, 4096 tokens 39.0 / 38.6, 8192 tokens 58.2 / 64.8 (stays sparse).
 //
 // A workgroup owns BM rows of dY^T x BN columns of X and a run of the tokens, 32 tokens a stage, four stages in LDS.  Both
 // operands are read from memory as they lie, [token][columns], straight into LDS, and the transposing LDS reads give a lane
@@ -71,12 +71,15 @@ struct DdShape {
     static_assert(NY * kWaves * 1024 == kYBytes && NX * kWaves * 1024 == kDdTok * PX && BN % 128 == 0);
 };
 
-// ODT: the type that is written, fp32 for runs' sums that dvals_sum_kernel adds.
-template <int DT, int ODT, int FM, int FN, int WR, int WC>
-__global__ __launch_bounds__(WR *WC * 64) void dvals_dense_kernel(
+// ODT: the type that is written, fp32 for runs' sums that dvals_sum_kernel adds.  TOTALS: chains shorter than the run, which takes a second
+// set of registers.
+template <int DT, int ODT, int FM, int FN, int WR, int WC, bool TOTALS>
+// (the launch bounds: with totals as many registers as two or three workgroups on a compute unit leave; with more of them the sums would
+// lie in accumulation registers, three instructions away from an addition)
+__global__ __launch_bounds__(WR *WC * 64, !TOTALS ? 1 : (FM == 1 ? 3 : 2)) void dvals_dense_kernel(
     const uint16_t *__restrict__ X, const uint16_t *__restrict__ dY, int64_t T, int32_t M, int32_t N, int32_t R,
     const int32_t *__restrict__ blk_cnt, const int32_t *__restrict__ blk_ptr, const int32_t *__restrict__ col_idx,
-    const int32_t *__restrict__ colstart, int32_t max_col, int32_t per, int32_t S, int64_t stride,
+    const int32_t *__restrict__ colstart, int32_t max_col, int32_t per, int32_t S, int32_t chain, int64_t stride,
     void *__restrict__ sums) {
     using G = DdShape<DT, FM, FN, WR, WC>;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -222,6 +225,15 @@ __global__ __launch_bounds__(WR *WC * 64) void dvals_dense_kernel(
         for (int g = 0; g < FN; ++g)
 #pragma unroll
             for (int i = 0; i < 16; ++i) acc[f][g][i] = 0.0f;
+    // What a chain of matrix instructions has added up goes to the totals when the next chain begins: see sums_chain below.
+    f32x16 total[TOTALS ? FM : 1][TOTALS ? FN : 1];
+    int chain_left = chain;
+    if constexpr (TOTALS) {
+#pragma unroll
+        for (int f = 0; f < FM; ++f)
+#pragma unroll
+            for (int g = 0; g < FN; ++g) total[f][g] = acc[f][g];
+    }
 
     using I0 = std::integral_constant<int, 0>;
     using I1 = std::integral_constant<int, 1>;
@@ -234,6 +246,17 @@ __global__ __launch_bounds__(WR *WC * 64) void dvals_dense_kernel(
     auto products = [&](auto half, auto fetch_next, auto load) {
         constexpr int H = decltype(half)::value;
         constexpr int kProducts = FM * FN, kReads = FM + FN;
+        if constexpr (TOTALS && H == 0) {
+            if (chain_left == 0) {  // uniform
+                chain_left = chain;
+                static_for<0, kProducts>([&](auto p) {
+                    constexpr int f = decltype(p)::value / FN, g = decltype(p)::value % FN;
+                    total[f][g] += acc[f][g];
+                    acc[f][g] = f32x16{};
+                });
+            }
+            --chain_left;
+        }
         static_for<0, kProducts>([&](auto p) {
             constexpr int P = decltype(p)::value;
             acc[P / FN][P % FN] = mfma32<DT>(xf[H][P % FN], yf[H][P / FN], acc[P / FN][P % FN]);
@@ -293,7 +316,8 @@ __global__ __launch_bounds__(WR *WC * 64) void dvals_dense_kernel(
         for (int g = 0; g < FN; ++g)
 #pragma unroll
             for (int q = 0; q < 4; ++q) {  // four consecutive columns of one row
-                const f32x16 v = acc[f][g];
+                f32x16 v = acc[f][g];
+                if constexpr (TOTALS) v += total[f][g];
                 *reinterpret_cast<f32x4 *>(out + (32 * wr + (lane & 31)) * G::kPitch + 32 * (wc * FN + g) + 8 * q + 4 * (lane >> 5)) =
                     f32x4{v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
             }
@@ -341,10 +365,10 @@ __global__ __launch_bounds__(256) void dvals_sum_kernel(int64_t B, int32_t R, co
     }
 }
 
-template <int DT, int ODT, int FM, int FN, int WR, int WC>
-int launch_dense(const DvalsDense &a, int S, int per) {
+template <int DT, int ODT, int FM, int FN, int WR, int WC, bool TOTALS>
+int launch_dense(const DvalsDense &a, int S, int per, int chain) {
     using G = DdShape<DT, FM, FN, WR, WC>;
-    auto k = dvals_dense_kernel<DT, ODT, FM, FN, WR, WC>;
+    auto k = dvals_dense_kernel<DT, ODT, FM, FN, WR, WC, TOTALS>;
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)G::kLds);
     if (e != hipSuccess) {  // (asking again is harmless)
         set_last_hip_error((int)e);
@@ -354,7 +378,7 @@ int launch_dense(const DvalsDense &a, int S, int per) {
     if (wgs >= ((int64_t)1 << 31)) return BSP_ERR_SHAPE;
     const int64_t stride = ((int64_t)a.R * a.capacity_cols + 3) / 4 * 4;
     k<<<(unsigned)wgs, G::kWaves * 64, G::kLds, a.s>>>(a.X, a.dY, a.T, (int32_t)a.M, (int32_t)a.N, a.R, a.blk_cnt, a.blk_ptr, a.col_idx,
-                                                       a.colstart, (int32_t)(a.capacity_cols - 1), per, S, stride, S > 1 ? (void *)a.partial : a.D);
+                                                       a.colstart, (int32_t)(a.capacity_cols - 1), per, S, chain, stride, S > 1 ? (void *)a.partial : a.D);
     if (S > 1) {
         const unsigned grid = (unsigned)(((int64_t)a.R * a.capacity_cols + 1023) / 1024);
         const int vec = aligned(a.D, 16) ? 1 : 0;
@@ -365,30 +389,52 @@ int launch_dense(const DvalsDense &a, int S, int per) {
 
 }  // namespace
 
-// Which tile and how many runs of the tokens: the least estimated time, microseconds fitted to 2700 calls of 768 to 4096 rows,
-// 256 to 4096 columns and 16 to 8192 tokens (8 % off on average; the choice costs 3 % against the best of all of them).  A
-// workgroup of the largest tile fills a compute unit; of the others two and three share one.  For example (MI355X, us of the
-// three with their best number of runs): 4096 x 1024, R = 16 at 5x, 8192 tokens 63 / 71 / 82; R = 32 at 1.43x, 4099 tokens
-// 47.6 / 40.5 / 45.2; 2304 x 768, R = 8 at 2x, 509 tokens 17.5 / 9.2 / 7.2.
-DvalsDenseChoice dvals_dense_choose(int64_t T, int64_t M, int64_t N, int32_t R, int64_t capacity_cols, int64_t partial_floats) {
+namespace {
+// The square of a sum's error grows with the stages of a chain of matrix instructions, which rounds a sum that grows all along, and with the
+// additions that put the chains together; a stage counts as much as 2.7 additions (dvals_sums_error).  Measured, sums of N(0, 1) products in
+// fp32 against 64 bits: 1.25e-7 of the value for a chain of 16 stages, 2.7e-7 of 64, 5.8e-7 of 256; 64 stages in chains of 4 0.97e-7, of 8
+// 1.03e-7, of 16 1.33e-7; 256 in chains of 8 1.36e-7.
+// The longest chain for sums over `runs` runs of `per` stages that are no further off than `error`, that of the sparse form's runs: with one
+// chain per run this form's were up to 2.1 times as far (4096 x 1024, R = 32 at 1.43x, 4099 tokens 4.0e-7 against 1.9e-7).  0: none is.
+int64_t sums_chain(int64_t per, int64_t runs, int64_t error) {
+    auto off = [&](int64_t c) { return dvals_sums_error(c, (per + c - 1) / c + runs - 1); };
+    const double k = (double)(error + 20 - 10 * runs), d = k * k - 1080.0 * (double)per;
+    int64_t c = per;
+    if (off(c) > error) c = d < 0.0 ? 0 : (int64_t)((k + __builtin_sqrt(d)) / 54.0);
+    while (c > 0 && off(c) > error) --c;
+    return c < per ? c : per;
+}
+}  // namespace
+
+// Which tile and how many runs of the tokens: the least estimated time of those whose sums are near enough, microseconds fitted to 17800
+// launches of 605 calls of 256 to 4096 rows and columns, 16 to 16384 tokens, 1.43x to 8x (4 to 7 % off on average; on 712
+// other calls the choice, the sparse form among it, costs 1.0 % against the fastest of all that was measured, more than 10 % in 2 % of them).  A
+// workgroup of the largest tile fills a compute unit; of the others two and three share one; a stage takes longer the more of the chip
+// is busy.  The largest tile has no registers for totals, so for fp32 results it is taken where its runs are as short as the sparse form's, at
+// low rates.  What the chains cost: fp32 results of 150 drawn calls take 1.045 of the time of one chain per run, 0.44 of the sparse form's alone.
+DvalsDenseChoice dvals_dense_choose(int64_t T, int64_t M, int64_t N, int32_t R, int64_t capacity_cols, int64_t partial_floats, int64_t error) {
     constexpr struct {
         int bm, bn;
-        double fixed, alone, shared, end;  // a stage of a workgroup alone on a compute unit, and per workgroup of several
-    } shapes[] = {{256, 256, 9.0, 0.534, 0.0, 0.0}, {128, 128, 5.2, 0.224, 0.264, 1.14}, {64, 128, 5.1, 0.170, 0.167, 0.61}};
+        double fixed, alone, full, shared, end, flush;  // a stage of a workgroup alone on its compute unit, more of it the fuller the chip
+                                                        // is, per workgroup of several; a workgroup's end; its sums to the totals
+    } shapes[] = {{256, 256, 5.4, 0.445, 0.079, 0.524, 3.8, 0.0}, {128, 128, 5.5, 0.200, 0.056, 0.176, 1.41, 0.285}, {64, 128, 4.5, 0.179, 0.030, 0.124, 0.77, 0.069}};
     const int64_t stages = (T + kDdTok - 1) / kDdTok, stride = ((int64_t)R * capacity_cols + 3) / 4 * 4;
-    DvalsDenseChoice best = {-1, 0, 0, 0.0};
+    DvalsDenseChoice best = {-1, 0, 0, 0, 0.0};
     for (int i = 0; i < 3; ++i) {
         const int64_t tiles = ((M + shapes[i].bm - 1) / shapes[i].bm) * ((N + shapes[i].bn - 1) / shapes[i].bn);
         for (int64_t S = 1; S <= 16 && S <= stages; ++S) {
             if ((S > 1 && S * stride > partial_floats) || tiles * S >= ((int64_t)1 << 30)) break;
             const int64_t per = (stages + S - 1) / S;
             if ((stages + per - 1) / per != S) continue;  // (runs without a stage)
-            const double count = (double)(tiles * S) / 256.0;  // workgroups per compute unit
-            const double stage = i == 0 ? shapes[i].alone * __builtin_ceil(count)
-                                        : (count <= 1.0 ? shapes[i].alone : __builtin_fmax(shapes[i].alone, shapes[i].shared * count));
-            double us = shapes[i].fixed + stage * (double)per + shapes[i].end * (count < 1.0 ? 1.0 : count);
-            if (S > 1) us += 1.8 + 1.3e-6 * (double)(S + 1) * (double)stride;
-            if (best.shape < 0 || us < best.us) best = {i, (int)S, (int)per, us};
+            const double count = (double)(tiles * S) / 256.0, rounds = __builtin_ceil(count);  // workgroups per compute unit
+            const double stage = __builtin_fmax(shapes[i].alone + shapes[i].full * __builtin_fmin(count, 1.0), shapes[i].shared * rounds);
+            double us = shapes[i].fixed + stage * (double)per + shapes[i].end * rounds;
+            if (S > 1) us += 1.0 + 0.25 * (double)S + 1.37e-6 * (double)(S + 1) * (double)stride;
+            if (best.shape >= 0 && us >= best.us) continue;
+            const int64_t chain = sums_chain(per, S, error);
+            if (chain < 1 || (i == 0 && chain < per)) continue;
+            us += shapes[i].flush * (double)per / (double)chain * rounds;
+            if (best.shape < 0 || us < best.us) best = {i, (int)S, (int)per, (int)chain, us};
         }
     }
     return best;
@@ -397,9 +443,14 @@ DvalsDenseChoice dvals_dense_choose(int64_t T, int64_t M, int64_t N, int32_t R, 
 int launch_dvals_dense(const DvalsDense &a, const DvalsDenseChoice &c) {
     auto shape = [&](auto dt, auto odt) {
         constexpr int DT = decltype(dt)::value, ODT = decltype(odt)::value;
-        if (c.shape == 0) return launch_dense<DT, ODT, 4, 2, 2, 4>(a, c.S, c.per);
-        if (c.shape == 1) return launch_dense<DT, ODT, 2, 2, 2, 2>(a, c.S, c.per);
-        return launch_dense<DT, ODT, 1, 2, 2, 2>(a, c.S, c.per);
+        if (c.shape == 0) return launch_dense<DT, ODT, 4, 2, 2, 4, false>(a, c.S, c.per, c.chain);
+        if constexpr (ODT == BSP_F32) {  // (16-bit results of one run ask for no chains)
+            if (c.chain < c.per)
+                return c.shape == 1 ? launch_dense<DT, ODT, 2, 2, 2, 2, true>(a, c.S, c.per, c.chain)
+                                    : launch_dense<DT, ODT, 1, 2, 2, 2, true>(a, c.S, c.per, c.chain);
+        }
+        if (c.shape == 1) return launch_dense<DT, ODT, 2, 2, 2, 2, false>(a, c.S, c.per, c.chain);
+        return launch_dense<DT, ODT, 1, 2, 2, 2, false>(a, c.S, c.per, c.chain);
     };
     auto go = [&](auto dt) {
         if (c.S > 1 || a.gdt == BSP_F32) return shape(dt, std::integral_constant<int, BSP_F32>{});

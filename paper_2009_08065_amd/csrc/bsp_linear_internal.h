@@ -262,10 +262,14 @@ struct DvalsDense {
     hipStream_t s;
 };
 struct DvalsDenseChoice {
-    int shape, S, per;  // tile, runs of the tokens, stages of a run
-    double us;          // the estimate
+    int shape, S, per, chain;  // tile, runs of the tokens, stages of a run, stages of a chain of its sums
+    double us;                 // the estimate
 };
-DvalsDenseChoice dvals_dense_choose(int64_t T, int64_t M, int64_t N, int32_t R, int64_t capacity_cols, int64_t partial_floats);
+// How far fp32 sums are from their values that chains of matrix instructions over `chain` stages of 32 tokens make, added up one after the
+// other: see bsp_linear_dvals_dense.hip.
+inline int64_t dvals_sums_error(int64_t chain, int64_t chains) { return 27 * chain + 10 * (chains - 1); }
+// (error: what the sums may be off)
+DvalsDenseChoice dvals_dense_choose(int64_t T, int64_t M, int64_t N, int32_t R, int64_t capacity_cols, int64_t partial_floats, int64_t error);
 int launch_dvals_dense(const DvalsDense &a, const DvalsDenseChoice &c);
 
 }  // namespace bsp

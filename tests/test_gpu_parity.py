@@ -1315,6 +1315,30 @@ def test_linear_dvals_list_built_by_any_call(N, built_by):
     assert_y_close(D, orc.linear_dvals(d["X"], dY, p_ref, gdt=orc.F32)[0], "f32")
 
 
+@pytest.mark.parametrize("R,rate,T,M,N", [(8, 2.0, 509, 2304, 768), (32, 1.4285, 4099, 1024, 1024), (16, 5.0, 8192, 1024, 1024), (16, 2.0, 2048, 1024, 1024),
+                                           (16, 3.0, 130, 768, 768), (16, 1.4285, 7000, 256, 1024), (16, 1.4285, 8192, 4096, 1024)])
+def test_linear_dvals_error_of_the_sums(R, rate, T, M, N):
+    """The dense form's fp32 sums are as near to 64 bits as the sparse form's, whose chains of matrix instructions are shorter (X at an address
+    of 8 bytes takes the sparse form).  1.1: the rule works with the storage's expected number of items; one chain per run was up to 2.1."""
+    X, dY = wl.normal(T + 21, (T, N), 1.0, "bf16"), wl.normal(T + 22, (T, M), 1.0, "bf16")
+    keep = wl.bernoulli_keep_mask(T + 23, M // R, N, 1.0 / rate)
+    p = bsp.bsp_pack(torch.zeros(M, N, dtype=torch.bfloat16, device="cuda"), R, torch.from_numpy(keep).cuda(), 32)
+    Xd = dev(X, "bf16")
+    X8 = torch.cat([Xd.new_zeros(4), Xd.flatten()])[4:].view_as(Xd)
+    assert X8.data_ptr() % 16 == 8 and Xd.data_ptr() % 16 == 0
+    some = list(range(0, M // R, max(1, M // R // 8)))
+    rows = np.concatenate([np.arange(b * R, (b + 1) * R) for b in some])
+    p_some = orc.pack(np.zeros((len(rows), N), np.float32), R, keep[some], 32, orc.BF16)
+    exact = orc.linear_dvals(X, dY[:, rows], p_some, n_threads=16)[1]
+    ptr = host(p.blk_ptr).astype(int)
+    off = []
+    for x in (Xd, X8):
+        D = bsp.bsp_linear_dvals(x, dev(dY, "bf16"), p, out_dtype=torch.float32).double().cpu().numpy()
+        D = np.concatenate([D[R * ptr[b]:R * ptr[b + 1]] for b in some])
+        off.append(np.linalg.norm(D - exact) / np.linalg.norm(exact))
+    assert off[0] <= 1.1 * off[1], off
+
+
 def test_config4_bert_large_layer_set_dvals():
     """The weight gradient of every BERT-large matrix at the benchmark's size (8192 tokens, 5x), every kept position."""
     for i, d in enumerate(wl.config4(R=16)):
