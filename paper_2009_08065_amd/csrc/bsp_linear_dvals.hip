@@ -536,7 +536,6 @@ struct DvLayout {
     int64_t max_items, max_units;
     int32_t tables;          // entries of a row-block's column table
     int64_t expected_strips;  // with the kept columns spread evenly over row-blocks and columns
-    int64_t least_strips;     // with as many columns in an item as it holds
     double expected_groups;   // of an item
     size_t items_at, groups_at, perm_at, slotcol_at, colstart_at, partial_at, total;
 };
@@ -553,8 +552,6 @@ DvLayout dv_layout(int64_t M, int64_t N, int32_t R, int64_t capacity_cols) {
     const double cols = (double)capacity_cols / (double)runs;
     const int64_t cut = (int64_t)(cols / kDvItemCols) + 1;
     L.expected_strips = ((R + 15) / 16 * runs * cut + kDvStrip - 1) / kDvStrip;
-    L.least_strips = ((R + 15) / 16 * (capacity_cols / kDvItemCols) + kDvStrip - 1) / kDvStrip;
-    if (L.least_strips < 1) L.least_strips = 1;
     L.expected_groups = cols / (double)cut / 16.0 + 1.0 < (double)kDvGroups ? cols / (double)cut / 16.0 + 1.0 : (double)kDvGroups;
     L.colstart_at = L.slotcol_at + (size_t)L.max_items * kDvItemCols * sizeof(uint16_t);
     L.partial_at = (L.colstart_at + (size_t)(M / R) * (size_t)L.tables * sizeof(int32_t) + 255) / 256 * 256;
@@ -571,6 +568,27 @@ bool dvals_dense_pays(double dense_us, int64_t tpu, int64_t S, const DvLayout &L
     const double rounds = (double)((units + kDvUnits - 1) / kDvUnits);
     const double bytes = (double)units * (double)kDvStrip * L.expected_groups * 1024.0 * (R % 16 == 8 && R < 16 ? 0.5 : 1.0);
     return dense_us < 10.9 + 1.207 * (double)tpu * rounds + 0.451e-6 * bytes;
+}
+
+// What the sparse form's sums of this call may be off (dvals_sums_error): how many tokens a chain of it has follows from its strips, and
+// these from how the kept columns fall into items.  The least of three ways: the same number in every row-block and range, to two
+// standard deviations of an independent choice, and numbers of all sizes, whose last items are half full.
+int64_t dv_sums_error(int64_t M, int64_t N, int32_t R, int32_t k_align, int64_t capacity_cols, int ntiles) {
+    const int64_t ranges = (N + kDvRange - 1) / kDvRange, runs = M / R * ranges;
+    const double width = (double)N / (double)ranges, pads = 0.5 * (double)(k_align - 1) / (double)ranges;
+    double k = (double)capacity_cols / (double)runs - pads;
+    k = k < 1.0 ? 1.0 : (k > width ? width : k);
+    const double spread = 2.0 * __builtin_sqrt(k * (1.0 - k / width)), full = (double)kDvItemCols;
+    const double few = __builtin_fmax(__builtin_ceil((k - spread) / full), 1.0), many = __builtin_ceil(__builtin_fmin(k + spread, width) / full);
+    const double mixed = __builtin_fmax(k / full + 0.5, 1.0);
+    int64_t least = INT64_MAX;
+    for (const double items : {few, many, mixed}) {
+        int tpu, S;
+        dv_ranges((int64_t)__builtin_ceil((double)((R + 15) / 16 * runs) * items / (double)kDvStrip), ntiles, tpu, S);
+        const int64_t e = dvals_sums_error(tpu, S);
+        if (e < least) least = e;
+    }
+    return least;
 }
 
 template <typename K>
@@ -654,12 +672,10 @@ extern "C" int bsp_linear_dvals(const void *X, const void *dY, int xdt, int64_t 
                                                                           (int32_t)lg, L.tables, colstart);
         if (fast) {
             if (N % 8 == 0 && aligned(X, 16)) {
-                int tpu, S, tpu_least, S_least;
+                int tpu, S;
                 dv_ranges(L.expected_strips, (int)ntiles, tpu, S);
-                dv_ranges(L.least_strips, (int)ntiles, tpu_least, S_least);
                 // A result in 16 bits does not show where its fp32 sum was rounded on the way (3e-7 beside 1.7e-4 or more).
-                const int64_t e = dvals_sums_error(tpu, S), e_least = dvals_sums_error(tpu_least, S_least);
-                const int64_t error = gdt != BSP_F32 ? INT64_MAX : (e < e_least ? e : e_least);
+                const int64_t error = gdt != BSP_F32 ? INT64_MAX : dv_sums_error(M, N, R, k_align, capacity_cols, (int)ntiles);
                 const DvalsDenseChoice c = dvals_dense_choose(T, M, N, R, capacity_cols, (int64_t)((L.total - L.partial_at) / sizeof(float)), error);
                 if (c.shape >= 0 && dvals_dense_pays(c.us, tpu, S, L, R))
                     return launch_dvals_dense(DvalsDense{(const uint16_t *)X, (const uint16_t *)dY, xdt, T, M, N, R, blk_cnt, blk_ptr, col_idx,

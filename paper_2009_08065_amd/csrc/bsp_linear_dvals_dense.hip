@@ -407,8 +407,9 @@ int64_t sums_chain(int64_t per, int64_t runs, int64_t error) {
 }  // namespace
 
 // Which tile and how many runs of the tokens: the least estimated time of those whose sums are near enough, microseconds fitted to 17800
-// launches of 605 calls of 256 to 4096 rows and columns, 16 to 16384 tokens, 1.43x to 8x (4 to 7 % off on average; on 712
-// other calls the choice, the sparse form among it, costs 1.0 % against the fastest of all that was measured, more than 10 % in 2 % of them).  A
+// launches of 605 calls of 256 to 4096 rows and columns, 16 to 16384 tokens, 1.43x to 8x (4 to 7 % off on average; on 400
+// other calls, on operands in the caches and on fresh ones, the choice, the sparse form among it, costs 1.0 % against the fastest of all that was
+// measured, more than 10 % in 2.8 % of them, 1.27 times at worst).  A
 // workgroup of the largest tile fills a compute unit; of the others two and three share one; a stage takes longer the more of the chip
 // is busy.  The largest tile has no registers for totals, so for fp32 results it is taken where its runs are as short as the sparse form's, at
 // low rates.  What the chains cost: fp32 results of 150 drawn calls take 1.045 of the time of one chain per run, 0.44 of the sparse form's alone.
@@ -417,7 +418,7 @@ DvalsDenseChoice dvals_dense_choose(int64_t T, int64_t M, int64_t N, int32_t R, 
         int bm, bn;
         double fixed, alone, full, shared, end, flush;  // a stage of a workgroup alone on its compute unit, more of it the fuller the chip
                                                         // is, per workgroup of several; a workgroup's end; its sums to the totals
-    } shapes[] = {{256, 256, 5.4, 0.445, 0.079, 0.524, 3.8, 0.0}, {128, 128, 5.5, 0.200, 0.056, 0.176, 1.41, 0.285}, {64, 128, 4.5, 0.179, 0.030, 0.124, 0.77, 0.069}};
+    } shapes[] = {{256, 256, 5.4, 0.445, 0.079, 0.524, 3.8, 0.0}, {128, 128, 5.5, 0.200, 0.056, 0.176, 1.41, 0.285}, {64, 128, 4.5, 0.179, 0.030, 0.135, 0.77, 0.069}};
     const int64_t stages = (T + kDdTok - 1) / kDdTok, stride = ((int64_t)R * capacity_cols + 3) / 4 * 4;
     DvalsDenseChoice best = {-1, 0, 0, 0, 0.0};
     for (int i = 0; i < 3; ++i) {
@@ -433,7 +434,7 @@ DvalsDenseChoice dvals_dense_choose(int64_t T, int64_t M, int64_t N, int32_t R, 
             if (best.shape >= 0 && us >= best.us) continue;
             const int64_t chain = sums_chain(per, S, error);
             if (chain < 1 || (i == 0 && chain < per)) continue;
-            us += shapes[i].flush * (double)per / (double)chain * rounds;
+            if (chain < per) us += shapes[i].flush * (double)per / (double)chain * rounds;
             if (best.shape < 0 || us < best.us) best = {i, (int)S, (int)per, (int)chain, us};
         }
     }
