@@ -4,6 +4,7 @@ Bars: bit-exact for sums of squares, norms, reweighting factors, gradients, mask
 compact storage; for Y, |y - y_oracle| <= tol * (|y_oracle| + rms(y_oracle)) with tol = 2e-2
 for bf16 / fp16 and 1e-5 for fp32."""
 import ctypes
+import warnings
 
 import numpy as np
 import pytest
@@ -1201,15 +1202,50 @@ def test_linear_dvals_small_shapes(dtype, R, T, M, N, p_keep, k_align):
         run_dvals(d["X"], dY, d["W"], R, keep, k_align, dtype, gdt="f32")   # the sums themselves, unrounded
 
 
-@pytest.mark.parametrize("dtype,gdt,R,T,M,N,rate,k_align", [
-    ("bf16", "f32", 16, 4098, 1040, 4104, 2.0, 32),      # the largest tile, runs of the tokens
-    ("f16", "f16", 8, 3001, 2312, 1288, 1.3, 8), ("bf16", "f32", 40, 2049, 2320, 1032, 2.0, 1),     # 128 x 128, one run
-    ("bf16", "bf16", 8, 1003, 520, 392, 2.0, 16), ("f16", "f32", 56, 1001, 560, 136, 3.0, 64),      # 64 x 128, runs
-    ("f16", "f16", 24, 515, 1032, 1032, 2.0, 32), ("bf16", "f32", 64, 33, 64, 8, 1.5, 64),          # 64 x 128, one run
-    ("bf16", "bf16", 8, 1, 8, 16, 2.0, 8), ("f16", "f32", 48, 64, 96, 256, 1.2, 32)])               # one tile, whole stages
-def test_linear_dvals_dense_tiles(dtype, gdt, R, T, M, N, rate, k_align):
+def kernels_of(call):
+    """What call() returns and the names of the kernels that it launched, as far as the profiler has seen them (it loses one now and then:
+    what may be asked of them is that none is another than expected)."""
+    with warnings.catch_warnings():
+        warnings.simplefilter("ignore")
+        with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as p:
+            result = call()
+            torch.cuda.synchronize()
+    return result, [e.name for e in p.events() if "_kernel" in e.name]
+
+
+def check_dvals_rows(D, p, some, X, dY, p_some, R, gdt, like=False):
+    """The panels of the row-blocks `some` of D against the oracle, pad slots +0."""
+    ptr, cnt, at = host(p.blk_ptr).astype(int), host(p.blk_cnt).astype(int), p_some["blk_ptr"]
+    rows = np.concatenate([np.arange(b * R, (b + 1) * R) for b in some])
+    ref, _ = orc.linear_dvals(X, dY[:, rows], p_some, gdt=CODE[gdt], n_threads=16)
+    got = np.concatenate([D[R * ptr[b]:R * ptr[b + 1]] for b in some])
+    if like:
+        _assert_like(got, ref, gdt)
+    else:
+        assert_y_close(got, ref, gdt)
+    for i, b in enumerate(some):
+        panel = got[R * at[i]:R * at[i + 1]].reshape(R, -1)
+        assert bits_equal(np.ascontiguousarray(panel[:, cnt[b]:]), np.zeros((R, panel.shape[1] - cnt[b]), np.float32))
+
+
+# the tile's template arguments: blocks of 32 rows and columns of a wavefront, wavefronts, a second set of sums or not
+BIG, MID, MID_TOTALS = ", 4, 2, 2, 4, false>", ", 2, 2, 2, 2, false>", ", 2, 2, 2, 2, true>"
+SMALL, SMALL_TOTALS = ", 1, 2, 2, 2, false>", ", 1, 2, 2, 2, true>"
+
+
+@pytest.mark.parametrize("dtype,gdt,R,T,M,N,rate,k_align,tile,runs", [
+    ("bf16", "f32", 16, 4098, 4112, 1032, 1.43, 32, BIG, True), ("f16", "f16", 16, 4098, 1040, 4104, 2.0, 32, BIG, True),
+    ("bf16", "f32", 32, 2049, 4128, 2056, 1.3, 32, BIG, False),
+    ("f16", "f16", 8, 3001, 2312, 1288, 1.3, 8, MID, False), ("bf16", "f32", 40, 2049, 2320, 1032, 2.0, 1, MID_TOTALS, False),
+    ("bf16", "f32", 16, 4098, 1040, 4104, 2.0, 32, MID_TOTALS, False), ("f16", "f32", 8, 2500, 4104, 1032, 1.3, 32, MID, False),
+    ("bf16", "bf16", 8, 1003, 520, 392, 2.0, 16, SMALL, True), ("f16", "f32", 56, 1001, 560, 136, 3.0, 64, SMALL, True),
+    ("f16", "f16", 24, 515, 1032, 1032, 2.0, 32, SMALL, False), ("bf16", "f32", 64, 33, 64, 8, 1.5, 64, SMALL_TOTALS, False),
+    ("bf16", "f32", 16, 2001, 2064, 1032, 2.0, 32, SMALL_TOTALS, False),
+    ("bf16", "bf16", 8, 1, 8, 16, 2.0, 8, SMALL, False), ("f16", "f32", 48, 64, 96, 256, 1.2, 32, SMALL_TOTALS, False)])
+def test_linear_dvals_dense_tiles(dtype, gdt, R, T, M, N, rate, k_align, tile, runs):
     """The dense form at its tiles' edges: rows, columns and tokens past the last tile, row-blocks across tiles, an empty and a full
-    row-block, pads, one run and several, one token with an infinity (the batch's last, which a ragged stage reads again)."""
+    row-block, pads, one run and several, one chain per run and several, one token with an infinity (the batch's last, which a ragged
+    stage reads again), a result at an address of its type.  That it is this tile that runs is part of the test."""
     d = wl.layer(R * 1000 + T + 13, T, M, N, dtype)
     dY = wl.normal(R * 83 + T, (T, M), 1.0, dtype)
     B = M // R
@@ -1219,23 +1255,57 @@ def test_linear_dvals_dense_tiles(dtype, gdt, R, T, M, N, rate, k_align):
         keep[B // 2, :] = 0
     p = bsp.bsp_pack(dev(d["W"], dtype), R, torch.from_numpy(keep).cuda(), k_align)
     some = sorted({0, B // 2, B - 1, B // 3, 128 // R, 256 // R} & set(range(B)))     # the oracle's row-blocks
-    rows = np.concatenate([np.arange(b * R, (b + 1) * R) for b in some])
-    p_some = orc.pack(d["W"][rows], R, keep[some], k_align, CODE[dtype])
-    ptr, cnt, at = host(p.blk_ptr).astype(int), host(p.blk_cnt).astype(int), p_some["blk_ptr"]
+    p_some = orc.pack(d["W"][np.concatenate([np.arange(b * R, (b + 1) * R) for b in some])], R, keep[some], k_align, CODE[dtype])
+    dYd = dev(dY, dtype)
     for spoil in (False, True):
         X = d["X"].copy()
         if spoil:
             X[T - 1, N // 2] = np.inf
-        D = host(bsp.bsp_linear_dvals(dev(X, dtype), dev(dY, dtype), p, out_dtype=TDT[gdt]))
-        ref, _ = orc.linear_dvals(X, dY[:, rows], p_some, gdt=CODE[gdt], n_threads=16)
-        got = np.concatenate([D[R * ptr[b]:R * ptr[b + 1]] for b in some])
+        Xd = dev(X, dtype)
+        D, names = kernels_of(lambda: bsp.bsp_linear_dvals(Xd, dYd, p, out_dtype=TDT[gdt]))
+        assert not any("dvals_partial" in n or "dvals_reduce" in n or "dvals_plain" in n for n in names), names
+        assert all(tile in n for n in names if "dvals_dense_kernel" in n), names
+        assert runs or not any("dvals_sum" in n for n in names), names
+        check_dvals_rows(host(D), p, some, X, dY, p_some, R, gdt, like=spoil)
+    odd = torch.zeros(R * p.total_cols + 1, dtype=TDT[gdt], device="cuda")[1:]
+    assert odd.data_ptr() % 16 == odd.element_size()
+    bsp.bsp_linear_dvals(Xd, dYd, p, D=odd)
+    assert bits_equal(host(odd), host(D))
+
+
+@pytest.mark.parametrize("dtype,gdt,R,rate,T,M,N,k_align", [
+    ("bf16", "f32", 16, 8.0, 7529, 2688, 896, 32), ("f16", "f32", 16, 8.0, 6260, 3584, 896, 32),     # where the rule takes this form
+    ("bf16", "f32", 16, 5.0, 8117, 896, 3584, 32), ("f16", "f32", 16, 5.0, 8192, 4096, 1024, 8),     # four column ranges; whole tiles
+    ("bf16", "f32", 8, 3.0, 2065, 2056, 1000, 16), ("f16", "f32", 24, 2.0, 1500, 1032, 1096, 1),     # half a slab in each row-block; two ranges
+    ("bf16", "bf16", 32, 1.5, 1090, 2048, 2056, 32), ("f16", "f32", 64, 4.0, 3000, 1024, 520, 64)])
+def test_linear_dvals_sparse_form(dtype, gdt, R, rate, T, M, N, k_align):
+    """The sparse form with many token tiles to a run, so that its ring of pieces goes round: one to four column ranges, half slabs, an
+    empty and a full row-block, a ragged last tile, one token with an infinity.  X at an address of 8 bytes takes it whatever the
+    sizes; where the rule on the sizes takes it too (marked), that is part of the test."""
+    rule = rate >= 5.0
+    X, W, dY = wl.normal(T + 1, (T, N), 1.0, dtype), wl.normal(T + 2, (M, N), 0.02, dtype), wl.normal(T + 3, (T, M), 1.0, dtype)
+    B = M // R
+    keep = wl.bernoulli_keep_mask(T + N + 7, B, N, 1.0 / rate)
+    keep[1, :], keep[B // 2, :] = 1, 0
+    p = bsp.bsp_pack(dev(W, dtype), R, torch.from_numpy(keep).cuda(), k_align)
+    some = sorted({0, 1, B // 3, B // 2, B - 1})
+    p_some = orc.pack(W[np.concatenate([np.arange(b * R, (b + 1) * R) for b in some])], R, keep[some], k_align, CODE[dtype])
+    dYd = dev(dY, dtype)
+    for spoil in (False, True):
         if spoil:
-            _assert_like(got, ref, gdt)
+            X[T - 1, N // 2] = np.inf
+        Xd = dev(X, dtype)
+        X8 = torch.cat([Xd.new_zeros(4), Xd.flatten()])[4:].view_as(Xd)
+        assert X8.data_ptr() % 16 == 8
+        D, names = kernels_of(lambda: bsp.bsp_linear_dvals(X8, dYd, p, out_dtype=TDT[gdt]))
+        assert not any("dvals_dense" in n or "dvals_sum" in n or "dvals_plain" in n for n in names), names
+        check_dvals_rows(host(D), p, some, X, dY, p_some, R, gdt, like=spoil)
+        D16, names = kernels_of(lambda: bsp.bsp_linear_dvals(Xd, dYd, p, out_dtype=TDT[gdt]))
+        if rule:
+            assert not any("dvals_dense" in n or "dvals_sum" in n for n in names), names
+            assert torch.equal(torch.nan_to_num(D16), torch.nan_to_num(D))
         else:
-            assert_y_close(got, ref, gdt)
-        for i, b in enumerate(some):                     # pad slots
-            panel = got[R * at[i]:R * at[i + 1]].reshape(R, -1)
-            assert bits_equal(np.ascontiguousarray(panel[:, cnt[b]:]), np.zeros((R, panel.shape[1] - cnt[b]), np.float32))
+            check_dvals_rows(host(D16), p, some, X, dY, p_some, R, gdt, like=spoil)
 
 
 def test_linear_dvals_seeded_random_shapes():
