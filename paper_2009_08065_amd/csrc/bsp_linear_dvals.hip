@@ -559,15 +559,13 @@ DvLayout dv_layout(int64_t M, int64_t N, int32_t R, int64_t capacity_cols) {
     return L;
 }
 
-// Whether the dense form (bsp_linear_dvals_dense.hip) is the faster one: against microseconds fitted to 605 calls of 256 to 4096 rows and
-// columns, 16 to 16384 tokens at 1.43x to 8x (7 % off on average).  Sparse / dense, whole calls in us: 4096 x 1024, R = 16 at 5x, 8192 tokens
-// 58.2 / 64.8, 4096 tokens 39.0 / 38.6; at 8x, 6000 tokens 41.6 / 49.6; 1024 x 1024 at 5x, 8192 tokens 31.7 / 25.8.  Near the line the wrong
-// one is taken now and then: at 5x, 6000 tokens 47.3 / 52.0 (dense).
+// Whether the dense form (bsp_linear_dvals_dense.hip) is the faster one: against microseconds fitted to 400 calls of 256 to 4096 rows and
+// columns, 64 to 8192 tokens at 1.43x to 5x, on operands in the caches and on fresh ones (6 % off on average).
 bool dvals_dense_pays(double dense_us, int64_t tpu, int64_t S, const DvLayout &L, int32_t R) {
     const int64_t units = L.expected_strips * S;
     const double rounds = (double)((units + kDvUnits - 1) / kDvUnits);
     const double bytes = (double)units * (double)kDvStrip * L.expected_groups * 1024.0 * (R % 16 == 8 && R < 16 ? 0.5 : 1.0);
-    return dense_us < 10.9 + 1.207 * (double)tpu * rounds + 0.451e-6 * bytes;
+    return dense_us < 10.6 + 1.39 * (double)tpu * rounds + 0.393e-6 * bytes;
 }
 
 // What the sparse form's sums of this call may be off (dvals_sums_error): how many tokens a chain of it has follows from its strips, and

@@ -20,19 +20,9 @@
 namespace bsp {
 namespace {
 
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-
 constexpr int kDdTok = 32;      // tokens of a stage
 constexpr int kDdStages = 4;    // stages in LDS
 constexpr int kDdPassPitch = 4; // floats that a row of the output tile is longer than its columns
-
-template <int DT>
-__device__ __forceinline__ f32x16 mfma32(uint4 a, uint4 b, f32x16 c) {
-    if constexpr (DT == BSP_BF16)
-        return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
-    else
-        return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
-}
 
 // What is exclusive-ored onto the column's byte offset in a token's row of PITCH bytes: four tokens' pieces of 64 bytes (what
 // half a transposing read takes) lie in 256 different bytes of the banks.
@@ -42,7 +32,7 @@ __device__ __forceinline__ uint32_t dd_turn(uint32_t token) {
 }
 
 // 64 lanes' 16 bytes at base + at to LDS at lds .. lds + 1023.  (Written out: for the builtin the compiler would wait for all such
-// loads before any LDS read.)
+// loads before any LDS read.  m0 is a reserved register, which can't be named as clobbered; nothing else in these kernels uses it.)
 __device__ __forceinline__ void load_to_lds(uint32_t lds, const uint8_t *base, uint32_t at) {
     asm volatile("s_mov_b32 m0, %0\n s_nop 0\n global_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(at), "s"(base));
 }
@@ -408,17 +398,20 @@ int64_t sums_chain(int64_t per, int64_t runs, int64_t error) {
 
 // Which tile and how many runs of the tokens: the least estimated time of those whose sums are near enough, microseconds fitted to 17800
 // launches of 605 calls of 256 to 4096 rows and columns, 16 to 16384 tokens, 1.43x to 8x (4 to 7 % off on average; on 400
-// other calls, on operands in the caches and on fresh ones, the choice, the sparse form among it, costs 1.0 % against the fastest of all that was
-// measured, more than 10 % in 2.8 % of them, 1.27 times at worst).  A
+// other calls, on operands in the caches and on fresh ones, the choice, the sparse form among it, costs 0.9 % against the fastest of all that was
+// measured, more than 10 % in 2.3 % of them, 1.23 times at worst).  A
 // workgroup of the largest tile fills a compute unit; of the others two and three share one; a stage takes longer the more of the chip
 // is busy.  The largest tile has no registers for totals, so for fp32 results it is taken where its runs are as short as the sparse form's, at
 // low rates.  What the chains cost: fp32 results of 150 drawn calls take 1.045 of the time of one chain per run, 0.44 of the sparse form's alone.
 DvalsDenseChoice dvals_dense_choose(int64_t T, int64_t M, int64_t N, int32_t R, int64_t capacity_cols, int64_t partial_floats, int64_t error) {
     constexpr struct {
         int bm, bn;
-        double fixed, alone, full, shared, end, flush;  // a stage of a workgroup alone on its compute unit, more of it the fuller the chip
-                                                        // is, per workgroup of several; a workgroup's end; its sums to the totals
-    } shapes[] = {{256, 256, 5.4, 0.445, 0.079, 0.524, 3.8, 0.0}, {128, 128, 5.5, 0.200, 0.056, 0.176, 1.41, 0.285}, {64, 128, 4.5, 0.179, 0.030, 0.135, 0.77, 0.069}};
+        double fixed, alone, full, shared, end, flush, sums;  // a stage of a workgroup alone on its compute unit, more of it the fuller the
+                                                              // chip is, per workgroup of several; a workgroup's end; its sums to
+                                                              // the totals; a million sums of a run
+    } shapes[] = {{256, 256, 5.4, 0.440, 0.220, 0.550, 3.8, 0.0, 0.9},
+                  {128, 128, 5.5, 0.200, 0.056, 0.176, 1.41, 0.285, 1.37},
+                  {64, 128, 4.5, 0.179, 0.030, 0.135, 0.77, 0.069, 1.37}};
     const int64_t stages = (T + kDdTok - 1) / kDdTok, stride = ((int64_t)R * capacity_cols + 3) / 4 * 4;
     DvalsDenseChoice best = {-1, 0, 0, 0, 0.0};
     for (int i = 0; i < 3; ++i) {
@@ -428,9 +421,11 @@ DvalsDenseChoice dvals_dense_choose(int64_t T, int64_t M, int64_t N, int32_t R, 
             const int64_t per = (stages + S - 1) / S;
             if ((stages + per - 1) / per != S) continue;  // (runs without a stage)
             const double count = (double)(tiles * S) / 256.0, rounds = __builtin_ceil(count);  // workgroups per compute unit
-            const double stage = __builtin_fmax(shapes[i].alone + shapes[i].full * __builtin_fmin(count, 1.0), shapes[i].shared * rounds);
+            // (the largest tile's stage takes 0.44 us on up to half of the compute units, 0.60 on seven eighths, 0.66 on all: the clocks)
+            const double fill = __builtin_fmin(count, 1.0), slower = i == 0 ? fill * fill * fill : fill;
+            const double stage = __builtin_fmax(shapes[i].alone + shapes[i].full * slower, shapes[i].shared * rounds);
             double us = shapes[i].fixed + stage * (double)per + shapes[i].end * rounds;
-            if (S > 1) us += 1.0 + 0.25 * (double)S + 1.37e-6 * (double)(S + 1) * (double)stride;
+            if (S > 1) us += 1.0 + 0.25 * (double)S + 1e-6 * shapes[i].sums * (double)(S + 1) * (double)stride;
             if (best.shape >= 0 && us >= best.us) continue;
             const int64_t chain = sums_chain(per, S, error);
             if (chain < 1 || (i == 0 && chain < per)) continue;

@@ -28,8 +28,6 @@
 namespace bsp {
 namespace {
 
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-
 constexpr int kThreadsX = 256;  // of the expansions
 constexpr int kRing = 4;       // stages of U in LDS
 constexpr int kStageK = 64;    // rows of the matrix per stage
@@ -37,16 +35,6 @@ constexpr int kRowBytes = 2 * kStageK;
 constexpr int kColPad = 256;   // columns of the expanded matrix are padded to whole workgroup tiles
 constexpr uint32_t kRangeGroup = 4;
 constexpr int kFrag = 1024;    // bytes of an operand of v_mfma_f32_32x32x16: 32 columns x 16 rows
-
-template <int DT>
-__device__ __forceinline__ f32x16 mfma32(uint4 a, uint4 b, f32x16 c) {
-    if constexpr (DT == BSP_BF16)
-        return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c,
-                                                       0, 0, 0);
-    else
-        return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0,
-                                                      0, 0);
-}
 
 // Bit n of row b of `kept`: row-block b keeps column n; rows are whole groups of kColPad columns.  (The workgroup of 256
 // columns whose thread t holds column t's place, of the row-block's first slab.)
