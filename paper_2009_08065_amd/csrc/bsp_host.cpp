@@ -108,16 +108,25 @@ PyObject *other_number(PyObject *o, const char *scalar) {
     return n;
 }
 
+// The number that stands in another's place, which may name one in turn (without end, if it names itself).  Takes the reference.
+template <typename T>
+bool read_instead(PyObject *n, bool (*read_number)(PyObject *, T &), T &out) {
+    bool ok = Py_EnterRecursiveCall(" while processing _as_parameter_") == 0;
+    if (ok) {
+        ok = read_number(n, out);
+        Py_LeaveRecursiveCall();
+    }
+    Py_DECREF(n);
+    return ok;
+}
+
 // Whole numbers: everything with __index__ (numpy's, a tensor of one).  Of one larger than the type the low bits.
 template <typename T>
 bool read_whole(PyObject *o, T &out) {
     PyObject *n = PyNumber_Index(o);
     if (!n) {
         n = other_number(o, std::is_unsigned_v<T> ? "c_ulong" : (sizeof(T) == 8 ? "c_long" : "c_int"));
-        if (!n) return false;
-        const bool ok = read_whole(n, out);
-        Py_DECREF(n);
-        return ok;
+        return n && read_instead(n, read_whole<T>, out);
     }
     out = static_cast<T>(PyLong_AsUnsignedLongLongMask(n));
     Py_DECREF(n);
@@ -128,10 +137,7 @@ bool read_real(PyObject *o, float &out) {
     const double v = PyFloat_AsDouble(o);
     if (v == -1.0 && PyErr_Occurred()) {
         PyObject *n = other_number(o, "c_float");
-        if (!n) return false;
-        const bool ok = read_real(n, out);
-        Py_DECREF(n);
-        return ok;
+        return n && read_instead(n, read_real, out);
     }
     out = static_cast<float>(v);
     return true;

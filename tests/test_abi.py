@@ -214,6 +214,18 @@ def test_native_functions_take_the_numbers_that_ctypes_takes():
             plain.bsp_prune_mask(None, 4, 4, t, -1, 0, None, None, None, 0, 0)
 
 
+def test_a_number_that_stands_for_itself_is_refused():
+    """An object that names itself as its _as_parameter_ ends as with ctypes, in a RecursionError and not on the stack."""
+    a, i = _Elsewhere(), _Elsewhere(torch.int32)
+    me = _Named(None)
+    me._as_parameter_ = me
+    for whole, real in ((me, 0.5), (64, me)):
+        with pytest.raises(RecursionError):
+            bsp.bsp._native().bsp_prune_mask(a, whole, 64, real, -1, 0, i, None, None, 0, 0)
+    with pytest.raises(RecursionError):
+        C.c_int64.from_param(me)
+
+
 def test_results_are_allocated_without_the_interpreter_lock():
     """While a result is allocated other Python threads run: an allocation that takes long (here for its filling, on a GPU for hipMalloc
     or the cache's flush) does not hold them."""
