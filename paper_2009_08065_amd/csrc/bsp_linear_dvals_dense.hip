@@ -359,10 +359,12 @@ template <int DT, int ODT, int FM, int FN, int WR, int WC, bool TOTALS>
 int launch_dense(const DvalsDense &a, int S, int per, int chain) {
     using G = DdShape<DT, FM, FN, WR, WC>;
     auto k = dvals_dense_kernel<DT, ODT, FM, FN, WR, WC, TOTALS>;
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)G::kLds);
-    if (e != hipSuccess) {  // (asking again is harmless)
-        set_last_hip_error((int)e);
-        return BSP_ERR_HIP;
+    if constexpr (G::kLds > 65536) {  // (asking again is harmless)
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)G::kLds);
+        if (e != hipSuccess) {
+            set_last_hip_error((int)e);
+            return BSP_ERR_HIP;
+        }
     }
     const int64_t tiles = ((a.M + G::BM - 1) / G::BM) * ((a.N + G::BN - 1) / G::BN), wgs = (tiles * S + 7) / 8 * 8;
     if (wgs >= ((int64_t)1 << 31)) return BSP_ERR_SHAPE;
