@@ -279,8 +279,9 @@ __host__ __device__ __forceinline__ void dv_ranges(int64_t strips, int ntiles, i
 // buffers in LDS, one workgroup barrier per tile: while tile i is multiplied out of one buffer, the copying
 // wavefronts write tile i + 1 into the other (every wavefront finished reading it before the barrier that ended
 // tile i - 1), piece by piece as it arrives, and ask for the same piece of tile i + 2 at once.
-// 4096 x 1024, 8192 tokens, R = 16, 5x: 51.6 us, 1.3 us a tile (67 and 2.7 when a tile was written whole before the next
-// was asked for); R = 32 at 1.43x, 4099 tokens 66 us (91).  LDS is busy for three quarters of a tile; 20 us are the
+// 4096 x 1024, 8192 tokens, R = 16, 5x: 51.6 us on operands in the caches, 58 on fresh ones, 1.3 us a tile (67 and 2.7 when a
+// tile was written whole before the next was asked for); R = 32 at 1.43x, 4099 tokens 66 us (91).  LDS is busy for 41 % of the
+// launch's clocks (35 % of that bank conflicts), which is three quarters of the 31 us that its 24 tiles take; the rest are the
 // launch's chain of dependent loads and the 41 MB of partial sums at its end.
 template <int DT>
 __global__ __launch_bounds__(kDvThreads) void dvals_partial_kernel(const uint16_t *__restrict__ X,

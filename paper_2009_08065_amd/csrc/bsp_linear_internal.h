@@ -189,11 +189,11 @@ inline int64_t steploop_groups(int64_t tiles, int64_t NG, int64_t N, double step
     return best;
 }
 // The kernel that streams X: how many of a group's eight streams a workgroup takes, one per computing wavefront.  With
-// fewer of them a wavefront's steps come sooner (0.82 and 0.76 of the time with 4 and 2), so a launch that fits one round
-// of 256 workgroups that way is shorter; a second round costs more than that.  Measured with 8 / 4 / 2, us: 1024 x 4096 at
-// 5x, 2048 tokens 27.7 / 21.9 / 20.5, 4096 tokens 28.6 / 23.6 / 39 (2 rounds), 8192 tokens 32 / 46 / 83; at 1.43x, 4096
-// tokens 55.6 / 47.0 / 83; 2048 x 1536 at 3x, 1024 tokens 16.7 / 12.2 / 11.1; 768 x 768 in 8-row blocks at 3x, 4099 tokens
-// 15.2 / 12.6 / 23.8.
+// fewer of them a wavefront's steps come sooner, and they are six deep (0.77 and 0.70 of the time with 4 and 2), so a launch
+// that fits one round of 256 workgroups that way is shorter; a second round costs more than that.  Measured with 8 / 4 / 2, us:
+// 1024 x 4096 at 5x, 2048 tokens 24.3 / 18.4 / 17.3, 4096 tokens 24.9 / 20.1 / 32.8 (2 rounds), 8192 tokens 28.8 / 40.6 / 69.6;
+// at 1.43x, 4096 tokens 51.8 / 39.4 / 68.3; 2048 x 1536 at 3x, 1024 tokens 13.5 / 10.2 / 9.7; 768 x 768 in 8-row blocks at 3x,
+// 4099 tokens 11.8 / 9.3 / 15.2.
 inline double stream_load(int64_t tiles, int64_t B, int waves) {
     const int64_t streams = (B + 3) / 4;
     return tile_rounds(tiles, (streams + waves - 1) / waves) * (waves == 8 ? 1.0 : (waves == 4 ? 0.77 : 0.70));

@@ -349,7 +349,9 @@ TiledArgs token_rows(const TiledArgs &a, int64_t first, int64_t count) {
 // True when this layer's call was taken (status in st).  Which kernel and which shape: the one with the least estimated
 // time.  Measured, us (many tokens / this one): 2304 x 768 at 2x, 24 tokens 10.4 / 5.0, 400 tokens 10.9 / 7.6,
 // 1200 tokens 11.7 / 15.3 (stays); 768 x 3072 at 2x, 24 tokens 31 / 6.3, 400 tokens 31 / 12.2, 1537 tokens 34 / 24.3
-// and at 3x 26.7 / 19.2; 1024 x 4096 at 5x, 2048 tokens 26.1 / 23.0, 4099 tokens 29.6 / 60 (stays).
+// and at 3x 26.7 / 19.2; 1024 x 4096 at 5x, 4099 tokens 29.6 / 60 (stays).  Those are from before the streaming kernel's loop of six
+// steps, which is as fast as this one near the border now: 768 x 3072 at 3x, 1537 tokens 17.6 / 17.9 (fresh X 18.9 / 18.8), and the
+// faster one at 5x: 1024 x 4096, 2048 tokens 16.6 / 23.0 (19.9 / 22.3), where the estimates still come here.
 // A batch a little longer than a whole number of token tiles on every XCD costs the kernels for many tokens a round of
 // mostly idle compute units, or the wide split that avoids it: then the tiles that are too many come here and only the others go
 // there, if that is less by the estimates: whole / in two, us, 1024 x 4096 with a residual at 1.43x, 4099 tokens 57.0 / 52.7, at 2x,

@@ -6,7 +6,8 @@
 // accumulators of four consecutive row-blocks (128 bytes of a token's output row) across all column chunks and
 // walks, chunk by chunk, the steps of its blocks inside the chunk -- the step loop of the kernel for narrow layers
 // (assembly: operand ring of four steps, hand-counted waits, X fragments of the next step requested between the
-// matrix instructions of this one), once per accumulator set.  Eight more wavefronts do nothing but copy X: while
+// matrix instructions of this one; with 4 and 2 computing wavefronts a ring of six steps and X fragments two steps ahead),
+// once per accumulator set.  Eight more wavefronts do nothing but copy X: while
 // the products of chunk q run out of one half of the 128 KiB tile, they write chunk q + 1 (64 tokens x 512
 // columns, transposed to [column][16 tokens]) into the other half, with the loads of the chunks after it already
 // in flight.  One barrier per chunk hands a filled half over and frees the other one.  Wavefronts that only load
