@@ -204,6 +204,15 @@ inline int stream_waves(int64_t tiles, int64_t B) {
         if (stream_load(tiles, B, w) < stream_load(tiles, B, best)) best = w;
     return best;
 }
+// The kernel on the compact storage: row-blocks of a workgroup's strip.  Enough strips to give every compute unit a workgroup, none of
+// fewer than 4 row-blocks or of more than its part of blk_ptr in LDS has room for.
+constexpr int kMaxStripBlocks = 1024;
+inline int64_t canonical_strip(int64_t ntiles, int64_t B) {
+    int64_t strips = (256 + ntiles - 1) / ntiles;
+    if (strips > (B + 3) / 4) strips = (B + 3) / 4;
+    const int64_t blocks = (B + strips - 1) / strips;
+    return blocks < kMaxStripBlocks ? blocks : kMaxStripBlocks;
+}
 // Steps the planned kernel may read past the last step of the storage (values unused).
 int plan_slack_steps();
 

@@ -595,75 +595,52 @@ int linear_t_expand(const void *U, int udt, int64_t T, int64_t M, int64_t N, int
 
 size_t linear_expand_bytes(int64_t M, int64_t N, int32_t R) { return expanded_bytes(N, M) + kept_bytes(M / R, N); }
 
-// Microseconds of both forms, fitted to 64 to 8192 tokens of 256 to 4096 rows and columns at 1.43x to 5x.  The gather takes
-// a step per 32 kept columns of a row-block and token tile, and its tiles shrink with the layer's width (64 tokens up to
-// 1024 columns, 16 up to 4096); the dense form an expansion, its tiles and the output.  Measured, gather / dense: 1024 x 4096,
-// 8192 tokens, R = 16 at 1.43x 342 / 81, at 5x 115 / 72, 2048 tokens at 5x 41 / 34 (stays), 512 at 5x 19 / 32;
-// 4096 x 1024, 8192 tokens, R = 16 at 1.43x 125 / 107, at 3x 76 / 103, R = 8 at 2x 167 / 104; 3072 x 768, 4096 tokens at 3x
-// 29 / 46.
-// Those leave out what grows with the layer and not with the tokens: the expansion writes the whole matrix, in workgroups
-// of at most 16 rows each, and few token tiles fill few XCDs; and row-blocks of one row, or more than 32.  So a second pair of
-// estimates has to agree, fitted to 2600 calls of 64 x 64 to 30528 x 768 and 16384 x 4096, R = 1 to 64, 1 to 8192 tokens, 1.1x to
-// 10x (the dense one to 15 %, the gather's to a factor of 2).  Of 709 calls that the first pair alone made dense, 39 were slower
-// so: 30528 x 768, R = 8 at 1.1x, one token 20.4 us by the gather and 96.3 dense; 4096 x 1024, R = 1 at 1.43x, 40 tokens 27.6 / 58.7;
-// 16384 x 4096, R = 16 at 1.1x, 40 tokens 115 / 266.
-namespace {
-bool expand_pays_strict(int64_t T, int64_t M, int64_t N, int32_t R, int64_t capacity_cols) {
-    const int64_t npad = (N + 255) / 256 * 256, tok = npad <= 1024 ? 64 : (npad <= 2048 ? 32 : 16);
-    const double steps = (double)capacity_cols / 32.0 * (double)((T + tok - 1) / tok) / 256.0;  // per compute unit
-    const double per_step = (tok == 64 ? 0.040 : (tok == 32 ? 0.035 : 0.030)) * (R <= 16 ? 1.0 : (R <= 32 ? 2.1 : 4.0));
-    double tiles, tiles_xcd;
-    choose_tile(T, N, M, &tiles, &tiles_xcd);
-    const double out = (double)T * (double)M * 1e-6;
-    if (8.0 + tiles + 0.5 * out >= 0.9 * (8.0 + per_step * steps)) return false;
-    const double workgroups = (double)((M + 255) / 256 * 256 / R) * (double)(npad / 256) * (double)((R + 15) / 16);
-    const double dense = 4.0 + 0.72 * tiles + 0.6 * (tiles_xcd - tiles) + 0.0018 * workgroups + 1.4e-6 * (double)M * (double)N + 0.7 * out;
-    constexpr double kStep[3][3] = {{0.050, 0.105, 1.1}, {0.042, 0.085, 0.39}, {0.042, 0.090, 0.35}};  // [width][R to 16, 32, 64]
-    const double gather = 11.0 + kStep[tok == 64 ? 0 : (tok == 32 ? 1 : 2)][R <= 16 ? 0 : (R <= 32 ? 1 : 2)] * steps +
-                          0.07 * (double)(M / R) * (double)((T + tok - 1) / tok) / 256.0;
-    return dense < gather;
-}
-
-// Those rules were made when the smallest tile was 64 x 128, and to be wrong on one side only: of 31600 calls of 64 to 16384
-// rows, 64 to 4096 columns, R = 1 to 64, 1 to 8192 tokens, 1.1x to 10x they lost 18 % of the time on average against the faster
-// form (1024 x 4096, R = 32 at 2x, 914 tokens 64 us by the gather, 32 dense; 896 x 896, R = 8 at 2x, 1752 tokens 26 / 15; 640 x 640,
-// R = 32 at 1.5x, 166 tokens 15.9 / 10.6).  These two estimates, fitted to those calls (the dense one to 8 %, the gather's to
-// 11 to 19 %), add the calls where dense is the shorter by a margin: 13 %, or 25 % for up to 1024 columns and twice as many rows or
-// more, where the gather's is up to 1.4 times too long (3072 x 768 at 1.4x, 476 tokens 14.0 us for 19.7).  With both the loss is 4 %, the mean
-// 0.88 of the time before, and 0.15 % of the calls are slower than by the gather by more than 8 % (up to 1.3x).  A call of two launches and a
-// workspace takes 10 us on the host, so nothing shorter is asked to be dense.  (The dense form rounds its sum once per 16 columns, the gather
-// once per 32 kept ones; the result's 16 bits hide both: against 64 bits 1024 x 4096 at 5x in fp16 2.06919e-4 and 2.06919e-4, the rounding of
-// the result alone 2.06919e-4.)
-bool expand_pays_fitted(int64_t T, int64_t M, int64_t N, int32_t R, int64_t capacity_cols) {
-    if (M > 16384 || T > 8192) return false;  // beyond what the estimates were fitted to
-    const int64_t npad = (N + 255) / 256 * 256, tok = npad <= 1024 ? 64 : (npad <= 2048 ? 32 : 16);
-    const double blocks = (double)(M / R), all = blocks * (double)(N + 31);
+// Whether a layer on its compact storage is the shorter one as an expansion and a dense product: microseconds of both forms, fitted to 59000
+// calls with a bias, each on inputs and results that were in no cache, of 256 to 60000 rows, 64 to 4096 columns, R = 1 to 64, 1 to 65536
+// tokens, 1.1x to 8x; half of them 768 / 3072-like matrices at 1.43x to 5x, a third of the token counts powers of two and their like (the dense
+// one to 4 to 8 % on average, the gather's to 6 to 9, 15 for more than 32 rows).  Measured, gather / dense: 1024 x 4096, R = 16 at
+// 5x, 8192 tokens 125 / 71, 2048 tokens 41.3 / 37.8 (stays); 3072 x 768 at 3x, 8192 tokens 53 / 55, 4096 tokens 31 / 37; 768 x 768 at 3x,
+// 8192 tokens 18.7 / 25.0; 896 x 896, R = 8 at 2x, 1752 tokens 24 / 14.
+// The gather goes in whole rounds: its workgroups, a token tile and a strip of row-blocks each, fill compute units, so 8192 tokens
+// of a narrow layer are one full round and 8200 are two.  An estimate by the mean (and an older one beside it that could say
+// dense by itself) made 9 % of the calls of 8192 tokens more than 8 % slower than by the gather, 0.75 % of all, and beyond 8192 tokens it
+// was asked for nothing, at 1.2 times the time.  Dense has to be the shorter one by 12 %: of 30000 calls that the fit has
+// not seen 0.12 % are slower by more than 8 % (0.3 % at 8192 tokens; 1.26 times at worst), the loss against the faster
+// form is 2 % of the time (6.5 % before), and the mean 0.80 of the gather alone.  A call of two launches and a workspace takes 10 us on the
+// host, so nothing shorter is asked to be dense.  (The dense form rounds its sum once per 16 columns, the gather once per 32 kept ones; the result's
+// 16 bits hide both: against 64 bits 1024 x 4096 at 5x in fp16 2.06919e-4 and 2.06919e-4, the rounding of the result alone 2.06919e-4.)
+bool linear_expand_pays(int64_t T, int64_t M, int64_t N, int32_t R, int64_t capacity_cols) {
+    const int64_t npad = (N + 255) / 256 * 256, tok = npad <= 1024 ? 64 : (npad <= 2048 ? 32 : 16), B = M / R;
+    const double blocks = (double)B, all = blocks * (double)(N + 31);
     const double cols = (double)capacity_cols < all ? (double)capacity_cols : all, out = (double)T * (double)M * 1e-6;
+
     const int few = few_columns(T, M);
-    double product;
-    if (few != 0) {
-        product = 7.37 + (few == 64 ? 0.168 : 0.246) * (double)((N + kStageK - 1) / kStageK);
+    const double workgroups = (double)((M + 255) / 256 * 256 / R) * (double)(npad / 256) * (double)((R + 15) / 16), MN = (double)M * (double)N;
+    const double stages = (double)((N + kStageK - 1) / kStageK);
+    double dense;
+    if (few == 64) {
+        dense = 7.83 + 0.150 * stages + 0.00070 * workgroups + 1.70e-6 * MN + 0.827 * out + 10.0e-6 * cols;
+    } else if (few == 128) {
+        dense = 7.61 + 0.233 * stages + 0.00077 * workgroups + 1.49e-6 * MN + 0.580 * out + 10.0e-6 * cols;
     } else {
         double tiles, tiles_xcd;
         choose_tile(T, N, M, &tiles, &tiles_xcd);
-        product = 3.33 + 0.80 * tiles + (tiles_xcd > tiles ? 0.73 * (tiles_xcd - tiles) : 0.0);
+        const double idle = tiles_xcd > tiles ? tiles_xcd - tiles : 0.0;
+        dense = 2.06 + 1.02 * tiles + 0.760 * idle + 0.00105 * workgroups + 0.956e-6 * MN + 0.460 * out + 12.6e-6 * cols;
     }
-    const double workgroups = (double)((M + 255) / 256 * 256 / R) * (double)(npad / 256) * (double)((R + 15) / 16);
-    const double dense = product + 0.0016 * workgroups + 1.52e-6 * (double)M * (double)N + 0.65 * out;
-    // [width][R to 16, 32, 64]: the call, a step of all compute units, a step of a row-block, 1000 columns, a million outputs
-    constexpr double kGather[3][3][5] = {
-        {{6.38, 0.0484, 0.334, 0.99, 1.20}, {6.30, 0.0594, 0.528, 1.35, 1.06}, {9.37, 0.568, 1.72, 1.04, 2.56}},
-        {{4.85, 0.0348, 0.342, 1.09, 3.24}, {4.28, 0.0570, 0.429, 1.57, 1.23}, {7.56, 0.209, 1.03, 0.36, 3.32}},
-        {{4.58, 0.0320, 0.334, 0.49, 4.11}, {3.91, 0.0567, 0.412, 0.84, 1.60}, {6.45, 0.222, 0.902, 0.03, 0.0}}};
-    const double *k = kGather[tok == 64 ? 0 : (tok == 32 ? 1 : 2)][R <= 16 ? 0 : (R <= 32 ? 1 : 2)];
-    const double gather = k[0] + k[1] * cols / 32.0 * (double)((T + tok - 1) / tok) / 256.0 + k[2] * cols / blocks / 32.0 +
-                          k[3] * 1e-3 * (double)N + k[4] * out;
-    return (dense < 10.0 ? 10.0 : dense) < (tok == 64 && M >= 2 * N ? 0.75 : 0.87) * gather;
-}
-}  // namespace
 
-bool linear_expand_pays(int64_t T, int64_t M, int64_t N, int32_t R, int64_t capacity_cols) {
-    return expand_pays_strict(T, M, N, R, capacity_cols) || expand_pays_fitted(T, M, N, R, capacity_cols);
+    // the call, a step of 32 kept columns of the workgroup that a compute unit is busy with, a step of a row-block (which one wavefront
+    // walks), a round's 1000 columns, a million outputs; by the tile of X (64, 32, 16 tokens) and the rows of a row-block (to 16, 32, 64)
+    constexpr double kGather[3][3][5] = {
+        {{6.00, 0.0344, 0.198, 2.17, 0.941}, {6.13, 0.0505, 0.310, 2.32, 0.890}, {9.50, 0.431, 0.647, 4.33, 2.58}},
+        {{2.67, 0.0269, 0.257, 2.67, 1.10}, {3.00, 0.0428, 0.293, 2.63, 0.938}, {0.0, 0.140, 0.813, 6.50, 2.48}},
+        {{0.57, 0.0229, 0.278, 1.77, 2.30}, {2.88, 0.0435, 0.291, 1.22, 1.27}, {0.0, 0.124, 0.636, 3.27, 2.29}}};
+    const double *k = kGather[tok == 64 ? 0 : (tok == 32 ? 1 : 2)][R <= 16 ? 0 : (R <= 32 ? 1 : 2)];
+    const int64_t ntiles = (T + tok - 1) / tok, strip = canonical_strip(ntiles, B), wgs = ntiles * ((B + strip - 1) / strip);
+    const int64_t together = 2 * npad * tok * 2 <= 156 * 1024 ? 2 : 1;  // workgroups that share a compute unit
+    const double gather = k[0] + k[1] * (double)((wgs + 255) / 256) * cols / 32.0 * (double)strip / blocks + k[2] * cols / blocks / 32.0 +
+                          k[3] * (double)((wgs + 256 * together - 1) / (256 * together)) * 1e-3 * (double)N + k[4] * out;
+    return (dense < 10.0 ? 10.0 : dense) < 0.88 * gather;
 }
 
 int linear_expand(const void *X, int xdt, int64_t T, int64_t M, int64_t N, int32_t R, const int32_t *blk_cnt,

@@ -33,7 +33,6 @@
 namespace bsp {
 namespace {
 
-constexpr int kMaxStripBlocks = 1024;  // row-blocks per strip (their blk_ptr slice is cached in LDS)
 constexpr int kRing = 4;               // steps of operands in flight per wavefront, canonical kernel
 constexpr int kPlanRing = 8;           // the same for the planned kernels with 8 wavefronts, divided by the fragments per
                                        // step (with 16 wavefronts: 2 steps).  Deeper rings were measured slower (4 to 8
@@ -968,16 +967,10 @@ int launch_canonical(const TiledArgs &a, int waves, hipStream_t s) {
     const size_t lds = tile_bytes<NSUB>(a.npad);
     static thread_local size_t configured = 0;  // per instantiation and thread
     const int64_t ntiles = (a.T + 16 * NSUB - 1) / (16 * NSUB);
-    int64_t nstrips = (256 + ntiles - 1) / ntiles;  // enough strips to give every compute unit a workgroup
-    if (nstrips < 1) nstrips = 1;
     auto kern = linear_tiled_canonical_kernel<DT, NFRAG, NSUB>;
     int st = raise_lds_limit(kern, lds, configured);
     if (st != BSP_OK) return st;
-    const int64_t max_strips = (a.B + 3) / 4;  // never fewer than 4 row-blocks per strip
-    if (nstrips > max_strips) nstrips = max_strips;
-    int64_t rb_per_strip = (a.B + nstrips - 1) / nstrips;
-    if (rb_per_strip > kMaxStripBlocks) rb_per_strip = kMaxStripBlocks;
-    nstrips = (a.B + rb_per_strip - 1) / rb_per_strip;
+    const int64_t rb_per_strip = canonical_strip(ntiles, a.B), nstrips = (a.B + rb_per_strip - 1) / rb_per_strip;
     if (ntiles * nstrips >= ((int64_t)1 << 31)) return BSP_ERR_SHAPE;
     kern<<<dim3((unsigned)(ntiles * nstrips)), dim3((unsigned)(waves * 64)), lds, s>>>(
         a.X, a.T, a.M, a.N, a.R, a.npad, a.blk_ptr, a.col_idx, a.vals, a.bias, a.Y, (int32_t)ntiles,
