@@ -16,7 +16,7 @@
 // column, is one 16-byte read) and the items' 16 columns of dY untransposed (the transposing LDS read delivers the
 // other operand).
 //
-// That form pays where a large layer keeps little and the batch is large (4096 x 1024 at 5x from about 5000 tokens); elsewhere the call is a dense
+// That form pays where a large layer keeps little and the batch is large (4096 x 1024 at 5x, fp32 result, from about 5000 tokens); elsewhere the call is a dense
 // product of which the kept positions are written (bsp_linear_dvals_dense.hip; dvals_dense_pays decides).
 #include "bsp_common.h"
 #include "bsp_linear_internal.h"
